@@ -63,16 +63,25 @@ struct ConvWArgs {
   const bf16 *gy = nullptr;  // padded [V][cout]
   int cout = 0;
   int cin_real = 0;  // input channels that have weights (<= cin)
-  int nchunks = 0;   // brick chunks, one partial sum each
-  float *part = nullptr;   // [nchunks][27][cin_real][cout]
-  float *bpart = nullptr;  // [nchunks][cout]
+  int nchunks = 0;   // voxel chunks, one partial sum each (set by conv_wgrad)
+  float *part = nullptr;   // [nchunks]: [27][cin_real][cout], then the bias [cout]
+};
+
+// How the weight gradient cuts the voxels (conv_wgrad): runs of the (y, x) plane
+// times segments of z, and the LDS areas of one run.
+struct WgradPlan {
+  int64_t nruns = 0, items = 0;  // runs per plane; runs x segments x samples
+  int nzseg = 0, nchunks = 0;
+  int S = 0;  // positions between the staged x rows of neighbouring dy
+  int gy_off = 0, zero_off = 0, lds = 0;  // bytes
 };
 
 int conv_forward(const ConvArgs &a, hipStream_t s);
 // K-steps (4 groups of 8 channels each) of a convolution over cin input
 // channels in the chunk-major order of the packed weights
 int conv_ksteps(int cin);
-int wgrad_chunks(const ConvWArgs &a);
+// floats of ConvWArgs::part
+size_t wgrad_part_floats(const ConvWArgs &a);
 int conv_wgrad(ConvWArgs a, float *gw, float *gb, hipStream_t s);
 int pack_forward(const float *W, int cin_real, int cin_pad, int cout, int ngroups_pad, bf16 *wp,
                  hipStream_t s);

@@ -61,7 +61,7 @@ struct UNet {
        *g3b = nullptr;
   float *gup1 = nullptr, *gskip1 = nullptr, *gup2 = nullptr, *gskip2 = nullptr, *gp2 = nullptr,
         *gp1 = nullptr;
-  float *part = nullptr, *bpart = nullptr, *hpart = nullptr;
+  float *part = nullptr, *hpart = nullptr;
   double *mpart = nullptr;
   int last_nb = 0;
   std::vector<void *> allocs;
@@ -204,9 +204,7 @@ int layer_wgrad(UNet &n, int l, int nb, const bf16 *g, hipStream_t s) {
   w.gy = g;
   w.cout = L.s.cout;
   w.cin_real = L.s.cin_real;
-  w.nchunks = wgrad_chunks(w);
   w.part = n.part;
-  w.bpart = n.bpart;
   return conv_wgrad(w, n.grad + L.wo, n.grad + L.bo, s);
 }
 
@@ -514,7 +512,7 @@ int q1_unet_create(q1_unet **out, int D, int H, int W, int batch, uint64_t seed,
   n.W = W;
   n.B = batch;
   int64_t off = 0;
-  size_t part_cap = 0, bpart_cap = 0;
+  size_t part_cap = 0;
   for (int l = 0; l < 10; ++l) {
     Layer &L = n.L[l];
     L.s = kSpec[l];
@@ -526,12 +524,13 @@ int q1_unet_create(q1_unet **out, int D, int H, int W, int batch, uint64_t seed,
     L.ngroups_b = 27 * L.s.cout / 8;
     L.nchunks_b = conv_ksteps(L.s.cout);
     ConvWArgs w;
-    w.g = n.grid(L.s.level, batch);
     w.cin = L.s.cin;
+    w.cin_real = L.s.cin_real;
     w.cout = L.s.cout;
-    const int nch = wgrad_chunks(w);
-    part_cap = std::max(part_cap, size_t(nch) * 27 * L.s.cin_real * L.s.cout);
-    bpart_cap = std::max(bpart_cap, size_t(nch) * L.s.cout);
+    for (int nb = 1; nb <= batch; ++nb) {  // fewer samples may be cut into more chunks
+      w.g = n.grid(L.s.level, nb);
+      part_cap = std::max(part_cap, wgrad_part_floats(w));
+    }
   }
   n.head_o = off;
   n.nparams = off + 17;
@@ -574,7 +573,6 @@ int q1_unet_create(q1_unet **out, int D, int H, int W, int batch, uint64_t seed,
   A(&n.gp2, v3 * 32);
   A(&n.gp1, v2 * 16);
   A(&n.part, part_cap);
-  A(&n.bpart, bpart_cap);
   A(&n.hpart, size_t(1024) * 17);
   A(&n.mpart, size_t(1024) * 2);
   if (!rc) {
@@ -783,12 +781,10 @@ int q1_conv3d_backward_weight(int B, int D, int H, int W, const uint16_t *a_d, i
   w.g = g;
   w.cout = cout;
   w.cin_real = cin;
-  w.nchunks = wgrad_chunks(w);
-  TmpBuf xp, gp, part, bpart;
+  TmpBuf xp, gp, part;
   Q1_HIP(hipMalloc(&xp.p, size_t(g.voxels()) * cin * sizeof(bf16)));
   Q1_HIP(hipMalloc(&gp.p, size_t(g.voxels()) * cout * sizeof(bf16)));
-  Q1_HIP(hipMalloc(&part.p, size_t(w.nchunks) * 27 * cin * cout * sizeof(float)));
-  Q1_HIP(hipMalloc(&bpart.p, size_t(w.nchunks) * cout * sizeof(float)));
+  Q1_HIP(hipMalloc(&part.p, std::max<size_t>(wgrad_part_floats(w), 1) * sizeof(float)));
   Q1_HIP(hipMemsetAsync(xp.p, 0, size_t(g.voxels()) * cin * sizeof(bf16), s));
   Q1_HIP(hipMemsetAsync(gp.p, 0, size_t(g.voxels()) * cout * sizeof(bf16), s));
   int rc = gather_padded(a_d, ca, up_a, b_d, cb, g, static_cast<bf16 *>(xp.p), s);
@@ -797,7 +793,6 @@ int q1_conv3d_backward_weight(int B, int D, int H, int W, const uint16_t *a_d, i
   w.x = static_cast<bf16 *>(xp.p);
   w.gy = static_cast<bf16 *>(gp.p);
   w.part = static_cast<float *>(part.p);
-  w.bpart = static_cast<float *>(bpart.p);
   if ((rc = conv_wgrad(w, gw_d, gb_d, s))) return rc;
   Q1_HIP(hipStreamSynchronize(s));
   return Q1_OK;
