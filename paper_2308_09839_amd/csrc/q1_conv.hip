@@ -50,161 +50,232 @@ __device__ __forceinline__ bf16x8 ld8(const bf16 *p) {
 
 // ---- convolution forward / backward-data ---------------------------------------
 //
-// A workgroup of four wavefronts computes an 8 x 8 x 4 voxel tile for 16 NB
-// output channels; wavefront w owns the 4 x 4 x 4 sub-tile at
-// (4 (w & 1), 4 (w >> 1)).  The input channels are taken in chunks of CC (16,
-// or 8 for an 8-channel input): the chunk's 10 x 10 x 6 halo tile (600 voxels
-// x CC channels, zero outside the padded grid) is staged in LDS once, and all
-// 27 taps of the chunk read their shifted voxels from there, so each input
-// voxel is loaded from memory once per chunk instead of once per tap; the
-// chunk's weights of the block's row group are staged beside it, so the K
-// loop issues no global loads.  K is
-// ordered chunk-major: chunk cc, then tap, then the 8-channel half h of the
-// chunk; each chunk's 27 (CC/8) groups are padded to whole K-steps of 4
-// groups with zero weights (conv_pack_* writes the matching layout).
+// A workgroup of four wavefronts computes 8 x 8 x 4 voxel tiles, marching in z, for
+// 16 output channels; a wavefront owns two rows of a tile (columns of the
+// instruction: 8 x 2 voxels) and its four slices.  The input channels are taken in
+// chunks of CC (16, or 8 for an 8-channel input): the chunk's 10 x 10 x 6 halo tile
+// (zero outside the padded grid) is staged in LDS once, and all 27 taps of the
+// chunk read their shifted voxels from there, so each input voxel is loaded from
+// memory once per chunk instead of once per tap; the chunk's weights of the block's
+// 16 output channels are staged beside it (once per workgroup when there is one
+// chunk), so the K loop issues no global loads.  The next chunk's loads are in
+// flight, in registers, while a chunk is computed.  K is ordered chunk-major: chunk
+// cc, then tap, then the 8-channel half h of the chunk; each chunk's 27 (CC/8)
+// groups are padded to whole K-steps of 4 groups with zero weights (k_pack_* write
+// the matching layout).
+//
+// The K loop is unrolled: a K-step's lane address is one of KSC registers set up
+// once (which of the step's taps a lane reads depends on its K-block only) plus an
+// immediate offset, so a step is five 16-byte LDS reads, issued one step ahead, and
+// four matrix instructions, with no index arithmetic.
+//
+// LDS banks: a 16-byte read serves lanes {0-3, 12-15, 20-23, 24-27}, then {4-11,
+// 16-19, 28-31}, then the same of the upper half in one pass over the 256 B of the
+// banks each (found from conflict counts).  So that neither group repeats a bank,
+// the halves of a voxel lie in planes a multiple of 256 B apart, 8 voxels of a row
+// contiguous in each, and a wavefront's two rows are w and w + 4: 640 B = 128 B
+// modulo 256.  Rows 2w and 2w + 1 of interleaved halves kept the LDS busy 1.7 times
+// as long.
+//
+// What bounds it: the LDS reads (1.25 KB per matrix instruction) on the finest
+// level, the halo tiles' traffic and FP32 stores elsewhere.  68^3, ten layers:
+// batch 1 136 us, batch 4 316 us forward and 353 us backward-data; before (index
+// arithmetic in the loop, conflicts, one tile per workgroup, tiles dealt round the
+// XCDs so that no L2 saw a neighbour's halo) 200, 500 and 485 us.  Measured and
+// dropped: 32 output channels per wavefront (within 5% either way), 2 and 8
+// slices per tile.
 
-constexpr int kTX = 8, kTY = 8, kTZ = 4;                 // output tile of a workgroup
-constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2;  // its halo tile
-constexpr int kHV = kHX * kHY * kHZ;                     // 600 voxels
+constexpr int kTX = 8, kTY = 8, kTZ = 4;     // output tile of a workgroup
+constexpr int kHX = kTX + 2, kHY = kTY + 2;  // its halo tile
 
-template <int NB, int CC>  // NB = 16-channel row blocks per wavefront, CC = staged channels
-__global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs a) {
-  constexpr int HG = CC / 8;                  // 8-channel groups per voxel and chunk
-  constexpr int KSC = (27 * HG + 3) / 4;      // K-steps per chunk
-  constexpr int ITEMS = (kHV * HG + 255) / 256;  // 16-byte input staging items per thread
-  constexpr int WROWS = 16 * NB;              // weight rows (output channels) of the block
-  constexpr int WITEMS = (KSC * 4 * WROWS + 255) / 256;  // 16-byte weight items per thread
-  __shared__ __align__(16) bf16 sx[kHV * CC];
-  __shared__ __align__(16) bf16 sw[KSC * 4 * WROWS * 8];  // the chunk's weights [ks][kg][row][8]
+template <int CC>  // staged channels
+__global__ __launch_bounds__(256, 3) void k_conv_fwd(ConvArgs a, int nseg) {
+  constexpr int TZ = kTZ, HG = CC / 8;      // slices; 8-channel groups per voxel and chunk
+  constexpr int NR = kHY * (TZ + 2);        // x rows of the halo tile
+  constexpr int HV = kHX * NR;              // voxels
+  constexpr int HP = (HV + 15) & ~15;       // voxels of a half's plane (whole 256 B)
+  constexpr int KSC = (27 * HG + 3) / 4;    // K-steps per chunk
+  constexpr int IPR = kHX * HG;             // 16-byte staging items per row
+  constexpr int RPP = 256 / IPR;            // rows per staging pass (the threads past them idle)
+  constexpr int PASSES = (NR + RPP - 1) / RPP;
+  constexpr int NW = KSC * 4 * 16;          // 16-byte weight items per chunk
+  constexpr int WITEMS = (NW + 255) / 256;  // per thread
+  __shared__ __align__(16) bf16 sx[HP * CC];  // [h][voxel][8]
+  __shared__ __align__(16) bf16 sw[NW * 8];   // the chunk's weights [ks][kg][row][8]
   const PGrid g = a.g;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int TX = (g.W + kTX - 1) / kTX, TY = (g.H + kTY - 1) / kTY, TZ = (g.D + kTZ - 1) / kTZ;
-  const int nrg = a.cout / (16 * NB);
-  int64_t t = blockIdx.x;
-  const int rg = int(t % nrg);
-  t /= nrg;
-  const int tx = int(t % TX);
-  t /= TX;
-  const int ty = int(t % TY);
-  t /= TY;
-  const int tz = int(t % TZ);
-  const int b = int(t / TZ);
+  const int TX = (g.W + kTX - 1) / kTX, TY = (g.H + kTY - 1) / kTY, TZn = (g.D + TZ - 1) / TZ;
+  const int nrg = a.cout / 16;
+  // each XCD takes a contiguous range of the tiles, whose halos then share its L2
+  unsigned t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int rg = int(t % unsigned(nrg));
+  t /= unsigned(nrg);
+  const int tx = int(t % unsigned(TX));
+  t /= unsigned(TX);
+  const int ty = int(t % unsigned(TY));
+  t /= unsigned(TY);
+  const int seg = int(t % unsigned(nseg));
+  const int b = int(t / unsigned(nseg));
   if (b >= g.B) return;
-  const int x0 = tx * kTX, y0 = ty * kTY, z0 = tz * kTZ;  // logical origin; halo (0,0,0) is
-                                                          // padded voxel (z0, y0, x0)
+  const int x0 = tx * kTX, y0 = ty * kTY;  // logical origin; halo (0,0,0) is padded voxel
+                                           // (z0, y0, x0)
+  // z tiles [t0, t1): the first TZn % nseg segments have one tile more
+  const int tq = TZn / nseg, tr = TZn - tq * nseg;
+  const int t0 = tq * seg + min(seg, tr), t1 = t0 + tq + (seg < tr ? 1 : 0);
   const int kg = lane >> 4, j = lane & 15;
-  const int vx = (w & 1) * 4 + (j & 3), vy = (w >> 1) * 4 + (j >> 2);  // in the tile
+  const int vx = j & 7, vy = w + 4 * (j >> 3);  // in the tile
 
-  f32x4 acc[NB][kTZ];
+  // this thread's staging items: 8 channels (half h) of voxel hx of rows r0, r0 + RPP, ...
+  // of the halo tile; voxels outside the padded grid read the first voxel of their
+  // slice's halo, which is zero
+  const int64_t plane = int64_t(g.Hp) * g.Wp;
+  const bf16 *xb = a.x + (int64_t(b) * g.Dp + int64_t(t0) * TZ) * plane * a.cin;
+  const int r0 = tid / IPR, hx = (tid - r0 * IPR) / HG, h = tid % HG;
+  unsigned xo[PASSES];  // voxel offsets from slice z0
 #pragma unroll
-  for (int r = 0; r < NB; ++r)
-#pragma unroll
-    for (int z = 0; z < kTZ; ++z) acc[r][z] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int nchunk = a.cin / CC;
-  for (int cc = 0; cc < nchunk; ++cc) {
-    if (cc) __syncthreads();  // the previous chunk's reads are done
-    u16x8 stage[ITEMS], wst[WITEMS];
-#pragma unroll
-    for (int k = 0; k < WITEMS; ++k) {  // the chunk's weights of this row group
-      const int it = k * 256 + tid;
-      wst[k] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      if (it < KSC * 4 * WROWS) {
-        const int row = it % WROWS, q = it / WROWS;  // q = ks * 4 + kg
-        wst[k] = *reinterpret_cast<const u16x8 *>(
-            a.wp + ((size_t(cc) * KSC * 4 + q) * a.cout + rg * WROWS + row) * 8);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {  // all loads issued before any LDS write
-      const int it = k * 256 + tid;
-      stage[k] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      if (it < kHV * HG) {
-        const int v = it / HG, h = it - v * HG;
-        const int hx = v % kHX, hy = (v / kHX) % kHY, hz = v / (kHX * kHY);
-        const int px = x0 + hx, py = y0 + hy, pz = z0 + hz;
-        if (px < g.Wp && py < g.Hp && pz < g.Dp)
-          stage[k] = *reinterpret_cast<const u16x8 *>(
-              a.x + (((int64_t(b) * g.Dp + pz) * g.Hp + py) * g.Wp + px) * a.cin + cc * CC + h * 8);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-      const int it = k * 256 + tid;
-      if (it < kHV * HG) *reinterpret_cast<u16x8 *>(sx + it * 8) = stage[k];
-    }
-#pragma unroll
-    for (int k = 0; k < WITEMS; ++k) {
-      const int it = k * 256 + tid;
-      if (it < KSC * 4 * WROWS) *reinterpret_cast<u16x8 *>(sw + it * 8) = wst[k];
-    }
-    __syncthreads();
-#pragma unroll 2
-    for (int ks = 0; ks < KSC; ++ks) {
-      const int G = 4 * ks + kg;
-      const bool real = G < 27 * HG;  // padding groups have zero weights
-      const int tap = real ? G / HG : 13, h = real ? G - (G / HG) * HG : 0;
-      const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-      bf16x8 wv[NB], xv[kTZ];
-#pragma unroll
-      for (int r = 0; r < NB; ++r)
-        wv[r] = *reinterpret_cast<const bf16x8 *>(sw + ((ks * 4 + kg) * WROWS + r * 16 + j) * 8);
-#pragma unroll
-      for (int zb = 0; zb < kTZ; ++zb)
-        xv[zb] = *reinterpret_cast<const bf16x8 *>(
-            sx + (((zb + dz) * kHY + (vy + dy)) * kHX + (vx + dx)) * CC + h * 8);
-#pragma unroll
-      for (int r = 0; r < NB; ++r)
-#pragma unroll
-        for (int zb = 0; zb < kTZ; ++zb)
-          acc[r][zb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[r], xv[zb], acc[r][zb], 0, 0, 0);
-    }
+  for (int k = 0; k < PASSES; ++k) {
+    const int r = min(r0 + k * RPP, NR - 1), hz = r / kHY, py = y0 + r - hz * kHY;
+    xo[k] = x0 + hx < g.Wp && py < g.Hp ? unsigned((hz * g.Hp + py) * g.Wp + x0 + hx) : 0u;
   }
-  // epilogue: lane holds output channels r*16 + 4*kg + i of voxel (x, y, z0 + zb)
-  const int ox = x0 + vx, oy = y0 + vy;
-  if (ox >= g.W || oy >= g.H) return;
-  const PGrid f = g.twice();
+  bf16 *sxw = sx + (h * HP + r0 * kHX + hx) * 8;
+  const bool stager = tid < RPP * IPR;
+  const bf16 *wb = a.wp + (rg * 16 + size_t(tid / 16) * a.cout + tid % 16) * 8;
+  u16x8 xs[PASSES], ws[WITEMS];
+  auto load_x = [&](const bf16 *x) {
 #pragma unroll
-  for (int zb = 0; zb < kTZ; ++zb) {
-    const int z = z0 + zb;
-    if (z >= g.D) break;
-    const int64_t vox = g.at(b, z, oy, ox);
-    for (int r = 0; r < NB; ++r) {
-      const int c0 = (rg * NB + r) * 16 + kg * 4;
+    for (int k = 0; k < PASSES; ++k)
+      xs[k] = *reinterpret_cast<const u16x8 *>(x + uint64_t(xo[k]) * unsigned(a.cin));
+  };
+  auto load_w = [&](int cc) {
+#pragma unroll
+    for (int k = 0; k < WITEMS; ++k) {  // [q][row] of this row group, q = ks * 4 + kg
+      const int q = NW % 256 == 0 || k < WITEMS - 1 || tid < NW % 256 ? k * 16 : 0;
+      ws[k] = *reinterpret_cast<const u16x8 *>(wb + size_t(cc * KSC * 4 + q) * a.cout * 8);
+    }
+  };
+  // lane address of K-step ks: group G = 4 ks + kg is (tap, h); padding groups (zero
+  // weights) read the centre tap
+  int ax[KSC];
+#pragma unroll
+  for (int ks = 0; ks < KSC; ++ks) {
+    int off[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int G = 4 * ks + q, tap = G < 27 * HG ? G / HG : 13, hh = G < 27 * HG ? G % HG : 0;
+      off[q] = hh * HP + ((tap / 9) * kHY + (tap / 3) % 3) * kHX + tap % 3;
+    }
+    const int o = kg < 2 ? (kg == 0 ? off[0] : off[1]) : (kg == 2 ? off[2] : off[3]);
+    ax[ks] = (o + vy * kHX + vx) * 8;
+  }
+  const bf16 *swl = sw + (kg * 16 + j) * 8;
+
+  // this lane's outputs: channels c + i of voxel (x, y, z0 + zb)
+  const int ox = x0 + vx, oy = y0 + vy, c = rg * 16 + kg * 4;
+  const bool inside = ox < g.W && oy < g.H;
+  int64_t vox = g.at(b, t0 * TZ, inside ? oy : 0, inside ? ox : 0);
+  float bias[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) bias[i] = a.bias ? a.bias[c + i] : 0.f;
+  f32x4 acc[TZ];
+  const int nchunk = a.cin / CC;
+  // outputs of z tile tz from the accumulators
+  auto store = [&](int tz) {
+    const int z0 = tz * TZ;
+    const int nz = inside ? min(TZ, g.D - z0) : 0;
+#pragma unroll
+    for (int zb = 0; zb < TZ; ++zb) {
+      if (zb >= nz) break;
       float v[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] = acc[r][zb][i] + (a.bias ? a.bias[c0 + i] : 0.f);
-        if (a.relu) v[i] = fmaxf(v[i], 0.f);
-      }
-      if (a.mask.p) {
-        const bf16 *m = a.mask.p + vox * a.mask.cs + a.mask.co + c0;
+      for (int i = 0; i < 4; ++i) v[i] = acc[zb][i] + bias[i];
+      if (a.relu)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (!(bf2f(m[i]) > 0.f)) v[i] = 0.f;
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+      if (a.mask.p) {
+        const ushort4 m =
+            *reinterpret_cast<const ushort4 *>(a.mask.p + vox * a.mask.cs + a.mask.co + c);
+        if (!(bf2f(m.x) > 0.f)) v[0] = 0.f;
+        if (!(bf2f(m.y) > 0.f)) v[1] = 0.f;
+        if (!(bf2f(m.z) > 0.f)) v[2] = 0.f;
+        if (!(bf2f(m.w) > 0.f)) v[3] = 0.f;
       }
       if (a.out.p) {
         const ushort4 o{f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
         if (!a.out_up) {
-          *reinterpret_cast<ushort4 *>(a.out.p + vox * a.out.cs + a.out.co + c0) = o;
+          *reinterpret_cast<ushort4 *>(a.out.p + vox * a.out.cs + a.out.co + c) = o;
         } else {
+          const PGrid f = g.twice();
+          bf16 *p = a.out.p + f.at(b, 2 * (z0 + zb), 2 * oy, 2 * ox) * a.out.cs + a.out.co + c;
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int64_t fv = f.at(b, 2 * z + (k >> 2), 2 * oy + ((k >> 1) & 1), 2 * ox + (k & 1));
-            *reinterpret_cast<ushort4 *>(a.out.p + fv * a.out.cs + a.out.co + c0) = o;
-          }
+          for (int k = 0; k < 8; ++k)
+            *reinterpret_cast<ushort4 *>(
+                p + ((int64_t(k >> 2) * f.Hp + ((k >> 1) & 1)) * f.Wp + (k & 1)) * a.out.cs) = o;
         }
       }
       if (a.o32) {
         const float4 o{v[0], v[1], v[2], v[3]};
         if (a.split == 0)
-          *reinterpret_cast<float4 *>(a.o32 + vox * a.cout + c0) = o;
-        else if (c0 < a.split)
-          *reinterpret_cast<float4 *>(a.o32 + vox * a.split + c0) = o;
+          *reinterpret_cast<float4 *>(a.o32 + vox * a.cout + c) = o;
+        else if (c < a.split)
+          *reinterpret_cast<float4 *>(a.o32 + vox * a.split + c) = o;
         else
-          *reinterpret_cast<float4 *>(a.o32b + vox * (a.cout - a.split) + (c0 - a.split)) = o;
+          *reinterpret_cast<float4 *>(a.o32b + vox * (a.cout - a.split) + (c - a.split)) = o;
       }
+      vox += plane;
+    }
+  };
+  load_w(0);
+  load_x(xb + h * 8);
+  int cc = 0, done = -1;  // done: a finished tile whose outputs are still in acc
+  for (int tz = t0; tz < t1;) {
+    if (done >= 0 || cc) __syncthreads();  // the previous chunk's reads are done
+    if (nchunk > 1 || tz == t0)
+#pragma unroll
+      for (int k = 0; k < WITEMS; ++k)
+        if (NW % 256 == 0 || k < WITEMS - 1 || tid < NW % 256)
+          *reinterpret_cast<u16x8 *>(sw + (k * 256 + tid) * 8) = ws[k];
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k)
+      if (stager && (NR % RPP == 0 || k < PASSES - 1 || r0 + k * RPP < NR))
+        *reinterpret_cast<u16x8 *>(sxw + k * RPP * kHX * 8) = xs[k];
+    __syncthreads();
+    // The finished tile's stores go out here, before the next loads: loads and
+    // stores complete in order on one counter, so a store issued after the loads
+    // would have to land before the next staging, with no work to cover it.
+    if (done >= 0) store(done);
+    done = -1;
+    const bool first = cc == 0;
+    if (++cc == nchunk) {
+      done = tz++;
+      cc = 0;
+      xb += TZ * plane * a.cin;
+    }
+    if (tz < t1) {  // the next chunk, or the next tile's first
+      if (nchunk > 1) load_w(cc);
+      load_x(xb + cc * CC + h * 8);
+    }
+    if (first)
+#pragma unroll
+      for (int zb = 0; zb < TZ; ++zb) acc[zb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 wv[2], xv[2][TZ];  // operands, read one K-step ahead of their use
+    auto read = [&](int ks) {
+      wv[ks & 1] = *reinterpret_cast<const bf16x8 *>(swl + ks * 4 * 16 * 8);
+#pragma unroll
+      for (int zb = 0; zb < TZ; ++zb)
+        xv[ks & 1][zb] = *reinterpret_cast<const bf16x8 *>(sx + ax[ks] + zb * kHX * kHY * 8);
+    };
+    read(0);
+#pragma unroll
+    for (int ks = 0; ks < KSC; ++ks) {
+      if (ks + 1 < KSC) read(ks + 1);
+#pragma unroll
+      for (int zb = 0; zb < TZ; ++zb)
+        acc[zb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[ks & 1], xv[ks & 1][zb], acc[zb],
+                                                          0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
+  if (done >= 0) store(done);
 }
 
 // ---- convolution backward-weight ---------------------------------------------------
@@ -771,24 +842,19 @@ int conv_forward(const ConvArgs &a, hipStream_t s) {
            a.nchunks, a.cin);
   Q1_CHECK(a.cout % 16 == 0 && a.cout >= 16 && a.cout <= 96, Q1_EUNSUPPORTED,
            "conv: %d output channels (16, 32, 48, 64, 96)", a.cout);
-  const int64_t tiles = int64_t(a.g.B) * ((a.g.D + kTZ - 1) / kTZ) * ((a.g.H + kTY - 1) / kTY) *
-                        ((a.g.W + kTX - 1) / kTX);
-  // row blocks per wavefront: all of them when that still gives 512 workgroups,
-  // else fewer (more workgroups, each staging its input tile once more)
-  // (the chunk's weights of two row blocks fill 28 KB of LDS beside the 19 KB input tile)
-  const int rb = a.cout / 16;
-  const int nb = rb % 2 == 0 && tiles * (rb / 2) >= 512 ? 2 : 1;
-  const unsigned blocks = unsigned(tiles * (rb / nb));
-  auto launch = [&](auto k8, auto k16) {
-    if (a.cin == 8)
-      hipLaunchKernelGGL(k8, dim3(blocks), dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL(k16, dim3(blocks), dim3(256), 0, s, a);
-  };
-  if (nb == 2)
-    launch(k_conv_fwd<2, 8>, k_conv_fwd<2, 16>);
+  // z segments: about 2,048 workgroups (three to a compute unit run at once; fewer,
+  // longer marches save weight loads and index set-up but leave uneven last rounds:
+  // batch 4 at 68^3 670 us of convolutions against 723 with 768 workgroups and 744
+  // with one tile each)
+  const int64_t cols = int64_t(a.g.B) * ((a.g.H + kTY - 1) / kTY) *
+                       ((a.g.W + kTX - 1) / kTX) * (a.cout / 16);
+  const int nzt = (a.g.D + kTZ - 1) / kTZ;
+  const int nseg = int(std::min<int64_t>(nzt, (2048 + cols - 1) / cols));
+  const dim3 blocks(unsigned((cols * nseg + 7) / 8 * 8));
+  if (a.cin == 8)
+    hipLaunchKernelGGL(k_conv_fwd<8>, blocks, dim3(256), 0, s, a, nseg);
   else
-    launch(k_conv_fwd<1, 8>, k_conv_fwd<1, 16>);
+    hipLaunchKernelGGL(k_conv_fwd<16>, blocks, dim3(256), 0, s, a, nseg);
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
