@@ -578,149 +578,226 @@ int conv_ksteps(int cin) {
   return (cin / k.CC) * k.KSC;
 }
 
-// forward: wp[q][co][jj] = W[tap][c + jj][co] for group q = (tap, c) of the
-// chunk-major order over cin_pad channels; zero for padding groups and
-// channels past cin_real.  W is [27][cin_real][cout] FP32.
-__global__ void k_pack_fwd(const float *__restrict__ W, int cin_real, int cin_pad, int cout,
-                           int ngroups_pad, bf16 *__restrict__ wp) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t n = int64_t(ngroups_pad) * cout * 8;
-  if (i >= n) return;
+// One launch packs the weights of up to kMaxPack convolutions (a network's forward and
+// backward-data forms: a launch each had cost 3.7 us, 20 times).  Forward:
+// wp[q][co][jj] = W[tap][c + jj][co] for group q = (tap, c) of the chunk-major order
+// over cin_pad channels; zero for padding groups and channels past cin_real; W is
+// [27][cin_real][cout] FP32.  Backward-data: the correlation with reversed taps and
+// swapped channels over an input of cout channels (the forward's outputs), output ci:
+// wq[q][ci][jj] = W[26 - tap][ci][c + jj].
+__global__ __launch_bounds__(256) void k_pack(PackJobs jobs) {
+  int n = 0;
+  while (n + 1 < jobs.n && blockIdx.x >= jobs.j[n + 1].block0) ++n;
+  const PackJob &p = jobs.j[n];
+  const int rows = p.bwd ? p.cin_real : p.cout;
+  const unsigned i = (blockIdx.x - p.block0) * 256 + threadIdx.x;
+  if (i >= unsigned(p.groups) * rows * 8) return;
   const int jj = int(i & 7);
-  const int co = int((i >> 3) % cout);
-  const int q = int((i >> 3) / cout);
+  const int row = int((i >> 3) % unsigned(rows)), q = int((i >> 3) / unsigned(rows));
   int tap, c;
-  KOrder(cin_pad).group(q, tap, c);
+  KOrder(p.bwd ? p.cout : p.cin_pad).group(q, tap, c);
   c += jj;
-  const float v = (tap < 27 && c < cin_real) ? W[(size_t(tap) * cin_real + c) * cout + co] : 0.f;
-  wp[i] = f2bf(v);
-}
-
-// backward-data: the correlation with reversed taps and swapped channels over
-// an input of cout channels (the forward's outputs), output ci:
-// wq[q][ci][jj] = W[26 - tap][ci][c + jj] for group q = (tap, c).
-__global__ void k_pack_bwd(const float *__restrict__ W, int cin, int cout, int ngroups_pad,
-                           bf16 *__restrict__ wq) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t n = int64_t(ngroups_pad) * cin * 8;
-  if (i >= n) return;
-  const int jj = int(i & 7);
-  const int ci = int((i >> 3) % cin);
-  const int q = int((i >> 3) / cin);
-  int tap, c;
-  KOrder(cout).group(q, tap, c);
-  c += jj;
-  const float v = tap < 27 ? W[(size_t(26 - tap) * cin + ci) * cout + c] : 0.f;
-  wq[i] = f2bf(v);
+  float v = 0.f;
+  if (tap < 27) {
+    if (p.bwd)
+      v = p.W[(size_t(26 - tap) * p.cin_real + row) * p.cout + c];
+    else if (c < p.cin_real)
+      v = p.W[(size_t(tap) * p.cin_real + c) * p.cout + row];
+  }
+  p.out[i] = f2bf(v);
 }
 
 // ---- layout changes, pooling, upsampling adjoints, masks ------------------------------
 
-// decompose a logical element index over [B][D][H][W][C]
-struct Elem {
-  int b, z, y, x, c;
+// A block per x row (b, z, y) of the grid: the row's index is split by scalar
+// divisions once per block, the threads take its 8-channel items (16-byte loads and
+// stores).  Per-element 64-bit divisions had bound these kernels: 68^3 batch 4, the
+// 16-channel adjoint of the pooling 61 us, 29 so, of which its 160 MB take most.
+struct Row {
+  int b, z, y;
+  __device__ Row(const PGrid &g, unsigned r) {
+    const unsigned q = r / unsigned(g.H);
+    y = int(r - q * unsigned(g.H));
+    b = int(q / unsigned(g.D));
+    z = int(q - unsigned(b) * unsigned(g.D));
+  }
 };
-__device__ __forceinline__ Elem decompose(int64_t i, const PGrid &g, int C) {
-  Elem e;
-  e.c = int(i % C);
-  int64_t v = i / C;
-  e.x = int(v % g.W);
-  v /= g.W;
-  e.y = int(v % g.H);
-  v /= g.H;
-  e.z = int(v % g.D);
-  e.b = int(v / g.D);
-  return e;
-}
+// the rows of a block: its own index, then every gridDim.x-th (grids are capped)
+#define Q1_FOR_ROWS(row, rows) \
+  for (unsigned row = blockIdx.x; row < (rows); row += gridDim.x)
 
-// padded concatenation of unpadded a (half grid when up_a) and b, 8 channels per thread
+struct F8 {
+  float v[8];
+};
+__device__ __forceinline__ F8 ldf8(const float *p) {
+  F8 r;
+  *reinterpret_cast<float4 *>(r.v) = *reinterpret_cast<const float4 *>(p);
+  *reinterpret_cast<float4 *>(r.v + 4) = *reinterpret_cast<const float4 *>(p + 4);
+  return r;
+}
+__device__ __forceinline__ u16x8 ldu8(const bf16 *p) { return *reinterpret_cast<const u16x8 *>(p); }
+
+// Item i of a flat sweep over voxels x C8 items: the voxel's coordinates and the item
+// (32-bit divisions while the sweep is that short).  For rows too short to fill a
+// block: a row of 68 items per block took 6.2 us at 68^3 where this takes 5.2.
+struct Item {
+  int b, z, y, x, c;
+  __device__ Item(uint64_t i, uint64_t n, unsigned C8, const PGrid &g) {
+    uint64_t v;
+    if (n >> 32) {
+      v = i / C8;
+      c = int(i - v * C8) * 8;
+    } else {
+      const unsigned u = unsigned(i) / C8;
+      c = int(unsigned(i) - u * C8) * 8;
+      v = u;
+    }
+    const unsigned w = unsigned(v), q = w / unsigned(g.W), p = q / unsigned(g.H);
+    x = int(w - q * unsigned(g.W));
+    y = int(q - p * unsigned(g.H));
+    b = int(p / unsigned(g.D));
+    z = int(p - unsigned(b) * unsigned(g.D));
+  }
+};
+
+// padded concatenation of unpadded a (half grid when up_a) and b (either may be
+// aligned to one element only: ALIGNED says whether both allow 16-byte loads)
+template <bool ALIGNED>
 __global__ void k_gather_padded(const bf16 *__restrict__ a, int ca, int up_a,
                                 const bf16 *__restrict__ b, int cb, PGrid g,
-                                bf16 *__restrict__ out) {
-  const int C8 = (ca + cb) >> 3;
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= int64_t(g.B) * g.D * g.H * g.W * C8) return;
-  const Elem e = decompose(i, g, C8);
-  const int c = e.c * 8;
+                                bf16 *__restrict__ out, uint64_t n) {
+  const uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const Item e(i, n, unsigned(ca + cb) >> 3, g);
   const bf16 *src;
-  if (c < ca) {
-    if (up_a) {
-      const int Dc = g.D / 2, Hc = g.H / 2, Wc = g.W / 2;
-      src = a + ((((int64_t)e.b * Dc + (e.z >> 1)) * Hc + (e.y >> 1)) * Wc + (e.x >> 1)) * ca + c;
-    } else {
-      src = a + ((((int64_t)e.b * g.D + e.z) * g.H + e.y) * g.W + e.x) * ca + c;
-    }
+  if (e.c < ca) {
+    const int64_t v = up_a ? ((int64_t(e.b) * (g.D / 2) + (e.z >> 1)) * (g.H / 2) + (e.y >> 1)) *
+                                     (g.W / 2) + (e.x >> 1)
+                           : ((int64_t(e.b) * g.D + e.z) * g.H + e.y) * g.W + e.x;
+    src = a + v * ca + e.c;
   } else {
-    src = b + ((((int64_t)e.b * g.D + e.z) * g.H + e.y) * g.W + e.x) * cb + (c - ca);
+    src = b + (((int64_t(e.b) * g.D + e.z) * g.H + e.y) * g.W + e.x) * cb + (e.c - ca);
   }
-  *reinterpret_cast<uint4 *>(out + g.at(e.b, e.z, e.y, e.x) * (ca + cb) + c) =
-      *reinterpret_cast<const uint4 *>(src);
+  u16x8 v;
+  if constexpr (ALIGNED) {
+    v = ldu8(src);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = src[k];
+  }
+  *reinterpret_cast<u16x8 *>(out + g.at(e.b, e.z, e.y, e.x) * (ca + cb) + e.c) = v;
 }
 
-__global__ void k_unpad_f32(const float *__restrict__ in, PGrid g, int C, float *__restrict__ out) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= int64_t(g.B) * g.D * g.H * g.W * C) return;
-  const Elem e = decompose(i, g, C);
-  out[i] = in[g.at(e.b, e.z, e.y, e.x) * C + e.c];
+// C a multiple of 8; out (the caller's) aligned to one float only
+__global__ void k_unpad_f32(const float *__restrict__ in, PGrid g, int C, float *__restrict__ out,
+                            unsigned rows) {
+  Q1_FOR_ROWS(row, rows) {
+    const Row r(g, row);
+    const float *p = in + g.at(r.b, r.z, r.y, 0) * C;
+    float *o = out + ((int64_t(r.b) * g.D + r.z) * g.H + r.y) * g.W * C;
+    const int64_t n = int64_t(g.W) * C;
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) o[i] = p[i];
+  }
 }
 
 // 2x2x2 average pooling of a channel window into a padded coarse tensor [C]
-__global__ void k_pool2(Slice in, PGrid f, int C, bf16 *__restrict__ out) {
+__global__ void k_pool2(Slice in, PGrid f, int C, bf16 *__restrict__ out, uint64_t n) {
   const PGrid g = f.half();
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= int64_t(g.B) * g.D * g.H * g.W * C) return;
-  const Elem e = decompose(i, g, C);
-  float s = 0.f;
+  const uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const Item e(i, n, unsigned(C) >> 3, g);
+  const bf16 *p = in.p + f.at(e.b, 2 * e.z, 2 * e.y, 2 * e.x) * in.cs + in.co + e.c;
+  u16x8 v[8], w;
 #pragma unroll
   for (int k = 0; k < 8; ++k)
-    s += bf2f(in.p[f.at(e.b, 2 * e.z + (k >> 2), 2 * e.y + ((k >> 1) & 1), 2 * e.x + (k & 1)) * in.cs +
-                   in.co + e.c]);
-  out[g.at(e.b, e.z, e.y, e.x) * C + e.c] = f2bf(s * 0.125f);
+    v[k] = ldu8(p + ((int64_t(k >> 2) * f.Hp + ((k >> 1) & 1)) * f.Wp + (k & 1)) * in.cs);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += bf2f(v[k][c]);
+    w[c] = f2bf(s * 0.125f);
+  }
+  *reinterpret_cast<u16x8 *>(out + g.at(e.b, e.z, e.y, e.x) * C + e.c) = w;
 }
 
 // coarse gpre = (sum of the 8 children of gup) * (mask > 0); gup FP32 padded fine [C];
 // the mask is the coarse activation, stored upsampled (read at the first child)
 __global__ void k_up_adjoint_mask(const float *__restrict__ gup, Slice mask, PGrid g, int C,
-                                  bf16 *__restrict__ out) {
+                                  bf16 *__restrict__ out, unsigned rows) {
   const PGrid f = g.twice();
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= int64_t(g.B) * g.D * g.H * g.W * C) return;
-  const Elem e = decompose(i, g, C);
-  float s = 0.f;
+  Q1_FOR_ROWS(row, rows) {
+    const Row r(g, row);
+    const unsigned C8 = unsigned(C) >> 3;
+    bf16 *o = out + g.at(r.b, r.z, r.y, 0) * C;
+    for (unsigned i = threadIdx.x; i < unsigned(g.W) * C8; i += blockDim.x) {
+      const unsigned x = i / C8;
+      const int c0 = int(i - x * C8) * 8;
+      const int64_t v = f.at(r.b, 2 * r.z, 2 * r.y, 2 * int(x));
+      const u16x8 m = ldu8(mask.p + v * mask.cs + mask.co + c0);
+      F8 ch[8];
 #pragma unroll
-  for (int k = 0; k < 8; ++k)
-    s += gup[f.at(e.b, 2 * e.z + (k >> 2), 2 * e.y + ((k >> 1) & 1), 2 * e.x + (k & 1)) * C + e.c];
-  const float m = bf2f(mask.p[f.at(e.b, 2 * e.z, 2 * e.y, 2 * e.x) * mask.cs + mask.co + e.c]);
-  out[g.at(e.b, e.z, e.y, e.x) * C + e.c] = f2bf(m > 0.f ? s : 0.f);
+      for (int k = 0; k < 8; ++k)
+        ch[k] = ldf8(gup + (v + (int64_t(k >> 2) * f.Hp + ((k >> 1) & 1)) * f.Wp + (k & 1)) * C + c0);
+      u16x8 w;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += ch[k].v[c];
+        w[c] = f2bf(bf2f(m[c]) > 0.f ? s : 0.f);
+      }
+      *reinterpret_cast<u16x8 *>(o + int64_t(i) * 8) = w;
+    }
+  }
 }
 
 // fine gpre = (gskip + gp[parent] / 8) * (mask > 0), all padded
 __global__ void k_pool_adjoint_add_mask(const float *__restrict__ gskip,
                                         const float *__restrict__ gp, Slice mask, PGrid f, int C,
-                                        bf16 *__restrict__ out) {
+                                        bf16 *__restrict__ out, unsigned rows) {
   const PGrid g = f.half();
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= int64_t(f.B) * f.D * f.H * f.W * C) return;
-  const Elem e = decompose(i, f, C);
-  const int64_t v = f.at(e.b, e.z, e.y, e.x);
-  const float s = gskip[v * C + e.c] + 0.125f * gp[g.at(e.b, e.z >> 1, e.y >> 1, e.x >> 1) * C + e.c];
-  const float m = bf2f(mask.p[v * mask.cs + mask.co + e.c]);
-  out[v * C + e.c] = f2bf(m > 0.f ? s : 0.f);
+  Q1_FOR_ROWS(row, rows) {
+    const Row r(f, row);
+    const unsigned C8 = unsigned(C) >> 3;
+    const int64_t v0 = f.at(r.b, r.z, r.y, 0), p0 = g.at(r.b, r.z >> 1, r.y >> 1, 0);
+    for (unsigned i = threadIdx.x; i < unsigned(f.W) * C8; i += blockDim.x) {
+      const unsigned x = i / C8;
+      const int c0 = int(i - x * C8) * 8;
+      const F8 a = ldf8(gskip + v0 * C + int64_t(i) * 8), p = ldf8(gp + (p0 + (x >> 1)) * C + c0);
+      const u16x8 m = ldu8(mask.p + (v0 + x) * mask.cs + mask.co + c0);
+      u16x8 w;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const float s = a.v[c] + 0.125f * p.v[c];
+        w[c] = f2bf(bf2f(m[c]) > 0.f ? s : 0.f);
+      }
+      *reinterpret_cast<u16x8 *>(out + v0 * C + int64_t(i) * 8) = w;
+    }
+  }
 }
 
 // ---- head, loss -------------------------------------------------------------------------
 
+// padded voxel of logical voxel i (32-bit divisions: a grid that fits the memory has
+// fewer than 2^32 voxels)
+__device__ __forceinline__ int64_t padded_voxel(unsigned i, const PGrid &g) {
+  const unsigned q = i / unsigned(g.W), p = q / unsigned(g.H), b = p / unsigned(g.D);
+  return g.at(int(b), int(p - b * unsigned(g.D)), int(q - p * unsigned(g.H)),
+              int(i - q * unsigned(g.W)));
+}
+
 // out[b][z][y][x] (unpadded) = sum_c t[v][c] wh[c] + bh, t padded [16]
-__global__ void k_head_fwd(const bf16 *__restrict__ t, PGrid g, const float *__restrict__ wh,
-                           float *__restrict__ out) {
+__global__ void k_head_fwd(const bf16 *__restrict__ t, PGrid g, unsigned nv,
+                           const float *__restrict__ wh, float *__restrict__ out) {
   constexpr int C = 16;
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= int64_t(g.B) * g.D * g.H * g.W) return;
-  const Elem e = decompose(i, g, 1);
-  const bf16 *tv = t + g.at(e.b, e.z, e.y, e.x) * C;
+  const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nv) return;
+  const bf16 *tv = t + padded_voxel(i, g) * C;
+  const u16x8 lo = ldu8(tv), hi = ldu8(tv + 8);
   float s = wh[C];
 #pragma unroll
-  for (int c = 0; c < C; ++c) s += bf2f(tv[c]) * wh[c];
+  for (int c = 0; c < C; ++c) s += bf2f(c < 8 ? lo[c] : hi[c - 8]) * wh[c];
   out[i] = s;
 }
 
@@ -729,7 +806,7 @@ constexpr int kHB = 256;  // threads per block of the head / loss reductions
 // gpre[v][c] = dout[v] wh[c] (t[v][c] > 0); per-block partials of
 // dL/dwh[c] = sum_v dout[v] t[v][c] and dL/dbh = sum_v dout[v]
 __global__ __launch_bounds__(kHB) void k_head_bwd(const float *__restrict__ dout,
-                                                 const bf16 *__restrict__ t, PGrid g,
+                                                 const bf16 *__restrict__ t, PGrid g, unsigned nv,
                                                  const float *__restrict__ wh,
                                                  bf16 *__restrict__ gpre,
                                                  float *__restrict__ part /*[nblk][17]*/) {
@@ -738,17 +815,24 @@ __global__ __launch_bounds__(kHB) void k_head_bwd(const float *__restrict__ dout
   float acc[C + 1];
 #pragma unroll
   for (int c = 0; c <= C; ++c) acc[c] = 0.f;
-  const int64_t nv = int64_t(g.B) * g.D * g.H * g.W;
-  for (int64_t i = int64_t(blockIdx.x) * kHB + threadIdx.x; i < nv; i += int64_t(gridDim.x) * kHB) {
-    const Elem e = decompose(i, g, 1);
-    const int64_t v = g.at(e.b, e.z, e.y, e.x);
+  const unsigned step = gridDim.x * kHB;
+  for (uint64_t j = blockIdx.x * kHB + threadIdx.x; j < nv; j += step) {
+    const unsigned i = unsigned(j);
+    const int64_t v = padded_voxel(i, g) * C;
     const float d = dout[i];
+    const u16x8 in[2] = {ldu8(t + v), ldu8(t + v + 8)};
     acc[C] += d;
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const float tv = bf2f(t[v * C + c]);
-      acc[c] += d * tv;
-      gpre[v * C + c] = f2bf(tv > 0.f ? d * wh[c] : 0.f);
+    for (int h = 0; h < 2; ++h) {
+      u16x8 o;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int c = 8 * h + k;
+        const float tv = bf2f(in[h][k]);
+        acc[c] += d * tv;
+        o[k] = f2bf(tv > 0.f ? d * wh[c] : 0.f);
+      }
+      *reinterpret_cast<u16x8 *>(gpre + v + 8 * h) = o;
     }
   }
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -804,10 +888,28 @@ __global__ __launch_bounds__(kHB) void k_mse_grad(const float *__restrict__ out,
                                                  const double *__restrict__ part, int nparts,
                                                  float *__restrict__ dout,
                                                  float *__restrict__ loss) {
+  // the sums of the parts, in the same fixed order in every block: thread t adds parts
+  // t, t + 256, ..., then the tree (one thread adding all of them took 80 us)
+  __shared__ double sh[2][kHB / 64];
   double den = 0.0, num = 0.0;
-  for (int k = 0; k < nparts; ++k) {
+  for (int k = threadIdx.x; k < nparts; k += kHB) {
     den += part[2 * k];
     num += part[2 * k + 1];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    den += __shfl_xor(den, o);
+    num += __shfl_xor(num, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sh[0][threadIdx.x >> 6] = den;
+    sh[1][threadIdx.x >> 6] = num;
+  }
+  __syncthreads();
+  den = num = 0.0;
+  for (int k = 0; k < kHB / 64; ++k) {
+    den += sh[0][k];
+    num += sh[1][k];
   }
   const float scale = den > 0.0 ? float(2.0 / den) : 0.f;
   for (int64_t i = int64_t(blockIdx.x) * kHB + threadIdx.x; i < n; i += int64_t(gridDim.x) * kHB)
@@ -833,7 +935,13 @@ __global__ void k_adam(float *__restrict__ th, const float *__restrict__ g, floa
 // ---- host launchers ---------------------------------------------------------------------
 
 static inline dim3 g1(int64_t n, int bs = 256) { return dim3(unsigned((n + bs - 1) / bs)); }
-static inline int64_t logical(const PGrid &g) { return int64_t(g.B) * g.D * g.H * g.W; }
+static inline unsigned logical(const PGrid &g) { return unsigned(g.B) * g.D * g.H * g.W; }
+// a block per x row of `items` 8-channel items
+static inline unsigned nrows(const PGrid &g) { return unsigned(g.B) * g.D * g.H; }
+static inline dim3 rows_of(const PGrid &g) { return dim3(std::min(nrows(g), 1u << 22)); }
+static inline dim3 row_threads(int items) {
+  return dim3(unsigned(std::min(256, (items + 63) / 64 * 64)));
+}
 
 int conv_forward(const ConvArgs &a, hipStream_t s) {
   Q1_CHECK(a.cin % 8 == 0 && a.cin >= 8 && (a.cin == 8 || a.cin % 16 == 0) && a.cin <= 96,
@@ -905,66 +1013,68 @@ int conv_wgrad(ConvWArgs a, float *gw, float *gb, hipStream_t s) {
   return Q1_OK;
 }
 
-int pack_forward(const float *W, int cin_real, int cin_pad, int cout, int ngroups_pad, bf16 *wp,
-                 hipStream_t s) {
-  const int64_t n = int64_t(ngroups_pad) * cout * 8;
-  hipLaunchKernelGGL(k_pack_fwd, g1(n), dim3(256), 0, s, W, cin_real, cin_pad, cout, ngroups_pad, wp);
-  Q1_HIP(hipGetLastError());
-  return Q1_OK;
+void PackJobs::add(const float *W, int cin_real, int cin_pad, int cout, bool bwd, bf16 *out) {
+  PackJob &p = j[n++];
+  p = PackJob{W, out, cin_real, cin_pad, cout, 4 * conv_ksteps(bwd ? cout : cin_pad), bwd, blocks};
+  blocks += (unsigned(p.groups) * (bwd ? cin_real : cout) * 8 + 255) / 256;
 }
 
-int pack_backward(const float *W, int cin, int cout, int ngroups_pad, bf16 *wq, hipStream_t s) {
-  const int64_t n = int64_t(ngroups_pad) * cin * 8;
-  hipLaunchKernelGGL(k_pack_bwd, g1(n), dim3(256), 0, s, W, cin, cout, ngroups_pad, wq);
+int pack_weights(const PackJobs &jobs, hipStream_t s) {
+  hipLaunchKernelGGL(k_pack, dim3(jobs.blocks), dim3(256), 0, s, jobs);
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
 
 int gather_padded(const bf16 *a, int ca, int up_a, const bf16 *b, int cb, const PGrid &g, bf16 *out,
                   hipStream_t s) {
-  hipLaunchKernelGGL(k_gather_padded, g1(logical(g) * ((ca + cb) / 8)), dim3(256), 0, s, a, ca, up_a,
-                     b, cb, g, out);
+  const bool aligned = (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) % 16 == 0;
+  const uint64_t n = uint64_t(logical(g)) * ((ca + cb) / 8);
+  hipLaunchKernelGGL((aligned ? k_gather_padded<true> : k_gather_padded<false>), g1(n), dim3(256),
+                     0, s, a, ca, up_a, b, cb, g, out, n);
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
 
 int unpad_f32(const float *in, const PGrid &g, int C, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_unpad_f32, g1(logical(g) * C), dim3(256), 0, s, in, g, C, out);
+  hipLaunchKernelGGL(k_unpad_f32, rows_of(g), row_threads(g.W * C), 0, s, in, g, C, out,
+                     nrows(g));
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
 
 int pool2(Slice in, const PGrid &fine, int C, bf16 *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool2, g1(logical(fine.half()) * C), dim3(256), 0, s, in, fine, C, out);
+  const uint64_t n = uint64_t(logical(fine.half())) * (C / 8);
+  hipLaunchKernelGGL(k_pool2, g1(n), dim3(256), 0, s, in, fine, C, out, n);
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
 
 int up_adjoint_mask(const float *gup, Slice mask_fine, const PGrid &coarse, int C, bf16 *out,
                     hipStream_t s) {
-  hipLaunchKernelGGL(k_up_adjoint_mask, g1(logical(coarse) * C), dim3(256), 0, s, gup, mask_fine,
-                     coarse, C, out);
+  hipLaunchKernelGGL(k_up_adjoint_mask, rows_of(coarse), row_threads(coarse.W * C / 8), 0, s, gup,
+                     mask_fine, coarse, C, out, nrows(coarse));
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
 
 int pool_adjoint_add_mask(const float *gskip, const float *gp, Slice mask, const PGrid &fine, int C,
                           bf16 *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool_adjoint_add_mask, g1(logical(fine) * C), dim3(256), 0, s, gskip, gp,
-                     mask, fine, C, out);
+  hipLaunchKernelGGL(k_pool_adjoint_add_mask, rows_of(fine), row_threads(fine.W * C / 8), 0, s,
+                     gskip, gp, mask, fine, C, out, nrows(fine));
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
 
 int head_forward(const bf16 *t, const PGrid &g, const float *wh, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_head_fwd, g1(logical(g)), dim3(256), 0, s, t, g, wh, out);
+  hipLaunchKernelGGL(k_head_fwd, g1(logical(g)), dim3(256), 0, s, t, g, logical(g), wh, out);
   Q1_HIP(hipGetLastError());
   return Q1_OK;
 }
 
 int head_backward(const float *dout, const bf16 *t, const PGrid &g, const float *wh, bf16 *gpre,
                   float *part, int nblk, float *gwh, hipStream_t s) {
-  hipLaunchKernelGGL(k_head_bwd, dim3(nblk), dim3(kHB), 0, s, dout, t, g, wh, gpre, part);
+  hipLaunchKernelGGL(k_head_bwd, dim3(nblk), dim3(kHB), 0, s, dout, t, g, logical(g), wh, gpre,
+                     part);
   Q1_HIP(hipGetLastError());
   return sum_parts(part, nblk, int64_t(17), gwh, s);
 }

@@ -83,9 +83,22 @@ int conv_ksteps(int cin);
 // floats of ConvWArgs::part
 size_t wgrad_part_floats(const ConvWArgs &a);
 int conv_wgrad(ConvWArgs a, float *gw, float *gb, hipStream_t s);
-int pack_forward(const float *W, int cin_real, int cin_pad, int cout, int ngroups_pad, bf16 *wp,
-                 hipStream_t s);
-int pack_backward(const float *W, int cin, int cout, int ngroups_pad, bf16 *wq, hipStream_t s);
+
+// Weights to pack for k_conv_fwd: the forward form, or (bwd) the backward-data one.
+constexpr int kMaxPack = 20;
+struct PackJob {
+  const float *W;
+  bf16 *out;  // [4 conv_ksteps(channels)][rows][8]
+  int cin_real, cin_pad, cout, groups, bwd;
+  unsigned block0;
+};
+struct PackJobs {
+  PackJob j[kMaxPack];
+  int n = 0;
+  unsigned blocks = 0;
+  void add(const float *W, int cin_real, int cin_pad, int cout, bool bwd, bf16 *out);
+};
+int pack_weights(const PackJobs &jobs, hipStream_t s);
 // unpadded [B][D][H][W][ca] (or its half grid when up_a) and [..][cb] -> padded concatenation
 int gather_padded(const bf16 *a, int ca, int up_a, const bf16 *b, int cb, const PGrid &g, bf16 *out,
                   hipStream_t s);

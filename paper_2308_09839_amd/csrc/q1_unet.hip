@@ -125,14 +125,12 @@ inline double u01(uint64_t seed, uint64_t i) {
 }
 
 int pack_all(UNet &n, hipStream_t s) {
-  for (int l = 0; l < 10; ++l) {
-    Layer &L = n.L[l];
-    int rc = pack_forward(n.theta + L.wo, L.s.cin_real, L.s.cin, L.s.cout, L.nchunks * 4, L.wp, s);
-    if (rc) return rc;
-    if (L.wq && (rc = pack_backward(n.theta + L.wo, L.s.cin_real, L.s.cout, L.nchunks_b * 4, L.wq, s)))
-      return rc;
+  PackJobs jobs;
+  for (Layer &L : n.L) {
+    jobs.add(n.theta + L.wo, L.s.cin_real, L.s.cin, L.s.cout, false, L.wp);
+    if (L.wq) jobs.add(n.theta + L.wo, L.s.cin_real, L.s.cin, L.s.cout, true, L.wq);
   }
-  return Q1_OK;
+  return pack_weights(jobs, s);
 }
 
 struct LayerIO {
@@ -711,7 +709,9 @@ int q1_conv3d_forward(int B, int D, int H, int W, const uint16_t *a_d, int ca, i
   Q1_HIP(hipMalloc(&xp.p, size_t(g.voxels()) * cin * sizeof(bf16)));
   Q1_HIP(hipMalloc(&yp.p, size_t(g.voxels()) * cout * sizeof(float)));
   Q1_HIP(hipMemsetAsync(xp.p, 0, size_t(g.voxels()) * cin * sizeof(bf16), s));
-  int rc = pack_forward(w_d, cin, cin, cout, nchunks * 4, static_cast<bf16 *>(wp.p), s);
+  PackJobs jobs;
+  jobs.add(w_d, cin, cin, cout, false, static_cast<bf16 *>(wp.p));
+  int rc = pack_weights(jobs, s);
   if (!rc) rc = gather_padded(a_d, ca, up_a, b_d, cb, g, static_cast<bf16 *>(xp.p), s);
   if (rc) return rc;
   ConvArgs c;
@@ -745,7 +745,9 @@ int q1_conv3d_backward_data(int B, int D, int H, int W, const uint16_t *gy_d, in
   Q1_HIP(hipMalloc(&gp.p, size_t(g.voxels()) * cout * sizeof(bf16)));
   Q1_HIP(hipMalloc(&xp.p, size_t(g.voxels()) * cin * sizeof(float)));
   Q1_HIP(hipMemsetAsync(gp.p, 0, size_t(g.voxels()) * cout * sizeof(bf16), s));
-  int rc = pack_backward(w_d, cin, cout, nchunks * 4, static_cast<bf16 *>(wq.p), s);
+  PackJobs jobs;
+  jobs.add(w_d, cin, cin, cout, true, static_cast<bf16 *>(wq.p));
+  int rc = pack_weights(jobs, s);
   if (!rc) rc = gather_padded(gy_d, cout, 0, nullptr, 0, g, static_cast<bf16 *>(gp.p), s);
   if (rc) return rc;
   ConvArgs c;
