@@ -12,17 +12,15 @@
 //   Laplace      v_a = k (c_a . g) / (6 det J),  g = sum_b c_b u_b,
 //   elasticity   v_a = S c_a / (6 det J),  S = lambda tr(H) I + mu (H + H^T),
 //                H = sum_b u_b (x) c_b (= det J grad u).
-// Hexahedra of order P = 2 (27 nodes) and 3 (64 nodes): (P+1)^3 threads per
-// element (a block holds 9 or 4 elements).  Thread r stages node r
-// (coordinates, input) in LDS, then evaluates quadrature point r of the
-// (P+1)^3 Gauss rule: the Jacobian J, its adjugate A
-// (rows the cross products of the columns, so J^-1 = A / det J) and the
-// reference gradients g of the input; it leaves in LDS the reference flux f,
-// with v_a = sum_q grad_hat phi_a(q) . f(q):
+// Hexahedra of order P = 2 (27 nodes) and 3 (64 nodes): (P+1)^2 lanes per
+// element, each with a line of P+1 nodes, then of quadrature points of the (P+1)^3
+// Gauss rule.  At a point: the Jacobian J, its adjugate A (rows the cross products
+// of the columns, so J^-1 = A / det J), the reference gradients g of the input and
+// the reference flux f, with v_a = sum_q grad_hat phi_a(q) . f(q):
 //   Laplace      f = k w A (sum_c g_c A_c) / det J,
 //   elasticity   f_i = w S_i A^T / det J,  H = G A (det J grad u, rows of G
 //                the reference gradients of the components), S as above;
-// finally thread r gathers v_r for node r.  Both element kinds scatter with
+// The diagonal keeps one thread per node and point.  Both element kinds scatter with
 // global atomics (the paper's one-thread-per-element strategy), after
 // y = x on Dirichlet nodes and 0 elsewhere.
 #include <hip/hip_runtime.h>
@@ -147,14 +145,40 @@ __global__ __launch_bounds__(kFB) void k_tet_diag(int64_t ne, int64_t nn,
 //
 // Order P = 2 (27 nodes) or 3 (64 nodes): nodes at t_m = -1 + 2m/P per
 // direction, local node a = i + (P+1) j + (P+1)^2 k, P+1 Gauss points per
-// direction.  A block holds 256 / (P+1)^3 elements, thread r of an element
-// staging node r and then evaluating quadrature point r.
+// direction.  In the diagonal's kernel a block holds 256 / (P+1)^3 elements, thread r
+// of an element staging node r and then evaluating quadrature point r.
 
 template <int P>
 struct QP {
   static constexpr int N = P + 1;          // nodes (and Gauss points) per direction
   static constexpr int NPTS = N * N * N;   // nodes (and points) per element
   static constexpr int E = 256 / NPTS;     // elements per block
+};
+
+// The apply's lanes and LDS areas: N^2 lanes per element, EW elements per wavefront,
+// LS lanes between neighbouring elements; entry (x, y, z) of element le at x + A y + B z + S le, in an array
+// of pairs and one of single values.  The strides are the best of a search under the bank
+// rules that the conflict counters fit: 16-byte accesses take lanes {0-3, 12-15, 20-23,
+// 24-27}, {4-11, 16-19, 28-31} and the same of the upper half, four passes over 256 B;
+// 8-byte ones 16 lanes at a time over 128 B.  Dense arrays (A = N, B = N^2, S = 3 N^3, no
+// pairs) kept the LDS busy 2.7 times as long as without conflicts.
+template <int P>
+struct QL;
+template <>
+struct QL<2> {
+  static constexpr int EW = 7, LS = 9, A = 5, B = 19, S = 57;
+  static __device__ __forceinline__ int elem(int lane) { return min(lane / 9, 6); }
+  static __device__ __forceinline__ int line(int lane) { return lane % 9; }  // lane 63: as lane 54
+};
+template <>
+struct QL<3> {
+  static constexpr int EW = 4, LS = 1, A = 5, B = 20, S = 84;
+  static __device__ __forceinline__ int elem(int lane) { return lane & 3; }
+  static __device__ __forceinline__ int line(int lane) { return lane >> 2; }
+};
+template <typename T>
+struct alignas(2 * sizeof(T)) Two {
+  T a, b;
 };
 
 // 1-D Lagrange basis of order P on [-1, 1] and its derivative (quadratic: the
@@ -286,6 +310,122 @@ __device__ __forceinline__ T qp_point(int r, const T (*sX)[QP<P>::NPTS],
   return dot3(j0, A[0]);
 }
 
+// Sum-factorised apply of order P, N = P + 1: N^2 lanes per element, each holding a
+// line of N values in registers, floor(64 / N^2) elements per wavefront (7 or 4).
+// Per field (coordinate or input component), with B[q][i] = L_i(p_q), D[q][i] = L_i'(p_q):
+//   A  lane (j, k), line in i:   S0 = B f, S1 = D f                    at (qx, j, k)
+//   B  lane (qx, k), line in j:  S0 = B S0, S1 = B S1, S2 = D S0       at (qx, qy, k)
+//   C  lane (qx, qy), line in k: g_xi = B S1, g_eta = B S2, g_zeta = D S0, kept in registers;
+// then the flux at the lane's N points (as in the comment at the top of this file) and,
+// per component, the transpose of C, B and A on it.  The lines turn through LDS, each
+// value written and read once per pass, one field at a time in 3 N^3 values per element;
+// an element's lanes lie in one wavefront, whose LDS instructions execute in order, so no
+// workgroup barrier is needed.  Lines are evaluated by even and odd parts (the points and
+// nodes are symmetric): 10 operations for B f and D f at the three points of order 2, not
+// 18.  The last node of a line is added to the next element's first when the two lanes
+// hold the same node id, which saves a third (order 2) or a quarter of the atomics.
+//
+// What bounds it: the atomics (36 of the 111 us of order 2 on 64^3, 58 of 119 of order 3
+// on 42^3, FP64: they leave L2 for memory), then the LDS turns and FP64 issue.  Forms with
+// one thread per node and point, which read each line N times and met at workgroup
+// barriers, took 285 and 349 us.
+
+// Values and derivatives of the interpolant of f at the N points.
+template <typename T, int P>
+struct Line {
+  static constexpr int N = P + 1, H = N / 2;  // H pairs of nodes (and points); order 2: a centre
+  // coefficient of the even (s = +1) or odd part of node pair n at the positive point q
+  static __device__ __forceinline__ T b(int q, int n, int s) {
+    return T(0.5) * (lag<T, P>(N - 1 - n, gpt<T, P>(N - 1 - q)) +
+                     T(s) * lag<T, P>(n, gpt<T, P>(N - 1 - q)));
+  }
+  static __device__ __forceinline__ T d(int q, int n, int s) {
+    return T(0.5) * (dlag<T, P>(N - 1 - n, gpt<T, P>(N - 1 - q)) +
+                     T(s) * dlag<T, P>(n, gpt<T, P>(N - 1 - q)));
+  }
+  template <bool VB, bool VD>
+  static __device__ __forceinline__ void eval(const T (&f)[N], T (&B)[N], T (&D)[N]) {
+    T e[H], o[H];
+#pragma unroll
+    for (int n = 0; n < H; ++n) {
+      e[n] = f[n] + f[N - 1 - n];
+      o[n] = f[N - 1 - n] - f[n];
+    }
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+      if constexpr (VB) {
+        T E = b(q, 0, 1) * e[0], O = b(q, 0, -1) * o[0];
+#pragma unroll
+        for (int n = 1; n < H; ++n) {
+          E += b(q, n, 1) * e[n];
+          O += b(q, n, -1) * o[n];
+        }
+        if constexpr (N % 2) E += lag<T, P>(H, gpt<T, P>(N - 1 - q)) * f[H];
+        B[q] = E - O;
+        B[N - 1 - q] = E + O;
+      }
+      if constexpr (VD) {  // the derivative's even part comes from the odd node sums
+        T E = d(q, 0, -1) * o[0], O = d(q, 0, 1) * e[0];
+#pragma unroll
+        for (int n = 1; n < H; ++n) {
+          E += d(q, n, -1) * o[n];
+          O += d(q, n, 1) * e[n];
+        }
+        if constexpr (N % 2) O += dlag<T, P>(H, gpt<T, P>(N - 1 - q)) * f[H];
+        D[q] = E - O;
+        D[N - 1 - q] = E + O;
+      }
+    }
+    if constexpr (N % 2) {  // the centre point is the centre node
+      if constexpr (VB) B[H] = f[H];
+      if constexpr (VD) D[H] = dlag<T, P>(N - 1, T(0)) * o[0];
+    }
+  }
+  // v (+)= B^T a or D^T a
+  template <bool DERIV, bool ADD>
+  static __device__ __forceinline__ void transp(const T (&a)[N], T (&v)[N]) {
+    T e[H], o[H];
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+      e[q] = a[q] + a[N - 1 - q];
+      o[q] = a[N - 1 - q] - a[q];
+    }
+#pragma unroll
+    for (int n = 0; n < H; ++n) {
+      T E, O;  // node N-1-n gets E + O, node n gets E - O (values), O + E, O - E (derivatives)
+      if constexpr (!DERIV) {
+        E = b(0, n, 1) * e[0];
+        O = b(0, n, -1) * o[0];
+      } else {
+        E = d(0, n, 1) * o[0];
+        O = d(0, n, -1) * e[0];
+      }
+#pragma unroll
+      for (int q = 1; q < H; ++q) {
+        E += (DERIV ? d(q, n, 1) * o[q] : b(q, n, 1) * e[q]);
+        O += (DERIV ? d(q, n, -1) * e[q] : b(q, n, -1) * o[q]);
+      }
+      if constexpr (N % 2 && DERIV) O += dlag<T, P>(N - 1, T(0)) * a[H];
+      if constexpr (ADD) {
+        v[n] += E - O;
+        v[N - 1 - n] += E + O;
+      } else {
+        v[n] = E - O;
+        v[N - 1 - n] = E + O;
+      }
+    }
+    if constexpr (N % 2) {
+      T c = DERIV ? dlag<T, P>(H, gpt<T, P>(N - 1)) * o[0]
+                  : lag<T, P>(H, gpt<T, P>(N - 1)) * e[0] + a[H];
+      if constexpr (ADD) c += v[H];
+      v[H] = c;
+    }
+  }
+};
+
+// order of this wavefront's LDS instructions, for the compiler (no instruction)
+__device__ __forceinline__ void lds_turn() { asm volatile("" ::: "memory"); }
+
 template <typename T, int PH, bool MASKED, int P>
 __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
                                                   const T *__restrict__ xyz,
@@ -294,269 +434,169 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
                                                   const uint8_t *__restrict__ mask,
                                                   const T *__restrict__ x, T *__restrict__ y,
                                                   const int *__restrict__ stop) {
-  constexpr int DPN = phys_dpn(PH);
-  constexpr int N = QP<P>::N, NPTS = QP<P>::NPTS, E = QP<P>::E;
+  constexpr int DPN = phys_dpn(PH), N = P + 1, L = N * N;
+  using Q = QL<P>;
+  using Ln = Line<T, P>;
   if (stop && *stop) return;
-  __shared__ T sX[E][3][NPTS];
-  __shared__ T sU[E][DPN][NPTS];
-  __shared__ T sF[E][DPN][3][NPTS];  // reference flux: [component][direction][point]
-  const int le = int(threadIdx.x) / NPTS, r = int(threadIdx.x) - NPTS * le;
-  const int64_t e = int64_t(blockIdx.x) * E + le;
-  const bool active = le < E && e < ne;
-  int64_t g = 0;
-  bool fixed = true;
-  if (active) {  // phase 1: node r
-    g = conn[int64_t(r) * ne + e];
-    fixed = MASKED && mask[g] != 0;
+  __shared__ Two<T> pairs[kFB / 64][Q::EW * Q::S];
+  __shared__ T singles[kFB / 64][Q::EW * Q::S];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // lanes past the last whole element repeat another's work (the same values to the same places)
+  const int le = Q::elem(lane), r = Q::line(lane);
+  // each XCD takes a contiguous range of the elements: the nodes that neighbours share
+  // are gathered and added to through one L2
+  const unsigned blk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int64_t ew = (int64_t(blk) * (kFB / 64) + w) * Q::EW + le;
+  const bool active = lane < Q::EW * L && ew < ne;
+  const int64_t e = ew < ne ? ew : ne - 1;
+  const int ra = r % N, rb = r / N;
+  // the lane's lines: in x at (ra, rb) = (y, z), in y at (x, z), in z at (x, y)
+  Two<T> *px = pairs[w] + Q::S * le + Q::A * ra + Q::B * rb;
+  Two<T> *py = pairs[w] + Q::S * le + ra + Q::B * rb, *pz = pairs[w] + Q::S * le + ra + Q::A * rb;
+  T *sy = singles[w] + (py - pairs[w]), *sz = singles[w] + (pz - pairs[w]);
+  int32_t nid[N];
+  bool fixed[N];
+  T f[3 + DPN][N];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) sX[le][c][r] = xyz[c * nn + g];
+  for (int i = 0; i < N; ++i) nid[i] = conn[(i + int64_t(N) * r) * ne + e];
 #pragma unroll
-    for (int j = 0; j < DPN; ++j) sU[le][j][r] = fixed ? T(0) : x[g * DPN + j];
+  for (int i = 0; i < N; ++i) {
+    fixed[i] = MASKED && mask[nid[i]] != 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) f[c][i] = xyz[c * nn + nid[i]];
+#pragma unroll
+    for (int j = 0; j < DPN; ++j) f[3 + j][i] = x[int64_t(nid[i]) * DPN + j];
+    if (MASKED && fixed[i])
+#pragma unroll
+      for (int j = 0; j < DPN; ++j) f[3 + j][i] = T(0);
   }
-  __syncthreads();
-  if (active) {  // phase 2: quadrature point r
-    T A[3][3], G[DPN][3];
-    const T det = qp_point<T, P, DPN>(r, sX[le], sU[le], A, G);
-    const T s = gwt<T, P>(r % N) * gwt<T, P>((r / N) % N) * gwt<T, P>(r / (N * N)) * rcp(det);
-    if constexpr (PH == 1) {
-      T p[3];  // det J times the physical gradient
-#pragma unroll
-      for (int m = 0; m < 3; ++m) p[m] = G[0][0] * A[0][m] + G[0][1] * A[1][m] + G[0][2] * A[2][m];
-      const T ks = coef[e] * s;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) sF[le][0][d][r] = ks * dot3(A[d], p);
-    } else {
-      const T lam = coef[e], mu = coef[ne + e];
-      T H[3][3];  // det J times the displacement gradient
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) H[i][j] = G[i][0] * A[0][j] + G[i][1] * A[1][j] + G[i][2] * A[2][j];
-      const T ltr = lam * (H[0][0] + H[1][1] + H[2][2]);
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        T Si[3];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) Si[j] = mu * (H[i][j] + H[j][i]) + (i == j ? ltr : T(0));
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sF[le][i][d][r] = s * dot3(Si, A[d]);
-      }
-    }
-  }
-  __syncthreads();
-  if (active && !fixed) {  // phase 3: node r gathers the test-function products
-    const Tab1<T, P> fx = of_function<T, P>(r % N), fy = of_function<T, P>((r / N) % N),
-                     fz = of_function<T, P>(r / (N * N));
-    T v[DPN];
-#pragma unroll
-    for (int j = 0; j < DPN; ++j) v[j] = T(0);
-#pragma unroll
-    for (int q = 0; q < NPTS; ++q) {
-      const int qx = q % N, qy = (q / N) % N, qz = q / (N * N);
-      const T d0 = fx.d[qx] * fy.b[qy] * fz.b[qz];
-      const T d1 = fx.b[qx] * fy.d[qy] * fz.b[qz];
-      const T d2 = fx.b[qx] * fy.b[qy] * fz.d[qz];
-#pragma unroll
-      for (int j = 0; j < DPN; ++j)
-        v[j] += d0 * sF[le][j][0][q] + d1 * sF[le][j][1][q] + d2 * sF[le][j][2][q];
-    }
-#pragma unroll
-    for (int j = 0; j < DPN; ++j) gadd(&y[g * DPN + j], v[j]);
-  }
-}
+  const T c0 = coef[e], c1 = PH == 3 ? coef[ne + e] : T(0);
 
-// Sum-factorised apply of order P: the per-point reference gradients of the
-// coordinates and the input, and the transposed evaluation of the flux, each
-// in three 1-D passes through LDS (one thread per index triple of the
-// element's N^3 nodes or points, N = P + 1):
-//   A  T0[qx][j][k] = sum_i B[qx][i] f[i][j][k],  T1 = the same with D
-//   B  from T0, T1 along y: f interpolated (T00), d/dxi (T10), d/deta (T01)
-//   C  along z: g_xi = B T10, g_eta = B T01, g_zeta = D T00 at (qx, qy, qz)
-// with B[q][i] = L_i(p_q) and D[q][i] = L_i'(p_q); then the flux at the point
-// (as k_qp_apply), and the transpose of A-B-C on it:
-//   v[i][j][k] = sum_q (D_i B_j B_k F_xi + B_i D_j B_k F_eta + B_i B_j D_k F_zeta).
-// O(N^4) per field instead of O(N^6).  QPE<P, DPN, T>::E elements per block.
-template <int P, int DPN, typename T>
-struct QPE {
-  static constexpr int NPTS = (P + 1) * (P + 1) * (P + 1);
-  static constexpr int F = 3 + DPN;                       // coordinates and input fields
-  static constexpr int RX = F > 3 * DPN ? F : 3 * DPN;    // node values, then the flux
-  static constexpr int RY = 2 * F > 3 * DPN ? 2 * F : 3 * DPN;
-  static constexpr int RZ = 3 * F > 2 * DPN ? 3 * F : 2 * DPN;
-  static constexpr int BYTES = (RX + RY + RZ) * NPTS * int(sizeof(T));  // per element
-  static constexpr int EMAX = 256 / NPTS;
-  static constexpr int EL = (40 * 1024) / BYTES;
-  static constexpr int E = EL < 1 ? 1 : (EL < EMAX ? EL : EMAX);
-};
-
-template <typename T, int PH, bool MASKED, int P>
-__global__ __launch_bounds__(256) void k_qp_apply_sf(int64_t ne, int64_t nn,
-                                                     const T *__restrict__ xyz,
-                                                     const int32_t *__restrict__ conn,
-                                                     const T *__restrict__ coef,
-                                                     const uint8_t *__restrict__ mask,
-                                                     const T *__restrict__ x, T *__restrict__ y,
-                                                     const int *__restrict__ stop) {
-  constexpr int DPN = phys_dpn(PH);
-  using Q = QPE<P, DPN, T>;
-  constexpr int N = P + 1, NPTS = Q::NPTS, E = Q::E, F = Q::F;
-  if (stop && *stop) return;
-  __shared__ T sX[E][Q::RX][NPTS];  // node values (F), then the flux (3 DPN)
-  __shared__ T sY[E][Q::RY][NPTS];  // pass A (2F), then the transposed pass C (3 DPN)
-  __shared__ T sZ[E][Q::RZ][NPTS];  // pass B (3F), then the transposed pass B (2 DPN)
-  const int le = int(threadIdx.x) / NPTS, r = int(threadIdx.x) - NPTS * le;
-  const int64_t e = int64_t(blockIdx.x) * E + le;
-  const bool active = le < E && e < ne;
-  const int a0 = r % N, a1 = (r / N) % N, a2 = r / (N * N);  // this thread's index triple
-  // the 1-D tables B[q][i] and D[q][i] (N x N, constants of the rule)
-  T Bt[N][N], Dt[N][N];
+  T G[3 + DPN][3][N];  // reference gradients at the lane's points (ra, rb, 0..N-1)
 #pragma unroll
-  for (int q = 0; q < N; ++q)
+  for (int m = 0; m < 3 + DPN; ++m) {
+    T B[N], D[N], U[N], a[N], b[N], c[N];
+    Ln::template eval<true, true>(f[m], B, D);
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      Bt[q][i] = lag<T, P>(i, gpt<T, P>(q));
-      Dt[q][i] = dlag<T, P>(i, gpt<T, P>(q));
+    for (int q = 0; q < N; ++q) px[q] = {B[q], D[q]};
+    lds_turn();
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const Two<T> t = py[Q::A * q];
+      a[q] = t.a;
+      b[q] = t.b;
     }
-  int64_t g = 0;
-  bool fixed = true;
-  if (active) {  // node (a0, a1, a2) = r
-    g = conn[int64_t(r) * ne + e];
-    fixed = MASKED && mask[g] != 0;
+    lds_turn();
+    Ln::template eval<true, true>(a, B, D);
+    Ln::template eval<true, false>(b, U, U);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) sX[le][c][r] = xyz[c * nn + g];
+    for (int q = 0; q < N; ++q) {
+      py[Q::A * q] = {U[q], D[q]};
+      sy[Q::A * q] = B[q];
+    }
+    lds_turn();
 #pragma unroll
-    for (int j = 0; j < DPN; ++j) sX[le][3 + j][r] = fixed ? T(0) : x[g * DPN + j];
+    for (int q = 0; q < N; ++q) {
+      const Two<T> t = pz[Q::B * q];
+      a[q] = t.a;
+      b[q] = t.b;
+      c[q] = sz[Q::B * q];
+    }
+    lds_turn();
+    Ln::template eval<true, false>(a, G[m][0], G[m][0]);
+    Ln::template eval<true, false>(b, G[m][1], G[m][1]);
+    Ln::template eval<false, true>(c, G[m][2], G[m][2]);
   }
-  __syncthreads();
-  if (active) {  // pass A at (qx, j, k) = (a0, a1, a2): contract i
+  // the flux of component c and direction d, in place of the input's gradients
+  const T wxy = gwt<T, P>(ra) * gwt<T, P>(rb);
 #pragma unroll
-    for (int f = 0; f < F; ++f) {
-      T t0 = T(0), t1 = T(0);
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const T v = sX[le][f][i + N * (a1 + N * a2)];
-        t0 += Bt[a0][i] * v;
-        t1 += Dt[a0][i] * v;
-      }
-      sY[le][2 * f][r] = t0;
-      sY[le][2 * f + 1][r] = t1;
-    }
-  }
-  __syncthreads();
-  if (active) {  // pass B at (qx, qy, k) = (a0, a1, a2): contract j
-#pragma unroll
-    for (int f = 0; f < F; ++f) {
-      T u00 = T(0), u10 = T(0), u01 = T(0);
-#pragma unroll
-      for (int jj = 0; jj < N; ++jj) {
-        const int s = a0 + N * (jj + N * a2);
-        const T v0 = sY[le][2 * f][s], v1 = sY[le][2 * f + 1][s];
-        u00 += Bt[a1][jj] * v0;
-        u10 += Bt[a1][jj] * v1;
-        u01 += Dt[a1][jj] * v0;
-      }
-      sZ[le][3 * f][r] = u00;
-      sZ[le][3 * f + 1][r] = u10;
-      sZ[le][3 * f + 2][r] = u01;
-    }
-  }
-  __syncthreads();
-  if (active) {  // pass C at (qx, qy, qz) = (a0, a1, a2): contract k, then the flux
-    T Gr[F][3];
-#pragma unroll
-    for (int f = 0; f < F; ++f) {
-      T gx = T(0), gy = T(0), gz = T(0);
-#pragma unroll
-      for (int kk = 0; kk < N; ++kk) {
-        const int s = a0 + N * (a1 + N * kk);
-        gx += Bt[a2][kk] * sZ[le][3 * f + 1][s];
-        gy += Bt[a2][kk] * sZ[le][3 * f + 2][s];
-        gz += Dt[a2][kk] * sZ[le][3 * f][s];
-      }
-      Gr[f][0] = gx;
-      Gr[f][1] = gy;
-      Gr[f][2] = gz;
-    }
-    const T j0[3] = {Gr[0][0], Gr[1][0], Gr[2][0]};
-    const T j1[3] = {Gr[0][1], Gr[1][1], Gr[2][1]};
-    const T j2[3] = {Gr[0][2], Gr[1][2], Gr[2][2]};
+  for (int q = 0; q < N; ++q) {
+    const T j0[3] = {G[0][0][q], G[1][0][q], G[2][0][q]};
+    const T j1[3] = {G[0][1][q], G[1][1][q], G[2][1][q]};
+    const T j2[3] = {G[0][2][q], G[1][2][q], G[2][2][q]};
     T A[3][3];
     cross(j1, j2, A[0]);
     cross(j2, j0, A[1]);
     cross(j0, j1, A[2]);
-    const T det = dot3(j0, A[0]);
-    const T s = gwt<T, P>(a0) * gwt<T, P>(a1) * gwt<T, P>(a2) * rcp(det);
+    const T s = wxy * gwt<T, P>(q) * rcp(dot3(j0, A[0]));
     if constexpr (PH == 1) {
-      T p[3];
+      T p[3];  // det J times the physical gradient
 #pragma unroll
-      for (int m = 0; m < 3; ++m) p[m] = Gr[3][0] * A[0][m] + Gr[3][1] * A[1][m] + Gr[3][2] * A[2][m];
-      const T ks = coef[e] * s;
+      for (int m = 0; m < 3; ++m)
+        p[m] = G[3][0][q] * A[0][m] + G[3][1][q] * A[1][m] + G[3][2][q] * A[2][m];
+      const T ks = c0 * s;
 #pragma unroll
-      for (int d = 0; d < 3; ++d) sX[le][d][r] = ks * dot3(A[d], p);
+      for (int d = 0; d < 3; ++d) G[3][d][q] = ks * dot3(A[d], p);
     } else {
-      const T lam = coef[e], mu = coef[ne + e];
-      T H[3][3];
+      T H[3][3];  // det J times the displacement gradient
 #pragma unroll
       for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int jj = 0; jj < 3; ++jj)
-          H[i][jj] = Gr[3 + i][0] * A[0][jj] + Gr[3 + i][1] * A[1][jj] + Gr[3 + i][2] * A[2][jj];
-      const T ltr = lam * (H[0][0] + H[1][1] + H[2][2]);
+        for (int j = 0; j < 3; ++j)
+          H[i][j] = G[3 + i][0][q] * A[0][j] + G[3 + i][1][q] * A[1][j] + G[3 + i][2][q] * A[2][j];
+      const T ltr = c0 * (H[0][0] + H[1][1] + H[2][2]);
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
         T Si[3];
 #pragma unroll
-        for (int jj = 0; jj < 3; ++jj) Si[jj] = mu * (H[i][jj] + H[jj][i]) + (i == jj ? ltr : T(0));
+        for (int j = 0; j < 3; ++j) Si[j] = c1 * (H[i][j] + H[j][i]) + (i == j ? ltr : T(0));
 #pragma unroll
-        for (int d = 0; d < 3; ++d) sX[le][3 * i + d][r] = s * dot3(Si, A[d]);
+        for (int d = 0; d < 3; ++d) G[3 + i][d][q] = s * dot3(Si, A[d]);
       }
     }
   }
-  __syncthreads();  // the flux F[c][d] of component c, direction d, at sX[le][3c + d]
-  if (active) {  // transposed pass C at (qx, qy, k) = (a0, a1, a2): contract qz
+  T v[DPN][N];
 #pragma unroll
-    for (int c = 0; c < DPN; ++c) {
-      T u0 = T(0), u1 = T(0), u2 = T(0);
+  for (int m = 0; m < DPN; ++m) {
+    T a[N], b[N], c[N], u0[N], u1[N];
+    Ln::template transp<false, false>(G[3 + m][0], a);
+    Ln::template transp<false, false>(G[3 + m][1], b);
+    Ln::template transp<true, false>(G[3 + m][2], c);
 #pragma unroll
-      for (int qz = 0; qz < N; ++qz) {
-        const int s = a0 + N * (a1 + N * qz);
-        u0 += Bt[qz][a2] * sX[le][3 * c][s];
-        u1 += Bt[qz][a2] * sX[le][3 * c + 1][s];
-        u2 += Dt[qz][a2] * sX[le][3 * c + 2][s];
-      }
-      sY[le][3 * c][r] = u0;
-      sY[le][3 * c + 1][r] = u1;
-      sY[le][3 * c + 2][r] = u2;
+    for (int q = 0; q < N; ++q) {
+      pz[Q::B * q] = {a[q], b[q]};
+      sz[Q::B * q] = c[q];
     }
-  }
-  __syncthreads();
-  if (active) {  // transposed pass B at (qx, j, k) = (a0, a1, a2): contract qy
+    lds_turn();
 #pragma unroll
-    for (int c = 0; c < DPN; ++c) {
-      T w0 = T(0), w1 = T(0);
-#pragma unroll
-      for (int qy = 0; qy < N; ++qy) {
-        const int s = a0 + N * (qy + N * a2);
-        w0 += Bt[qy][a1] * sY[le][3 * c][s];
-        w1 += Dt[qy][a1] * sY[le][3 * c + 1][s] + Bt[qy][a1] * sY[le][3 * c + 2][s];
-      }
-      sZ[le][2 * c][r] = w0;
-      sZ[le][2 * c + 1][r] = w1;
+    for (int q = 0; q < N; ++q) {
+      const Two<T> t = py[Q::A * q];
+      a[q] = t.a;
+      b[q] = t.b;
+      c[q] = sy[Q::A * q];
     }
-  }
-  __syncthreads();
-  if (active && !fixed) {  // transposed pass A at node (i, j, k) = (a0, a1, a2): contract qx
+    lds_turn();
+    Ln::template transp<false, false>(a, u0);
+    Ln::template transp<true, false>(b, u1);
+    Ln::template transp<false, true>(c, u1);
 #pragma unroll
-    for (int c = 0; c < DPN; ++c) {
-      T v = T(0);
+    for (int q = 0; q < N; ++q) py[Q::A * q] = {u0[q], u1[q]};
+    lds_turn();
 #pragma unroll
-      for (int qx = 0; qx < N; ++qx) {
-        const int s = qx + N * (a1 + N * a2);
-        v += Dt[qx][a0] * sZ[le][2 * c][s] + Bt[qx][a0] * sZ[le][2 * c + 1][s];
-      }
-      gadd(&y[g * DPN + c], v);
+    for (int q = 0; q < N; ++q) {
+      const Two<T> t = px[q];
+      a[q] = t.a;
+      b[q] = t.b;
     }
+    lds_turn();
+    Ln::template transp<true, false>(a, v[m]);
+    Ln::template transp<false, true>(b, v[m]);
   }
+  // the line's last node goes to the next element's lane when that starts with it
+  const int32_t next = __shfl(nid[0], (lane + Q::LS) & 63);
+  const bool give = active && le + 1 < Q::EW && ew + 1 < ne && next == nid[P];
+  const bool take = __shfl(int(give), (lane - Q::LS) & 63) && active && le > 0;
+#pragma unroll
+  for (int m = 0; m < DPN; ++m) {
+    const T in = __shfl(v[m][P], (lane - Q::LS) & 63);
+    if (take) v[m][0] += in;
+  }
+  if (!active) return;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (!fixed[i] && !(i == P && give))
+#pragma unroll
+      for (int m = 0; m < DPN; ++m) gadd(&y[int64_t(nid[i]) * DPN + m], v[m][i]);
 }
 
 // diag: Laplace sum_q k w |t|^2 / det J, elasticity
@@ -643,23 +683,16 @@ int family_apply_t(Op &op, const void *xv, void *yv, hipStream_t s, const int *s
                          x, y, stop);
     } else {
       auto run = [&](auto pc) {
-        constexpr int P = decltype(pc)::value;
-        using Q = QPE<P, DPN, T>;
-        const dim3 grid(unsigned((op.n_elems + Q::E - 1) / Q::E));
-        hipLaunchKernelGGL((m ? k_qp_apply_sf<T, PH, true, P> : k_qp_apply_sf<T, PH, false, P>),
-                           grid, dim3(Q::E * Q::NPTS), 0, s, op.n_elems, op.n_nodes, xyz,
-                           op.conn, coef, op.mask, x, y, stop);
+        constexpr int P = decltype(pc)::value, EB = kFB / 64 * QL<P>::EW;
+        const dim3 grid(unsigned(((op.n_elems + EB - 1) / EB + 7) / 8 * 8));
+        hipLaunchKernelGGL((m ? k_qp_apply<T, PH, true, P> : k_qp_apply<T, PH, false, P>), grid,
+                           dim3(kFB), 0, s, op.n_elems, op.n_nodes, xyz, op.conn, coef, op.mask,
+                           x, y, stop);
       };
-      // triquadratic: the per-point form (measured on 64^3 FP64 9.0 GDOF/s against 8.1
-      // sum-factorised); tricubic: the sum-factorised form (42^3 FP64 6.3 against 3.2)
-      if (op.elem == Q1_HEX27) {
-        const dim3 grid(unsigned((op.n_elems + QP<2>::E - 1) / QP<2>::E));
-        hipLaunchKernelGGL((m ? k_qp_apply<T, PH, true, 2> : k_qp_apply<T, PH, false, 2>), grid,
-                           dim3(kFB), 0, s, op.n_elems, op.n_nodes, xyz, op.conn, coef,
-                           op.mask, x, y, stop);
-      } else {
+      if (op.elem == Q1_HEX27)
+        run(std::integral_constant<int, 2>{});
+      else
         run(std::integral_constant<int, 3>{});
-      }
     }
   }
   Q1_HIP(hipGetLastError());
