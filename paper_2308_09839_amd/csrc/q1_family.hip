@@ -156,8 +156,8 @@ struct QP {
 };
 
 // The apply's lanes and LDS areas: N^2 lanes per element, EW elements per wavefront,
-// LS lanes between neighbouring elements; entry (x, y, z) of element le at x + A y + B z + S le, in an array
-// of pairs and one of single values.  The strides are the best of a search under the bank
+// LS lanes between neighbouring elements; entry (x, y, z) of element le at
+// x + A y + B z + S le, in an array of pairs and one of single values.  The strides are the best of a search under the bank
 // rules that the conflict counters fit: 16-byte accesses take lanes {0-3, 12-15, 20-23,
 // 24-27}, {4-11, 16-19, 28-31} and the same of the upper half, four passes over 256 B;
 // 8-byte ones 16 lanes at a time over 128 B.  Dense arrays (A = N, B = N^2, S = 3 N^3, no
@@ -166,13 +166,13 @@ template <int P>
 struct QL;
 template <>
 struct QL<2> {
-  static constexpr int EW = 7, LS = 9, A = 5, B = 19, S = 57;
-  static __device__ __forceinline__ int elem(int lane) { return min(lane / 9, 6); }
-  static __device__ __forceinline__ int line(int lane) { return lane % 9; }  // lane 63: as lane 54
+  static constexpr int EW = 7, LS = 1, A = 6, B = 19, S = 55;
+  static __device__ __forceinline__ int elem(int lane) { return lane % 7; }
+  static __device__ __forceinline__ int line(int lane) { return min(lane / 7, 8); }  // 63: as 56
 };
 template <>
 struct QL<3> {
-  static constexpr int EW = 4, LS = 1, A = 5, B = 20, S = 84;
+  static constexpr int EW = 4, LS = 1, A = 5, B = 20, S = 92;
   static __device__ __forceinline__ int elem(int lane) { return lane & 3; }
   static __device__ __forceinline__ int line(int lane) { return lane >> 2; }
 };
@@ -325,10 +325,13 @@ __device__ __forceinline__ T qp_point(int r, const T (*sX)[QP<P>::NPTS],
 // 18.  The last node of a line is added to the next element's first when the two lanes
 // hold the same node id, which saves a third (order 2) or a quarter of the atomics.
 //
-// What bounds it: the atomics (36 of the 111 us of order 2 on 64^3, 58 of 119 of order 3
-// on 42^3, FP64: they leave L2 for memory), then the LDS turns and FP64 issue.  Forms with
-// one thread per node and point, which read each line N times and met at workgroup
-// barriers, took 285 and 349 us.
+// What bounds it: the LDS turns (busy 71% of the time at order 2 in FP64), then the
+// gathers' cache accesses and FP64 issue.  FP64 Laplace, order 2 on 64^3 74 us, order 3 on
+// 42^3 64 us; with an atomic per lane and node in place of the rows (2.4 sums to a request;
+// the requests leave L2 for memory) 111 and 119 us; one thread per node and point, which
+// read each line N times and met at workgroup barriers, 285 and 349 us.  Measured and
+// dropped: box tiles on lattices with sums kept in LDS over a march in z (114 us at order
+// 2: their barriers and accumulator traffic cost what the gathers and atomics saved).
 
 // Values and derivatives of the interpolant of f at the N points.
 template <typename T, int P>
@@ -438,9 +441,11 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
   using Q = QL<P>;
   using Ln = Line<T, P>;
   if (stop && *stop) return;
-  __shared__ Two<T> pairs[kFB / 64][Q::EW * Q::S];
-  __shared__ T singles[kFB / 64][Q::EW * Q::S];
+  constexpr int NP = Q::EW * Q::S;
+  __shared__ Two<T> area[kFB / 64][NP + (NP + 1) / 2];  // pairs, then single values
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  Two<T> *pairs = area[w];
+  T *singles = reinterpret_cast<T *>(pairs + NP);
   // lanes past the last whole element repeat another's work (the same values to the same places)
   const int le = Q::elem(lane), r = Q::line(lane);
   // each XCD takes a contiguous range of the elements: the nodes that neighbours share
@@ -451,9 +456,9 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
   const int64_t e = ew < ne ? ew : ne - 1;
   const int ra = r % N, rb = r / N;
   // the lane's lines: in x at (ra, rb) = (y, z), in y at (x, z), in z at (x, y)
-  Two<T> *px = pairs[w] + Q::S * le + Q::A * ra + Q::B * rb;
-  Two<T> *py = pairs[w] + Q::S * le + ra + Q::B * rb, *pz = pairs[w] + Q::S * le + ra + Q::A * rb;
-  T *sy = singles[w] + (py - pairs[w]), *sz = singles[w] + (pz - pairs[w]);
+  Two<T> *px = pairs + Q::S * le + Q::A * ra + Q::B * rb;
+  Two<T> *py = pairs + Q::S * le + ra + Q::B * rb, *pz = pairs + Q::S * le + ra + Q::A * rb;
+  T *sy = singles + (py - pairs), *sz = singles + (pz - pairs);
   int32_t nid[N];
   bool fixed[N];
   T f[3 + DPN][N];
@@ -591,12 +596,29 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
     const T in = __shfl(v[m][P], (lane - Q::LS) & 63);
     if (take) v[m][0] += in;
   }
-  if (!active) return;
+  // The sums go out in the order of the rows (line, element, node), through LDS: where ids
+  // run along x, consecutive lanes add to consecutive addresses, and a 64-byte atomic
+  // request carries several of them instead of two or three.
+  constexpr int ENT = Q::EW * L * N;  // entries of the wavefront
+  static_assert(sizeof(area[0]) >= ENT * (DPN * sizeof(T) + sizeof(int32_t)), "sums and ids fit");
+  T *out = reinterpret_cast<T *>(pairs);
+  int32_t *ids = reinterpret_cast<int32_t *>(out + ENT * DPN);
+  const int at = (r * Q::EW + le) * N;
+  lds_turn();
+  if (lane < Q::EW * L)
 #pragma unroll
-  for (int i = 0; i < N; ++i)
-    if (!fixed[i] && !(i == P && give))
+    for (int i = 0; i < N; ++i) {
 #pragma unroll
-      for (int m = 0; m < DPN; ++m) gadd(&y[int64_t(nid[i]) * DPN + m], v[m][i]);
+      for (int m = 0; m < DPN; ++m) out[(at + i) * DPN + m] = v[m][i];
+      ids[at + i] = active && !fixed[i] && !(i == P && give) ? nid[i] : -1;
+    }
+  lds_turn();
+#pragma unroll
+  for (int k = 0; k < (ENT * DPN + 63) / 64; ++k) {
+    const int j = k * 64 + lane;
+    const int32_t n = j < ENT * DPN ? ids[j / DPN] : -1;
+    if (n >= 0) gadd(&y[int64_t(n) * DPN + j % DPN], out[j]);
+  }
 }
 
 // diag: Laplace sum_q k w |t|^2 / det J, elasticity
