@@ -222,10 +222,31 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
     T *__restrict__ x, T *__restrict__ r, T *__restrict__ r_old,
     const double *__restrict__ part_pq, int npq, const double *__restrict__ part_rho_k,
     double *__restrict__ part_rho_k1, double *__restrict__ part_rr, Status *__restrict__ st) {
-  if (st->done) return;
+  // Nothing below depends on another load's result until alpha: the flag, the partials and
+  // the first round of the vectors are requested together, one memory latency in all.
+  const int done = st->done;
   const int nb = gridDim.x;
+  const Range rg = block_range(n);
+  // four elements per thread and round: all their loads (at clamped indices)
+  // before any store; the additions keep the order i, i + 256, ...
+  constexpr int U = 4;
+  T rv[U], xv[U], wv[U];
+  TP pv[U], qv[U];
+  auto load = [&](int64_t i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = min(i0 + u * kRT, n - 1);
+      rv[u] = r[i];
+      xv[u] = x[i];
+      pv[u] = p[i];
+      qv[u] = q[i];
+      if constexpr (!FLEX) wv[u] = w[i];
+    }
+  };
+  load(rg.i0 + threadIdx.x);
   double t[2];
   sum_partials_nc<2>({part_pq, part_rho_k}, {npq, nb}, t);
+  if (done) return;
   const double pq = t[0], rho = t[1];
   if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -235,23 +256,9 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
     return;
   }
   const double alpha = rho / pq;
-  const Range rg = block_range(n);
   double v[2] = {0.0, 0.0};
-  // four elements per thread and round: all their loads (at clamped indices)
-  // before any store; the additions keep the order i, i + 256, ...
-  constexpr int U = 4;
   for (int64_t i0 = rg.i0 + threadIdx.x; i0 < rg.i1; i0 += U * kRT) {
-    T rv[U], xv[U], wv[U];
-    TP pv[U], qv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = min(i0 + u * kRT, rg.i1 - 1);
-      rv[u] = r[i];
-      xv[u] = x[i];
-      pv[u] = p[i];
-      qv[u] = q[i];
-      if constexpr (!FLEX) wv[u] = w[i];
-    }
+    if (i0 >= rg.i0 + U * kRT) load(i0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t i = i0 + u * kRT;
@@ -280,27 +287,32 @@ __global__ __launch_bounds__(kRT) void k_pcg_direction(
     TP *__restrict__ p, const double *__restrict__ part_num, const double *__restrict__ part_den,
     const double *__restrict__ part_rr, const double *__restrict__ part_bb, double tol2, int it,
     int maxit, Status *__restrict__ st) {
-  if (st->done) return;
+  const int done = st->done;  // as in k_pcg_update: one memory latency for all first loads
   const int nb = gridDim.x;
+  const Range rg = block_range(n);
+  constexpr int U = 4;
+  T zv[U];
+  TP pv[U];
+  auto load = [&](int64_t i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = min(i0 + u * kRT, n - 1);
+      zv[u] = z ? z[i] : T(w[i] * r[i]);
+      pv[u] = p[i];
+    }
+  };
+  load(rg.i0 + threadIdx.x);
   double t[4];
   sum_partials_n<4>({part_num, part_den, part_rr, part_bb}, nb, t);
+  if (done) return;
   const double num = t[0], den = t[1], rr = t[2], bb = t[3];
   const bool conv = rr <= tol2 * bb;
   const bool bad = !isfinite(rr);
   const bool stop = conv || bad || it >= maxit;
   if (!stop) {
     const double beta = num / den;
-    const Range rg = block_range(n);
-    constexpr int U = 4;  // as in k_pcg_update: a round's loads before its stores
     for (int64_t i0 = rg.i0 + threadIdx.x; i0 < rg.i1; i0 += U * kRT) {
-      T zv[U];
-      TP pv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t i = min(i0 + u * kRT, rg.i1 - 1);
-        zv[u] = z ? z[i] : T(w[i] * r[i]);
-        pv[u] = p[i];
-      }
+      if (i0 >= rg.i0 + U * kRT) load(i0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t i = i0 + u * kRT;

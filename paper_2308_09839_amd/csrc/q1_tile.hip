@@ -469,7 +469,7 @@ __global__ __launch_bounds__(256) void k_apply_block(
     const uint32_t *__restrict__ tile_lat, const uint32_t *__restrict__ tile_addr,
     const int32_t *__restrict__ tile_g0, int64_t sy, int64_t sz, double *__restrict__ dot_part) {
   constexpr int DPN = phys_dpn(PH);
-  if (stop && *stop) return;
+  const int halt = stop ? *stop : 0;  // tested once the tile's records are requested
   constexpr int UOFF = PA ? 0 : 3;
   constexpr int NR = UOFF + DPN;  // [x, y, z,] u[DPN], stored field by field
   using FT = FxTile<DPN>;
@@ -542,6 +542,7 @@ __global__ __launch_bounds__(256) void k_apply_block(
       for (int j = 0; j < DPN; ++j) rec[k][UOFF + j] = x[g * DPN + j];
     }
     if (base == 0) first_step();
+    if (halt) return;
 #pragma unroll
     for (int k = 0; k < KN; ++k) {
       const int i = base + k * 256 + tid;
@@ -688,7 +689,7 @@ __global__ __launch_bounds__(256) void k_apply_owner(int nx, int ny, int nz,
   using F = OwnTile;
   constexpr int NC = EK >= kOwnKuhn ? 6 : 1;  // cell coefficients
   constexpr bool ALLX = EK != kOwnPar;          // all 8 corners' coordinates
-  if (stop && *stop) return;
+  const int halt = stop ? *stop : 0;  // tested once the staging loads are out
   __shared__ T sR[4 * F::NS];   // x, y, z, input (0 on Dirichlet nodes), field by field
   __shared__ double sV[F::NA];  // accumulator over the owned box
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -770,6 +771,7 @@ __global__ __launch_bounds__(256) void k_apply_owner(int nx, int ny, int nz,
   T cnext[NC];
 #pragma unroll
   for (int t = 0; t < NC; ++t) cnext[t] = ld_off(coef, eo[0] + uint32_t(t * sizeof(T)));
+  if (halt) return;
 #pragma unroll
   for (int k = 0; k < F::KN; ++k) {
     const int i = k * 256 + tid;
@@ -901,7 +903,7 @@ __global__ __launch_bounds__(256) void k_apply_block_tet(
     const T *__restrict__ xyz, const T *__restrict__ x, T *__restrict__ y,
     const int *__restrict__ stop, const int32_t *__restrict__ slot, T *__restrict__ halo) {
   constexpr int DPN = phys_dpn(PH);
-  if (stop && *stop) return;
+  const int halt = stop ? *stop : 0;  // tested once the tile's records are requested
   constexpr int NR = 3 + DPN;
   constexpr int KN = 4;  // node records per thread issued together (1024 per round)
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -939,6 +941,7 @@ __global__ __launch_bounds__(256) void k_apply_block_tet(
         kslot[k] = sl[k];
       }
     }
+    if (halt) return;
 #pragma unroll
     for (int k = 0; k < KN; ++k) {
       const int i = base + k * 256 + tid;
@@ -1121,28 +1124,46 @@ __global__ __launch_bounds__(256) void k_halo_sum(int64_t n, const int32_t *__re
                                                   double *__restrict__ dot_part,
                                                   const double *__restrict__ tile_part,
                                                   int64_t n_tiles) {
-  if (stop && *stop) return;
+  constexpr int kHaloX = DPN == 1 ? 6 : 2;
+  const int halt = stop ? *stop : 0;  // tested once the first loads are out
   const int64_t base = int64_t(blockIdx.x) * 256 * kHaloNpt + threadIdx.x;
   int64_t jj[kHaloNpt];
   int32_t h[kHaloNpt], e0[kHaloNpt], e1[kHaloNpt];
+  T acc[kHaloNpt][DPN], xv[kHaloNpt][DPN];
 #pragma unroll
   for (int p = 0; p < kHaloNpt; ++p) {
     jj[p] = min(base + p * 256, n - 1);
     h[p] = hnode[jj[p]];
     e0[p] = hptr[jj[p]];
     e1[p] = hptr[jj[p] + 1];
-  }
-  T acc[kHaloNpt][DPN];
-#pragma unroll
-  for (int p = 0; p < kHaloNpt; ++p)
 #pragma unroll
     for (int c = 0; c < DPN; ++c)  // (read but unused on Dirichlet nodes)
       acc[p][c] = halo[jj[p] * DPN + c] + halo[(n + jj[p]) * DPN + c];
+  }
+  if (halt) return;
+  // the input where it is used (the other lanes read one entry), requested before the sums
 #pragma unroll
   for (int p = 0; p < kHaloNpt; ++p)
-    for (int32_t k = e0[p]; k < e1[p]; ++k)
 #pragma unroll
-      for (int c = 0; c < DPN; ++c) acc[p][c] += halo[(2 * n + k) * DPN + c];
+    for (int c = 0; c < DPN; ++c)
+      xv[p][c] = x ? x[int64_t(dot_part || h[p] < 0 ? h[p] & 0x3fffffff : 0) * DPN + c] : T(1);
+  // the extra slots of nodes on more than two tiles, several at a time (on a lattice an
+  // edge has two and a corner six; six at a time cost the 3-DOF kinds their occupancy)
+#pragma unroll
+  for (int p = 0; p < kHaloNpt; ++p)
+    for (int32_t k = e0[p]; k < e1[p]; k += kHaloX) {
+      T v[kHaloX][DPN];
+#pragma unroll
+      for (int u = 0; u < kHaloX; ++u)
+#pragma unroll
+        for (int c = 0; c < DPN; ++c)
+          v[u][c] = halo[(2 * n + min(k + u, e1[p] - 1)) * DPN + c];
+#pragma unroll
+      for (int u = 0; u < kHaloX; ++u)
+        if (k + u < e1[p])
+#pragma unroll
+          for (int c = 0; c < DPN; ++c) acc[p][c] += v[u][c];
+    }
   double dsum = 0.0;
 #pragma unroll
   for (int p = 0; p < kHaloNpt; ++p) {
@@ -1151,9 +1172,9 @@ __global__ __launch_bounds__(256) void k_halo_sum(int64_t n, const int32_t *__re
     const int64_t g = h[p] & 0x3fffffff;
 #pragma unroll
     for (int c = 0; c < DPN; ++c) {
-      const T v = fixed ? (x ? x[g * DPN + c] : T(1)) : orphan ? T(0) : acc[p][c];
+      const T v = fixed ? xv[p][c] : orphan ? T(0) : acc[p][c];
       y[g * DPN + c] = v;
-      if (dot_part) dsum += double(x[g * DPN + c]) * double(v);
+      if (dot_part) dsum += double(xv[p][c]) * double(v);
     }
   }
   // dot_part: x.y over this workgroup's nodes plus its range of the tile partials
