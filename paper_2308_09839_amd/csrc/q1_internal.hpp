@@ -42,6 +42,7 @@ struct TileMap {
   uint16_t *lconn = nullptr;      // [n_steps*64][8] corner indices into the tile list (0xffff: empty)
   void *coef_t = nullptr;         // cell coefficients in lane order [ncoef][n_steps*64]
   int64_t n_reset = 0;            // shared or Dirichlet nodes, reset before each apply
+  bool orphans = false;           // some node belongs to no element (and so to no tile)
   int32_t *reset = nullptr;
   bool lds_atomic = false;        // corners collide within a step: accumulate with LDS atomics
   bool split = false;             // block variants: bitwise-reproducible split accumulation
@@ -142,6 +143,23 @@ int launch_apply_tile(Op &op, const void *x, void *y, hipStream_t s, const int *
 int64_t apply_dot_parts(const Op &op, int64_t *n_final);
 int launch_apply_dot(Op &op, const void *x, void *y, hipStream_t s, const int *stop,
                      double *parts);
+// The apply of launch_apply_dot with the solver's direction step in its staging: the test
+// after iteration `it` (see direction_test) and, unless it stops the solve, p_new = w r +
+// beta p_old, q = A p_new and the partials of p_new.q.  r and w are FP64 when wide, else of
+// the operator's dtype (as p); num, rr: nb partials each of rho_it and r.r.
+struct Status;
+struct DirStep {
+  const void *r, *w, *p_old;
+  void *p_new;
+  const double *num, *rr;
+  int nb;
+  double tol2;
+  int it, maxit;
+  bool wide;
+  Status *st;
+};
+bool apply_dir_ok(const Op &op);
+int launch_apply_dir(Op &op, const DirStep &d, void *q, hipStream_t s, double *parts);
 int launch_diag_tile(Op &op, void *d, hipStream_t s);
 // The diagonal on owner-computes tiles of tetrahedra (bitwise reproducible).
 int launch_diag_owner(Op &op, void *d, hipStream_t s);

@@ -20,7 +20,8 @@
 //   update     alpha = rho_k / p.q; x += alpha p; r -= alpha q;
 //              partials of rho_{k+1} = r.(w r) and of r.r
 //   direction  convergence test on r.r; beta = rho_{k+1} / rho_k;
-//              p = w r + beta p
+//              p = w r + beta p (within a batch of queued iterations, on the block and
+//              owner-computes operators, the next apply does this as it stages p)
 // Vectors are of the operator's type T (double or float); every dot product
 // accumulates in double.
 #include <hip/hip_runtime.h>
@@ -33,20 +34,13 @@
 #include <vector>
 
 #include "q1_internal.hpp"
+#include "q1_reduce.hpp"
 
 namespace q1 {
 
-constexpr int kRT = 256;      // threads per reduction block
-constexpr int kMaxRB = 1024;  // partial sums per reduction (4 blocks per compute unit)
 // partials of p.q that a block apply may form (tile and halo-sum workgroups); an
 // operator needing more takes the separate dot kernel
 constexpr int kMaxDotParts = 32768;
-
-// Device status record, read by the host every few iterations.
-struct Status {
-  int done, status, iter, pad;
-  double rr, bb, rho, aux;
-};
 
 // Workspace of q1_pcg_noalloc: the status record, the reduction partials and
 // the four solver vectors (r, p, q, w) of at most Q1_NOALLOC_MAX_DOF entries,
@@ -69,78 +63,6 @@ __global__ void k_clear_status(Status *st) {
   static_assert(sizeof(Status) % sizeof(int) == 0, "status record of whole words");
   int *w = reinterpret_cast<int *>(st);
   for (int i = threadIdx.x; i < int(sizeof(Status) / sizeof(int)); i += blockDim.x) w[i] = 0;
-}
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
-// Sum of N values over the block, returned to every thread (fixed order).
-template <int N>
-__device__ __forceinline__ void block_sum(double (&v)[N]) {
-  __shared__ double sh[N][kRT / 64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
-  __syncthreads();
-  if (lane == 0)
-#pragma unroll
-    for (int i = 0; i < N; ++i) sh[i][w] = v[i];
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    double s = sh[i][0];
-#pragma unroll
-    for (int k = 1; k < kRT / 64; ++k) s += sh[i][k];
-    v[i] = s;
-  }
-}
-
-// Re-reduce the partials written by an earlier kernel, R rows of cnt[r] >= 1
-// partials each: thread t adds partials t, t + 256, ... of each row in order,
-// then the fixed block sum (the same value in every block).  The loads of four
-// rounds are issued together, at clamped indices, before any of them is added.
-template <int R>
-__device__ __forceinline__ void sum_partials_nc(const double *const (&rows)[R],
-                                                const int (&cnt)[R], double (&out)[R]) {
-  constexpr int U = 4;
-  int m = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    out[r] = 0.0;
-    m = cnt[r] > m ? cnt[r] : m;
-  }
-  for (int j0 = int(threadIdx.x); j0 < m; j0 += U * kRT) {
-    double a[U][R];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int r = 0; r < R; ++r) a[u][r] = rows[r][min(j0 + u * kRT, cnt[r] - 1)];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (j0 + u * kRT < cnt[r]) out[r] += a[u][r];
-  }
-  block_sum<R>(out);
-}
-
-// the same with one count for every row
-template <int R>
-__device__ __forceinline__ void sum_partials_n(const double *const (&rows)[R], int nb,
-                                               double (&out)[R]) {
-  int cnt[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) cnt[r] = nb;
-  sum_partials_nc<R>(rows, cnt, out);
-}
-
-__device__ __forceinline__ double sum_partials(const double *__restrict__ part, int nb) {
-  double out[1];
-  sum_partials_n<1>({part}, nb, out);
-  return out[0];
 }
 
 struct Range {
@@ -220,8 +142,8 @@ template <typename T, bool FLEX, typename TP = T>
 __global__ __launch_bounds__(kRT) void k_pcg_update(
     int64_t n, const TP *__restrict__ p, const TP *__restrict__ q, const T *__restrict__ w,
     T *__restrict__ x, T *__restrict__ r, T *__restrict__ r_old,
-    const double *__restrict__ part_pq, int npq, const double *__restrict__ part_rho_k,
-    double *__restrict__ part_rho_k1, double *__restrict__ part_rr, Status *__restrict__ st) {
+    const double *__restrict__ part_pq, int npq, int k, double *__restrict__ part_rho_k1,
+    double *__restrict__ part_rr, Status *__restrict__ st) {
   // Nothing below depends on another load's result until alpha: the flag, the partials and
   // the first round of the vectors are requested together, one memory latency in all.
   const int done = st->done;
@@ -244,10 +166,9 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
     }
   };
   load(rg.i0 + threadIdx.x);
-  double t[2];
-  sum_partials_nc<2>({part_pq, part_rho_k}, {npq, nb}, t);
+  const double rho = st->rho2[k & 1];
+  const double pq = sum_partials(part_pq, npq);
   if (done) return;
-  const double pq = t[0], rho = t[1];
   if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       st->done = 1;
@@ -284,9 +205,8 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
 template <typename T, typename TP = T>
 __global__ __launch_bounds__(kRT) void k_pcg_direction(
     int64_t n, const T *__restrict__ r, const T *__restrict__ w, const T *__restrict__ z,
-    TP *__restrict__ p, const double *__restrict__ part_num, const double *__restrict__ part_den,
-    const double *__restrict__ part_rr, const double *__restrict__ part_bb, double tol2, int it,
-    int maxit, Status *__restrict__ st) {
+    TP *__restrict__ p, const double *__restrict__ part_num, const double *__restrict__ part_rr,
+    double tol2, int it, int maxit, Status *__restrict__ st) {
   const int done = st->done;  // as in k_pcg_update: one memory latency for all first loads
   const int nb = gridDim.x;
   const Range rg = block_range(n);
@@ -302,32 +222,15 @@ __global__ __launch_bounds__(kRT) void k_pcg_direction(
     }
   };
   load(rg.i0 + threadIdx.x);
-  double t[4];
-  sum_partials_n<4>({part_num, part_den, part_rr, part_bb}, nb, t);
+  double beta;
   if (done) return;
-  const double num = t[0], den = t[1], rr = t[2], bb = t[3];
-  const bool conv = rr <= tol2 * bb;
-  const bool bad = !isfinite(rr);
-  const bool stop = conv || bad || it >= maxit;
-  if (!stop) {
-    const double beta = num / den;
-    for (int64_t i0 = rg.i0 + threadIdx.x; i0 < rg.i1; i0 += U * kRT) {
-      if (i0 >= rg.i0 + U * kRT) load(i0);
+  if (direction_test(part_num, part_rr, nb, tol2, it, maxit, st, beta)) return;
+  for (int64_t i0 = rg.i0 + threadIdx.x; i0 < rg.i1; i0 += U * kRT) {
+    if (i0 >= rg.i0 + U * kRT) load(i0);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t i = i0 + u * kRT;
-        if (i < rg.i1) p[i] = TP(double(zv[u]) + beta * double(pv[u]));
-      }
-    }
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->iter = it;
-    st->rr = rr;
-    st->bb = bb;
-    st->rho = num;
-    if (stop) {
-      st->done = 1;
-      st->status = conv ? Q1_OK : (bad ? Q1_EBREAKDOWN : Q1_ENOCONV);
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * kRT;
+      if (i < rg.i1) p[i] = direction_value<TP>(zv[u], pv[u], beta);
     }
   }
 }
@@ -636,6 +539,7 @@ namespace {
 struct Work {
   void *r = nullptr, *p = nullptr, *q = nullptr, *w = nullptr, *r_old = nullptr,
        *z = nullptr;
+  void *p2 = nullptr;      // second direction buffer (applies that take the direction step)
   double *part = nullptr;  // [8][kMaxRB]
   double *dparts = nullptr;  // [kMaxDotParts]: p.q partials formed by the apply
   Status *st = nullptr;    // device
@@ -645,12 +549,20 @@ struct Work {
   Work(const Work &) = delete;
   ~Work() {
     if (!owned) return;
-    void *d[] = {r, p, q, w, r_old, z, part, dparts, st};
+    void *d[] = {r, p, q, w, r_old, z, p2, part, dparts, st};
     for (void *v : d)
       if (v) (void)hipFree(v);
     if (hst) (void)hipHostFree(hst);
   }
 };
+
+// The second direction buffer; false (no error left behind) when device memory is short.
+bool second_buffer(void **p, size_t bytes) {
+  if (*p || hipMalloc(p, bytes) == hipSuccess) return true;
+  *p = nullptr;
+  (void)hipGetLastError();
+  return false;
+}
 
 int nblocks_for(int64_t n) {
   const int64_t b = (n + int64_t(kRT) * 8 - 1) / (int64_t(kRT) * 8);
@@ -752,10 +664,16 @@ int pcg_t(Op &op, int pc, const T *b, T *x, double rtol, int maxit, q1_stats *st
   const int64_t need_dot = apply_dot_parts(op, &n_dot);
   const bool fused_dot = need_dot > 0 && need_dot <= kMaxDotParts && W.dparts;
   const int npq = fused_dot ? int(n_dot) : nb;
+  // within a batch of iterations the apply takes the previous iteration's direction step
+  // where it can (p then alternates between two buffers, if the second one fits)
+  const bool fused_dir = fused_dot && W.owned && apply_dir_ok(op) &&
+                         second_buffer(&W.p2, size_t(n) * sizeof(T));
+  T *p_alt = static_cast<T *>(W.p2);
   hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, W.st);
   hipLaunchKernelGGL((k_pcg_init<T>), dim3(nb), dim3(kRT), 0, s, n, b, w, x, r, p, part_rho[0],
                      part_bb, 1);
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRT), 0, s, part_bb, nb, &W.st->bb);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRT), 0, s, part_rho[0], nb, &W.st->rho2[0]);
   Q1_HIP(hipGetLastError());
   if ((rc = read_status(W, s))) return rc;
   const double bb = W.hst->bb;
@@ -772,18 +690,23 @@ int pcg_t(Op &op, int pc, const T *b, T *x, double rtol, int maxit, q1_stats *st
       const int m = std::min(batch, maxit - launched);
       for (int j = 0; j < m; ++j) {
         const int k = launched + j;
-        if (fused_dot) {  // p.q partials formed by the apply
+        if (fused_dir && j > 0) {  // the test and the direction of iteration k, then the apply
+          const DirStep d{r,  w,    p, p_alt,  part_rho[k & 1], part_rr,
+                          nb, tol2, k, maxit, sizeof(T) == 8,  W.st};
+          if ((rc = launch_apply_dir(op, d, q, s, W.dparts))) return rc;
+          std::swap(p, p_alt);
+        } else if (fused_dot) {  // p.q partials formed by the apply
           if ((rc = launch_apply_dot(op, p, q, s, &W.st->done, W.dparts))) return rc;
         } else {
           if ((rc = launch_apply(op, p, q, s, &W.st->done))) return rc;
           hipLaunchKernelGGL((k_dot<T>), dim3(nb), dim3(kRT), 0, s, n, p, q, part_pq, W.st);
         }
         hipLaunchKernelGGL((k_pcg_update<T, false>), dim3(nb), dim3(kRT), 0, s, n, p, q, w, x, r,
-                           nullptr, fused_dot ? W.dparts : part_pq, npq, part_rho[k & 1],
+                           nullptr, fused_dot ? W.dparts : part_pq, npq, k,
                            part_rho[(k + 1) & 1], part_rr, W.st);
-        hipLaunchKernelGGL((k_pcg_direction<T>), dim3(nb), dim3(kRT), 0, s, n, r, w, nullptr, p,
-                           part_rho[(k + 1) & 1], part_rho[k & 1], part_rr, part_bb, tol2, k + 1,
-                           maxit, W.st);
+        if (!fused_dir || j + 1 == m)
+          hipLaunchKernelGGL((k_pcg_direction<T>), dim3(nb), dim3(kRT), 0, s, n, r, w, nullptr, p,
+                             part_rho[(k + 1) & 1], part_rr, tol2, k + 1, maxit, W.st);
         while (next_snap < snap.n && snap.iters[next_snap] == k + 1)
           Q1_HIP(hipMemcpyAsync(snap.dst[next_snap++], x, size_t(n) * sizeof(T),
                                 hipMemcpyDeviceToDevice, s));
@@ -1010,14 +933,14 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
   Work W;  // FP64 residual and inverse diagonal, partials and status
   int rc = alloc_work<double>(W, n, false);
   if (rc) return rc;
-  float *p = nullptr, *q = nullptr;  // FP32 directions
+  float *p = nullptr, *q = nullptr, *p_alt = nullptr;  // FP32 directions
   struct Free {
-    float **a, **b;
+    float **a, **b, **c;
     ~Free() {
-      if (*a) (void)hipFree(*a);
-      if (*b) (void)hipFree(*b);
+      for (float **v : {a, b, c})
+        if (*v) (void)hipFree(*v);
     }
-  } fr{&p, &q};
+  } fr{&p, &q, &p_alt};
   Q1_HIP(hipMalloc(&p, size_t(n) * sizeof(float)));
   Q1_HIP(hipMalloc(&q, size_t(n) * sizeof(float)));
   const auto t0 = std::chrono::steady_clock::now();
@@ -1032,12 +955,15 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
   const int64_t need_dot = apply_dot_parts(A32, &n_dot);
   const bool fused_dot = need_dot > 0 && need_dot <= kMaxDotParts && W.dparts;
   const int npq = fused_dot ? int(n_dot) : nb;
+  const bool fused_dir = fused_dot && apply_dir_ok(A32) &&  // as in pcg_t
+                         second_buffer(reinterpret_cast<void **>(&p_alt), size_t(n) * sizeof(float));
   Q1_HIP(hipMemsetAsync(W.st, 0, sizeof(Status), s));
   // x = 0, r = b, partials of rho_0 = b.(w b) and b.b; p = (float) (w b)
   hipLaunchKernelGGL((k_pcg_init<double>), dim3(nb), dim3(kRT), 0, s, n, b, w, x, r, nullptr,
                      part_rho[0], part_bb, 0);
   hipLaunchKernelGGL(k_direction_start, grid1(n), dim3(256), 0, s, n, w, r, p);
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRT), 0, s, part_bb, nb, &W.st->bb);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRT), 0, s, part_rho[0], nb, &W.st->rho2[0]);
   Q1_HIP(hipGetLastError());
   if ((rc = read_status(W, s))) return rc;
   const double bb = W.hst->bb;
@@ -1052,9 +978,15 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
       int batch = 1;
       bool stop = false;
       while (!stop && k < maxit) {
-        const int m = std::min(batch, maxit - k);
+        const int m = std::min(batch, maxit - k), k0 = k;
+        float *const at_start[2] = {p, p_alt};
         for (int j = 0; j < m; ++j, ++k) {
-          if (fused_dot) {
+          if (fused_dir && j > 0) {
+            const DirStep d{r,  w,        p, p_alt, part_rho[k & 1], part_rr,
+                            nb, thr / bb, k, maxit, true,           W.st};
+            if ((rc = launch_apply_dir(A32, d, q, s, W.dparts))) return rc;
+            std::swap(p, p_alt);
+          } else if (fused_dot) {
             if ((rc = launch_apply_dot(A32, p, q, s, &W.st->done, W.dparts))) return rc;
           } else {
             if ((rc = launch_apply(A32, p, q, s, &W.st->done))) return rc;
@@ -1062,15 +994,21 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
                                W.st);
           }
           hipLaunchKernelGGL((k_pcg_update<double, false, float>), dim3(nb), dim3(kRT), 0, s, n,
-                             p, q, w, x, r, nullptr, fused_dot ? W.dparts : part_pq, npq,
-                             part_rho[k & 1], part_rho[(k + 1) & 1], part_rr, W.st);
-          hipLaunchKernelGGL((k_pcg_direction<double, float>), dim3(nb), dim3(kRT), 0, s, n, r,
-                             w, nullptr, p, part_rho[(k + 1) & 1], part_rho[k & 1], part_rr,
-                             part_bb, thr / bb, k + 1, maxit, W.st);
+                             p, q, w, x, r, nullptr, fused_dot ? W.dparts : part_pq, npq, k,
+                             part_rho[(k + 1) & 1], part_rr, W.st);
+          if (!fused_dir || j + 1 == m)
+            hipLaunchKernelGGL((k_pcg_direction<double, float>), dim3(nb), dim3(kRT), 0, s, n, r,
+                               w, nullptr, p, part_rho[(k + 1) & 1], part_rr, thr / bb, k + 1,
+                               maxit, W.st);
         }
         Q1_HIP(hipGetLastError());
         if ((rc = read_status(W, s))) return rc;
         stop = W.hst->done != 0;
+        if (stop && fused_dir && W.hst->iter > k0) {  // the buffer of the last direction used
+          const int j = (W.hst->iter - 1 - k0) & 1;
+          p = at_start[j];
+          p_alt = at_start[j ^ 1];
+        }
         batch = std::min(batch * 2, 32);
       }
       if (W.hst->done && W.hst->status == Q1_EBREAKDOWN) {
@@ -1097,8 +1035,7 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
       // continue from the true residual, keeping p: beta = rho(new r) / rho_{k-1}
       hipLaunchKernelGGL(k_clear_done, dim3(1), dim3(1), 0, s, W.st);
       hipLaunchKernelGGL((k_pcg_direction<double, float>), dim3(nb), dim3(kRT), 0, s, n, r, w,
-                         nullptr, p, part_rho[k & 1], part_rho[(k + 1) & 1], part_rr, part_bb,
-                         0.0, k, maxit + 1, W.st);
+                         nullptr, p, part_rho[k & 1], part_rr, 0.0, k, maxit + 1, W.st);
       Q1_HIP(hipGetLastError());
     }
   }

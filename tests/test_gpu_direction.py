@@ -1,0 +1,68 @@
+"""The direction step inside the apply: q1_pcg, whose applies take the step of the iteration
+before within a batch of iterations, against q1_pcg_noalloc, which keeps the separate kernel.
+Both round the step the same way and sum in the same order, so everything is compared for
+equality: on lattice, jittered, affine and tetrahedral tiles and on a mesh with unused nodes (which
+no tile stages), at iteration limits on both sides of the batch edges (1, 2, 4, ...) and where
+the solve converges inside a batch.  The mixed solver restarts from inside a batch: it must
+reach its tolerance in about the iterations of FP64 PCG whatever the refresh factor."""
+import numpy as np
+import pytest
+
+import seeded_inputs as si
+from helpers import dev, make_op, problem
+
+pytestmark = pytest.mark.gpu
+
+
+def case(physics, n, jitter, unused=0):
+    pr = problem(physics, n, jitter, 95, True)
+    if unused:
+        extra = np.zeros((3, unused)) + 7.0
+        pr["xyz"] = np.concatenate([pr["xyz"], extra], axis=1)
+        pr["mask"] = np.concatenate([pr["mask"], np.zeros(unused, dtype=pr["mask"].dtype)])
+    dpn = 1 if physics == 1 else 3
+    b = si.vec_uniform(pr["xyz"].shape[1] * dpn, 95, si.STREAM_RHS)
+    b[np.repeat(pr["mask"].astype(bool), dpn)] = 0.0
+    if unused:
+        b[-unused * dpn:] = 0.0
+    return pr, b
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("physics,n,jitter,unused", [
+    (1, (32, 16, 8), 0.0, 0), (1, (17, 9, 5), 0.0, 0), (1, (13, 11, 9), 0.1, 0),
+    (1, (1, 1, 1), 0.0, 0), (2, (9, 8, 7), 0.1, 0), (3, (16, 8, 6), 0.0, 0),
+    (3, (9, 8, 7), 0.1, 0), (1, (9, 8, 7), 0.1, 3)])
+def test_direction_in_apply(physics, n, jitter, unused, dtype):
+    import torch
+    import paper_2308_09839_amd as q1
+    print(f"\n[direction] physics={physics} n={n} unused={unused} dtype={dtype}", flush=True)
+    pr, b = case(physics, n, jitter, unused)
+    op = make_op(pr, dtype, 0)
+    bd = dev(b, torch.float64 if dtype == 0 else torch.float32)
+    for rtol, maxit in ((0.0, 1), (0.0, 2), (0.0, 3), (0.0, 4), (0.0, 12), (1e-4, 5000)):
+        x, ref = torch.full_like(bd, 3.0), torch.full_like(bd, -5.0)
+        st = q1.q1_pcg(op, 1, bd, x, rtol, maxit)
+        st_ref = q1.q1_pcg_noalloc(op, 1, bd, ref, rtol, maxit)
+        for key in ("status", "iters", "true_rel_res"):
+            assert st[key] == st_ref[key] or (st[key] != st[key] and st_ref[key] != st_ref[key]), \
+                (maxit, key, st[key], st_ref[key])
+        assert np.array_equal(x.cpu().numpy(), ref.cpu().numpy(), equal_nan=True), maxit
+
+
+@pytest.mark.parametrize("physics,n,jitter", [(1, (16, 8, 8), 0.0), (1, (11, 9, 8), 0.1),
+                                              (3, (8, 7, 6), 0.1)])
+@pytest.mark.parametrize("delta", [0.5, 0.1, 0.013])
+def test_mixed_restarts(orc, physics, n, jitter, delta):
+    import torch
+    import paper_2308_09839_amd as q1
+    print(f"\n[mixed restarts] physics={physics} n={n} delta={delta}", flush=True)
+    pr, b = case(physics, n, jitter)
+    A = orc.assemble(physics, pr["xyz"], pr["conn"], pr["coef"], pr["mask"])
+    bd = dev(b, torch.float64)
+    xd = torch.full_like(bd, 7.0)
+    st = q1.q1_mpcg(make_op(pr, 0, 0), make_op(pr, 1, 0), bd, xd, 1e-10, delta, 20000)
+    assert st["status"] == 0
+    assert orc.true_rel_res(A, xd.cpu().numpy(), b) <= 1e-10 * (1 + 1e-3)
+    ref = orc.pcg(A, b, rtol=1e-10)
+    assert st["iters"] <= 1.25 * ref.iters + 5, (st["iters"], ref.iters)
