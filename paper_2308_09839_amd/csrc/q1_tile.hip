@@ -1305,6 +1305,7 @@ struct HostTiles {
   bool corner_collision = false;   // two lanes of a step share a node at one corner
   std::vector<uint8_t> tile_affine;  // every element of the tile is a parallelepiped
   std::vector<int32_t> slot, hptr, hnode;  // halo slots of the block variant
+  bool orphans = false;            // some node, free or Dirichlet, belongs to no element
   std::vector<uint32_t> tile_lat;    // lattice description of each tile (0: none)
   bool split = true;                 // every tile admits the split accumulation
   std::vector<uint32_t> tile_addr;   // lattice addressing: kAddrValid | face bits, or 0
@@ -1561,6 +1562,7 @@ int plan_tiles(const std::vector<int32_t> &conn, const std::vector<T> &xyz,
     const int32_t g = H.reset[j];
     const bool fixed = !mask.empty() && mask[g];
     hp[j + 1] = hp[j] + (fixed ? 0 : std::max(0, ntile[g] - 2));
+    H.orphans = H.orphans || ntile[g] == 0;
     H.hnode[j] = fixed            ? int32_t(uint32_t(g) | 0x80000000u)
                  : ntile[g] == 0 ? int32_t(uint32_t(g) | 0x40000000u)
                                  : g;
@@ -1757,9 +1759,7 @@ int build_tiles_t(Op &op, hipStream_t s, int patch_x, int patch_y, int layers) {
   tm.max_nodes = H.max_nodes;
   tm.n_reset = int64_t(H.reset.size());
   tm.n_entries = int64_t(H.nodes.size());
-  tm.orphans = std::any_of(H.hnode.begin(), H.hnode.end(), [](int32_t h) {
-    return h >= 0 && (uint32_t(h) & 0x40000000u);
-  });
+  tm.orphans = H.orphans;
   tm.lds_atomic = H.corner_collision;
   tm.split = block && hex && H.split && !H.corner_collision;
   tm.all_affine = std::all_of(H.tile_affine.begin(), H.tile_affine.end(),

@@ -14,12 +14,13 @@ from helpers import dev, make_op, problem
 pytestmark = pytest.mark.gpu
 
 
-def case(physics, n, jitter, unused=0):
+def case(physics, n, jitter, unused=0, held=0):
     pr = problem(physics, n, jitter, 95, True)
     if unused:
         extra = np.zeros((3, unused)) + 7.0
         pr["xyz"] = np.concatenate([pr["xyz"], extra], axis=1)
         pr["mask"] = np.concatenate([pr["mask"], np.zeros(unused, dtype=pr["mask"].dtype)])
+        pr["mask"][pr["mask"].size - held:] = 1  # Dirichlet nodes that no element references
     dpn = 1 if physics == 1 else 3
     b = si.vec_uniform(pr["xyz"].shape[1] * dpn, 95, si.STREAM_RHS)
     b[np.repeat(pr["mask"].astype(bool), dpn)] = 0.0
@@ -48,6 +49,30 @@ def test_direction_in_apply(physics, n, jitter, unused, dtype):
             assert st[key] == st_ref[key] or (st[key] != st[key] and st_ref[key] != st_ref[key]), \
                 (maxit, key, st[key], st_ref[key])
         assert np.array_equal(x.cpu().numpy(), ref.cpu().numpy(), equal_nan=True), maxit
+
+
+def test_held_unused_nodes():
+    """Dirichlet nodes that no element references belong to no tile either; what the second
+    direction buffer held before the solve must not be read there."""
+    import torch
+    import paper_2308_09839_amd as q1
+    print("\n[direction, held unused nodes]", flush=True)
+    pr, b = case(1, (9, 8, 7), 0.1, 3, 2)
+    op = make_op(pr, 0, 0)
+    b[-2:] = (0.5, -2.0)
+    bd = dev(b)
+    fill = [torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+            for n in (bd.numel(), 4 * bd.numel(), 1 << 20)]
+    del fill
+    torch.cuda.empty_cache()
+    x, ref = torch.full_like(bd, 3.0), torch.full_like(bd, -5.0)
+    st = q1.q1_pcg(op, 1, bd, x, 1e-8, 500)
+    st_ref = q1.q1_pcg_noalloc(op, 1, bd, ref, 1e-8, 500)
+    assert st["status"] == st_ref["status"] == 0 and st["iters"] == st_ref["iters"]
+    assert np.array_equal(x.cpu().numpy(), ref.cpu().numpy())
+    # the operator is the identity there: |x_i - b_i| = |r_i| <= |r| <= rtol |b|
+    held = np.abs(x.cpu().numpy()[-2:] - b[-2:])
+    assert held.max() <= 1e-8 * np.linalg.norm(b) * (1 + 1e-3)
 
 
 @pytest.mark.parametrize("physics,n,jitter", [(1, (16, 8, 8), 0.0), (1, (11, 9, 8), 0.1),
