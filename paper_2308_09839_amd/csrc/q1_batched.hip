@@ -1,20 +1,21 @@
 // Batched persistent Jacobi-PCG: many independent scalar-Laplace problems,
 // each with up to four right-hand sides, solved by ONE cooperative launch.
 //
-// Each problem p owns a contiguous range of single-wavefront workgroups
-// (sized in proportion to its expected work).  The waves of a problem meet at
-// a two-level barrier of global counters; problems never wait for each
+// Each problem p owns a contiguous range of workgroups of one or four
+// wavefronts (sized in proportion to its expected work), which meet at
+// a barrier of global counters and flags; problems never wait for each
 // other.  Vectors are stored interleaved [node][R] so that one gather of a
 // node serves all R right-hand sides.  Per iteration (the CG operations of
 // Table 4, regrouped):
 //   P1  over the operator's LDS tiles (as in q1_tile.hip): the direction
 //       update p = D^{-1} r + beta p_old on each tile's nodes into LDS (the
-//       node's writer entry also stores it, and q = p on Dirichlet nodes,
-//       their rows of A p), then q = A p from the staged p, with the partials
-//       of p^T A p (element energies sum_e p_e^T A_e p_e and p^2 on Dirichlet
-//       nodes).  p alternates between two buffers, so reading p_old and
-//       writing p needs no barrier in between.
-//   P2  alpha = rho / p^T A p; x += alpha p; r -= alpha q; q = 0 once read;
+//       node's writer entry also stores it), then the tile's part of q = A p
+//       from the staged p, written to the tile's slot of each of its free nodes,
+//       with the partials of p^T A p (p times the tile's sums, and p^2 on
+//       Dirichlet nodes by the writer entry).  p alternates between two buffers,
+//       so reading p_old and writing p needs no barrier in between.
+//   P2  q of a node = the sum of its slots (contiguous, in tile order; p on a
+//       Dirichlet node); alpha = rho / p^T A p; x += alpha p; r -= alpha q;
 //       partials of rho' = r^T D^{-1} r and r^T r; then the convergence test
 //       and beta = rho'/rho for the next P1
 // with one barrier after each phase.  In the mixed-precision form the search
@@ -52,20 +53,42 @@ constexpr int kRmax = 4;
 constexpr uint32_t kSharedBitB = 0x80000000u;
 constexpr uint32_t kFixedBitB = 0x40000000u;
 constexpr uint32_t kIdMaskB = 0x3fffffffu;
-// In the per-problem copy of the tile node lists the search-direction phase
-// reads, bit 29 marks the one entry (in the first tile holding the node) that
+// In the copy of the tile node lists the search-direction phase reads, bit 29
+// (kOwnEntry) marks the one entry (in the first tile holding the node) that
 // writes the node's new direction; ids are then below 2^29.
-constexpr uint32_t kOwnBitB = 0x20000000u;
-constexpr uint32_t kIdMaskOwnB = 0x1fffffffu;
+constexpr uint32_t kIdMaskOwnB = kOwnEntry - 1;
 constexpr unsigned kSpinLimit = 1u << 26;  // barrier polls before giving up
-// Nodes per lane per round in the vector phases: every load of a round is
-// issued before its stores (gfx9 waits for loads and stores on one counter, so
-// a round costs one load and one store latency whatever kU is).
-constexpr int kU = 4;
-constexpr int kStage = 8;  // node ids per lane per staging round of a tile
+// In the staging, the write-back and the vector phases a lane takes one right-hand side of a
+// node: 64 / R nodes per instruction, so that the R values of a node (32 bytes for R = 4) and
+// its neighbours' leave in whole lines.  (One node with all its R values per lane fetched every
+// line R times, since these accesses bypass the caches.)
+// Rounds issue all their loads before their stores: gfx9 waits for loads and stores on one
+// counter, so a round costs one load and one store latency whatever its length is.
+// A workgroup is NW wavefronts: four on parallelepiped tiles, which then stage, compute and
+// write one tile together (one step of 64 elements each, the right-hand sides in turn, so that
+// three fit a SIMD), and one otherwise (general elements keep their geometry for all sides at
+// once, in 256 and more registers).  Twelve problems of 16^3 to 40^3 with four right-hand sides:
+// 74 us per iteration with one wave per workgroup, 57 with four.
+template <int R, int NW>
+struct Lanes {
+  static constexpr int NLW = kW / R;    // nodes per instruction of a wave
+  static constexpr int NL = NLW * NW;   // and of the workgroup
+  // nodes per lane per round: of the vector phases, of a tile's staging and of its node words
+  static constexpr int kU = NW > 1 || R == 1 ? 4 : 6;
+  static constexpr int kStage = NW > 1 ? 2 * R : R == 1 ? 8 : 12;
+  static constexpr int kIds = NW > 1 ? 2 : 8;
+  int c, sub;                           // right-hand side and node of this lane
+  bool act;                             // R = 3 leaves one lane of a wave idle
+  __device__ Lanes() {
+    const int lane = threadIdx.x & (kW - 1), wave = threadIdx.x / kW;
+    c = lane % R;
+    sub = wave * NLW + lane / R;
+    act = lane < NLW * R;
+  }
+};
 
 // partial-sum slots per problem: [slot][rhs][nwg]
-enum { kEnergy = 0, kMp2 = 1, kRho = 2, kRR = 3, kBB = 4, kRho0 = 5, kSlots = 6 };
+enum { kPQ = 0, kRho = 1, kRR = 2, kBB = 3, kRho0 = 4, kSlots = 5 };
 
 struct BProb {
   int64_t nn;
@@ -77,19 +100,22 @@ struct BProb {
   const uint4 *lconn;
   const double *coef_t;
   const double *xyz;
-  const int32_t *reset;
-  int64_t n_reset;
   const uint8_t *mask;
-  double *b, *x, *r, *q;      // [nn][R]
+  const uint32_t *nptr;       // [nn + 1]: first slot of a node (bit 31: Dirichlet, no slots)
+  const int32_t *pos;         // [entries]: slot of a tile entry (-1 on Dirichlet nodes)
+  int64_t n_slots;
+  double *b, *x, *r;          // [nn][R]
+  double *q;                  // [n_slots][R]
   double *p[2];               // [nn][R]: directions of odd and even iterations
   const double *w;            // inverse diagonal [nn]
   // mixed precision: FP32 geometry, coefficients and directions; FP64 refresh output
   const float *xyz32, *coef32;
-  float *p32[2], *q32;        // [nn][R]
-  double *t;                  // [nn][R]
+  float *p32[2];              // [nn][R]
+  float *q32;                 // [n_slots][R]
+  double *t;                  // [n_slots][R]
   double *part;               // [kSlots][R][nwg]
-  double *tot;                // [kSub + 1][2R] sub-group and problem totals
-  unsigned *bar;              // [kBarWords]: two-level barrier counters, generation
+  double *tot;                // [2][kSub][2R] sub-group totals, two buffers
+  unsigned *bar;              // [kBarWords]: sub-group counters and flags
   int wg0, nwg;
   int *iters, *status, *nref; // [R]
   double *rr, *bb;            // [R]
@@ -114,14 +140,17 @@ struct BProbG {
   const Q1_GLB uint4 *lconn;
   const Q1_GLB double *coef_t;
   const Q1_GLB double *xyz;
-  const Q1_GLB int32_t *reset;
-  int64_t n_reset;
   const Q1_GLB uint8_t *mask;
-  Q1_GLB double *b, *x, *r, *q;
+  const Q1_GLB uint32_t *nptr;
+  const Q1_GLB int32_t *pos;
+  int64_t n_slots;
+  Q1_GLB double *b, *x, *r;
+  Q1_GLB double *q;
   Q1_GLB double *p[2];
   const Q1_GLB double *w;
   const Q1_GLB float *xyz32, *coef32;
-  Q1_GLB float *p32[2], *q32;
+  Q1_GLB float *p32[2];
+  Q1_GLB float *q32;
   Q1_GLB double *t;
   Q1_GLB double *part;
   Q1_GLB double *tot;
@@ -131,7 +160,7 @@ struct BProbG {
   Q1_GLB double *rr, *bb;
 };
 static_assert(sizeof(BProbG) == sizeof(BProb) && offsetof(BProbG, bb) == offsetof(BProb, bb) &&
-                  offsetof(BProbG, n_reset) == offsetof(BProb, n_reset) &&
+                  offsetof(BProbG, n_slots) == offsetof(BProb, n_slots) &&
                   offsetof(BProbG, wg0) == offsetof(BProb, wg0),
               "BProbG must mirror BProb");
 
@@ -149,9 +178,10 @@ __device__ __forceinline__ BProb load_problem(const BProb *src) {
   P.lconn = (const uint4 *)G.lconn;
   P.coef_t = (const double *)G.coef_t;
   P.xyz = (const double *)G.xyz;
-  P.reset = (const int32_t *)G.reset;
-  P.n_reset = G.n_reset;
   P.mask = (const uint8_t *)G.mask;
+  P.nptr = (const uint32_t *)G.nptr;
+  P.pos = (const int32_t *)G.pos;
+  P.n_slots = G.n_slots;
   P.b = (double *)G.b;
   P.x = (double *)G.x;
   P.r = (double *)G.r;
@@ -179,57 +209,104 @@ __device__ __forceinline__ BProb load_problem(const BProb *src) {
 }
 #undef Q1_GLB
 
+// Every value that one wave writes and another reads within the launch (r, p, q, the partial
+// sums and totals; x and t of the mixed form) is read and written with these: relaxed atomics
+// at agent scope, which go past the caches of the accelerator dies to the point where all
+// dies see the same memory.  settle() waits until this wave's earlier accesses have been
+// performed there, so what it then announces (a counter, a generation) can only be seen
+// after them.
+template <typename E>
+__device__ __forceinline__ E get(const E *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename E>
+__device__ __forceinline__ void put(E *p, E v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void settle() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 __device__ __forceinline__ double wave_sum64(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
 
-// Barrier of the nwg waves of one problem, optionally fused with the sum of two
-// partial-sum slots (sa, sb; sa < 0 for none) over the waves; false when the
-// spin limit was hit.  Two levels, so neither arrivals nor polling meet on one
-// address and no wave reads all nwg partials: wave me belongs to sub-group
-// me % kSub, whose counter and generation copy share a cache line of their
-// own.  The last arrival of a sub-group sums its members' partials (in member
-// order) into the sub-group's totals, resets the counter and arrives at the top
-// counter; the last top arrival sums the sub-group totals (in sub-group order),
-// writes the problem's totals, resets the top counter and writes the new
-// generation into every copy, which the waves poll.  Every wave then reads the
-// same totals, so all waves hold bit-identical scalars and take the same branch.
-// Ordering: the counters, generation copies and polls are relaxed atomics,
-// ordered by explicit fences (a release fence before each arrival, an acquire
-// fence after it is known to be complete), so each wave writes back and
-// invalidates its L2 once per barrier instead of once per poll.
-// bar: [0] top count, [32 (1 + k)] sub-counter k, [32 (1 + k) + 1] its generation.
-// tot: [kSub][2R] sub-group totals, then [2R] problem totals.
-constexpr unsigned kSub = 8;
-constexpr unsigned kBarWords = 32 * (kSub + 1);
+// Sum of v over the lanes of this lane's right-hand side (lane % R), in every such lane.
+template <int R>
+__device__ __forceinline__ double rhs_sum(double v, int lane) {
+  if constexpr (R == 3) {
+    double t = 0.0;
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+      const double w = wave_sum64(lane % R == c && lane < kW - 1 ? v : 0.0);
+      if (lane % R == c) t = w;
+    }
+    return t;
+  } else {
+#pragma unroll
+    for (int off = 32; off >= R; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+  }
+}
+
+// The same over the NW waves of the workgroup, in wave order.
+template <int R, int NW>
+__device__ __forceinline__ double group_sum(double v, int lane) {
+  v = rhs_sum<R>(v, lane);
+  if constexpr (NW > 1) {
+    __shared__ double sh[NW][R];
+    const int wave = threadIdx.x / kW;
+    if (lane < R) sh[wave][lane] = v;
+    __syncthreads();
+    v = sh[0][lane % R];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += sh[w][lane % R];
+    __syncthreads();
+  }
+  return v;
+}
+
+// Barrier of the nwg workgroups of one problem (one wave of each), optionally fused with the
+// sum of two partial-sum slots (sa, sb; either < 0 for none) over the workgroups; false when
+// the spin limit was hit.  Workgroup me belongs to sub-group me % kSub, whose counter and flag
+// share a cache line of their own.  The last arrival of a sub-group sums its members' partials
+// (in member order) into the sub-group's totals, resets the counter and raises the flag to
+// this barrier's number.  Every workgroup polls all the flags (a lane each) and then adds the
+// sub-groups' totals in order, so every lane holds bit-identical totals of its right-hand side
+// (a, b) and all take the same branch.  The totals alternate between two buffers: a sub-group
+// can only come to the barrier after the next once everyone has left this one (it needs their arrival at the next).
+// Ordering: every exchanged value is accessed past the caches (get, put) and each arrival and
+// flag is preceded by settle(), so no wave writes back or invalidates an L2.  Agent-scope
+// fences at each arrival did so for the die's whole L2, one wave after another: an iteration of
+// twelve problems (16^3 to 40^3, one right-hand side) took 151 us, 47 without them and 34 now.
+// A further counter over the sub-groups, whose last arrival makes the totals and releases
+// everyone, costs four more memory round trips: 16^3 with four right-hand sides 20.1 us per
+// iteration against 18.4.  Sub-groups: arrivals on one counter are served one by one, while each
+// workgroup polls all the flags; 40^3 with four right-hand sides (400 workgroups): 4
+// sub-groups 43 us per iteration, 8 37, 16 33, 32 36.
+// bar: [32 k] counter of sub-group k, [32 k + 1] its flag.  tot: [2][kSub][2R].
+constexpr unsigned kSub = 16;
+constexpr unsigned kBarWords = 32 * kSub;
 template <int R>
 __device__ __forceinline__ bool problem_sync(const BProb &P, unsigned me, unsigned nwg,
-                                             int *error, int sa, int sb, double (&a)[R],
-                                             double (&b)[R]) {
+                                             int *error, unsigned &gen, int sa, int sb, double &a,
+                                             double &b) {
   const int lane = threadIdx.x;
-  unsigned *bar = P.bar;
-  double *sub_tot = P.tot, *all_tot = P.tot + kSub * 2 * R;
   const unsigned nsub = nwg < kSub ? nwg : kSub;  // sub-groups in use
   const unsigned sub = me % nsub;
   const unsigned members = (nwg - sub + nsub - 1) / nsub;
-  unsigned *sc = bar + 32 * (1 + sub);
-  unsigned gen = 0;
-  int sub_last = 0;
-  // the generation is read before the fence, which waits for the read to return
-  // and so orders it before this wave's arrival
-  if (lane == 0) gen = __hip_atomic_load(sc + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // this wave's writes, all XCDs
-  if (lane == 0) {
-    sub_last = __hip_atomic_fetch_add(sc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-               members - 1;
-  }
-  gen = __shfl(gen, 0);
-  sub_last = __shfl(sub_last, 0);
-  int top_last = 0;
-  if (sub_last) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  unsigned *sc = P.bar + 32 * sub;
+  double *tot = P.tot + (gen & 1) * (kSub * 2 * R);
+  ++gen;
+  int last = 0;
+  settle();  // this wave's writes
+  if (lane == 0)
+    last = __hip_atomic_fetch_add(sc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           members - 1;
+  if (__shfl(last, 0)) {
     if (sa >= 0) {
       double va[R], vb[R];
 #pragma unroll
@@ -238,92 +315,115 @@ __device__ __forceinline__ bool problem_sync(const BProb &P, unsigned me, unsign
         const int64_t w = sub + int64_t(k) * nsub;
 #pragma unroll
         for (int c = 0; c < R; ++c) {
-          va[c] += P.part[(int64_t(sa) * R + c) * nwg + w];
-          vb[c] += P.part[(int64_t(sb) * R + c) * nwg + w];
+          va[c] += get(&P.part[(int64_t(sa) * R + c) * nwg + w]);
+          if (sb >= 0) vb[c] += get(&P.part[(int64_t(sb) * R + c) * nwg + w]);
         }
       }
 #pragma unroll
       for (int c = 0; c < R; ++c) {
         va[c] = wave_sum64(va[c]);
-        vb[c] = wave_sum64(vb[c]);
+        if (sb >= 0) vb[c] = wave_sum64(vb[c]);
       }
       if (lane == 0) {
 #pragma unroll
         for (int c = 0; c < R; ++c) {
-          sub_tot[sub * 2 * R + c] = va[c];
-          sub_tot[sub * 2 * R + R + c] = vb[c];
+          put(&tot[sub * 2 * R + c], va[c]);
+          put(&tot[sub * 2 * R + R + c], vb[c]);
         }
       }
     }
-    // every member has arrived: the counter is reset before the release fence,
-    // so the reset is complete before anyone can pass this barrier
-    if (lane == 0) __hip_atomic_store(sc, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    if (lane == 0) {
-      top_last = __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                 nsub - 1;
-    }
-    top_last = __shfl(top_last, 0);
+    // every member has arrived: the counter is reset before settle(), so the reset is
+    // complete before anyone can pass this barrier
+    if (lane == 0) put(sc, 0u);
+    settle();
+    if (lane == 0) put(sc + 1, gen);
   }
+  // wait until every sub-group's flag has come to this barrier (the faster ones may show the
+  // next one already, but no further: that needs this workgroup)
   bool ok = true;
-  if (top_last) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (sa >= 0 && lane < 2 * R) {
-      double t = 0.0;
-      for (unsigned k = 0; k < nsub; ++k) t += sub_tot[k * 2 * R + lane];
-      all_tot[lane] = t;
-    }
-    if (lane == 0) __hip_atomic_store(bar, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // totals and reset before release
-    if (lane == 0) {
-      for (unsigned k = 0; k < nsub; ++k)
-        __hip_atomic_store(bar + 32 * (1 + k) + 1, gen + 1u, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    }
-  } else if (lane == 0) {
-    unsigned spins = 0;
-    while (__hip_atomic_load(sc + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gen) {
-      __builtin_amdgcn_s_sleep(2);
-      if (++spins > kSpinLimit ||
-          __hip_atomic_load(error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-        __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = false;
-        break;
-      }
+  unsigned spins = 0;
+  const unsigned *flag = P.bar + 32 * (unsigned(lane) < nsub ? unsigned(lane) : 0u) + 1;
+  while (__any(int(get(flag) - gen) < 0)) {
+    __builtin_amdgcn_s_sleep(1);
+    if (++spins > kSpinLimit || __any(get(error))) {
+      if (lane == 0) put(error, 1);
+      ok = false;
+      break;
     }
   }
-  ok = __shfl(ok ? 1 : 0, 0) != 0;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  settle();  // nothing below is requested before the flags were seen
   if (ok && sa >= 0) {
+    const int c = lane % R;
+    double va[kSub], vb[kSub];
 #pragma unroll
-    for (int c = 0; c < R; ++c) {
-      a[c] = __hip_atomic_load(all_tot + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      b[c] = __hip_atomic_load(all_tot + R + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (unsigned k = 0; k < kSub; ++k) {
+      const unsigned o = min(k, nsub - 1) * 2 * R;
+      va[k] = get(&tot[o + c]);
+      vb[k] = get(&tot[o + R + c]);
     }
+    a = b = 0.0;
+#pragma unroll
+    for (unsigned k = 0; k < kSub; ++k)
+      if (k < nsub) {
+        a += va[k];
+        b += vb[k];
+      }
   }
   return ok;
 }
 
-// plain barrier
-template <int R>
-__device__ __forceinline__ bool problem_barrier(const BProb &P, unsigned me, unsigned nwg,
-                                                int *error) {
-  double a[R], b[R];
-  return problem_sync<R>(P, me, nwg, error, -1, -1, a, b);
+// problem_sync of workgroups: the first wave meets the other workgroups' once every wave of
+// this one has settled, and hands on what it brings back.
+template <int R, int NW>
+__device__ __forceinline__ bool group_sync(const BProb &P, unsigned me, unsigned nwg, int *error,
+                                           unsigned &gen, int sa, int sb, double &a,
+                                           double &b) {
+  if constexpr (NW == 1) {
+    return problem_sync<R>(P, me, nwg, error, gen, sa, sb, a, b);
+  } else {
+    __shared__ double sh[2 * R];
+    __shared__ int sh_ok;
+    settle();
+    __syncthreads();
+    if (threadIdx.x < kW) {
+      const bool ok = problem_sync<R>(P, me, nwg, error, gen, sa, sb, a, b);
+      if (threadIdx.x == 0) sh_ok = ok ? 1 : 0;
+      if (threadIdx.x < R) {
+        sh[threadIdx.x] = a;
+        sh[R + threadIdx.x] = b;
+      }
+    }
+    __syncthreads();
+    const int c = (threadIdx.x & (kW - 1)) % R;
+    a = sh[c];
+    b = sh[R + c];
+    const bool ok = sh_ok != 0;
+    __syncthreads();
+    return ok;
+  }
 }
 
-// dst = A src over this wave's tiles (src, dst [nn][R] of type T; LDS accumulation
+// plain barrier
+template <int R, int NW>
+__device__ __forceinline__ bool problem_barrier(const BProb &P, unsigned me, unsigned nwg,
+                                                int *error, unsigned &gen) {
+  double a = 0.0, b = 0.0;
+  return group_sync<R, NW>(P, me, nwg, error, gen, -1, -1, a, b);
+}
+
+// dst = A src over this workgroup's tiles (src [nn][R], dst [n_slots][R] of type T; LDS accumulation
 // in FP64), used by the FP64 refresh of the mixed form.  The R right-hand sides are the components of one element product, so the geometry
 // is evaluated once per element; PAR: every tile of every problem is a
 // parallelepiped tile (flagged at set-up), so only corners 0, 1, 2, 4 are read
 // and the closed-form parallelepiped action is used.  Dirichlet corners read
-// zero; Dirichlet and shared nodes of dst are set by the caller; right-hand
-// sides marked skip are neither read nor written.
-template <typename T, int R, bool PAR>
-__device__ __forceinline__ void apply_phase(const BProb &P, int me, int nwg, int lane,
+// zero; dst is by slot, as q; right-hand sides marked skip are neither read nor
+// written.
+template <typename T, int R, bool PAR, int NW>
+__device__ __forceinline__ void apply_phase(const BProb &P, int me, int nwg, int lane, int wave,
                                             double *acc, uint32_t *sId, const T *xyz,
                                             const T *coef_t, const T *src, T *dst,
-                                            const bool (&skip)[R]) {
+                                            int skip_m) {
+  constexpr int kIds = Lanes<R, NW>::kIds;
   for (int t = me; t < P.n_tiles; t += nwg) {
     const int n0 = P.node_ptr[t], nm = P.node_ptr[t + 1] - n0;
     const int s0 = P.tile_step[t], s1 = P.tile_step[t + 1];
@@ -332,18 +432,18 @@ __device__ __forceinline__ void apply_phase(const BProb &P, int me, int nwg, int
     // latency (its gathers) instead of two
     uint4 pk_next = make_uint4(0xffffffffu, 0, 0, 0);
     T k_next = T(0);
-    if (s0 < s1) {
-      pk_next = P.lconn[int64_t(s0) * kW + lane];
-      k_next = coef_t[int64_t(s0) * kW + lane];
+    if (s0 + wave < s1) {
+      pk_next = P.lconn[int64_t(s0 + wave) * kW + lane];
+      k_next = coef_t[int64_t(s0 + wave) * kW + lane];
     }
-    // node ids staged kStage per lane per round, all loads of a round issued first
-    for (int ib = lane; ib < nm; ib += kStage * kW) {
-      uint32_t id[kStage];
+    // node ids staged kIds per lane per round, all loads of a round issued first
+    for (int ib = threadIdx.x; ib < nm; ib += kIds * NW * kW) {
+      uint32_t id[kIds];
 #pragma unroll
-      for (int u = 0; u < kStage; ++u) id[u] = ib + u * kW < nm ? P.nodes[n0 + ib + u * kW] : 0u;
+      for (int u = 0; u < kIds; ++u) id[u] = P.nodes[n0 + min(ib + u * NW * kW, nm - 1)];
 #pragma unroll
-      for (int u = 0; u < kStage; ++u) {
-        const int i = ib + u * kW;
+      for (int u = 0; u < kIds; ++u) {
+        const int i = ib + u * NW * kW;
         if (i >= nm) continue;
         sId[i] = id[u];
 #pragma unroll
@@ -351,13 +451,13 @@ __device__ __forceinline__ void apply_phase(const BProb &P, int me, int nwg, int
       }
     }
     __syncthreads();
-    for (int s = s0; s < s1; ++s) {
+    for (int s = s0 + wave; s < s1; s += NW) {
       const int64_t slot = int64_t(s) * kW + lane;
       const uint4 pk = pk_next;
       const T k = k_next;
-      if (s + 1 < s1) {
-        pk_next = P.lconn[slot + kW];
-        k_next = coef_t[slot + kW];
+      if (s + NW < s1) {
+        pk_next = P.lconn[slot + NW * kW];
+        k_next = coef_t[slot + NW * kW];
       }
       if (pk.x == 0xffffffffu) continue;
       const int lc[8] = {int(pk.x & 0xffff), int(pk.x >> 16), int(pk.y & 0xffff),
@@ -377,124 +477,126 @@ __device__ __forceinline__ void apply_phase(const BProb &P, int me, int nwg, int
         if (!PAR || a == 0 || a == 1 || a == 2 || a == 4)
 #pragma unroll
           for (int d = 0; d < 3; ++d) X[d][a] = xyz[d * P.nn + g[a]];
-      T u[R][8], v[R][8];
+      if constexpr (NW > 1) {  // one right-hand side at a time: a quarter of the registers
+#pragma unroll 1
+        for (int c = 0; c < R; ++c) {
+          if ((skip_m >> c) & 1) continue;
+          T u[1][8], v[1][8];
 #pragma unroll
-      for (int a = 0; a < 8; ++a)
+          for (int a = 0; a < 8; ++a) u[0][a] = fx[a] ? T(0) : get(&src[g[a] * R + c]);
+          laplace_element_parallelepiped_n<T, 1>(X, u, k, v);
 #pragma unroll
-        for (int c = 0; c < R; ++c) u[c][a] = (fx[a] || skip[c]) ? T(0) : src[g[a] * R + c];
-      if constexpr (PAR)
-        laplace_element_parallelepiped_n<T, R>(X, u, k, v);
-      else
-        laplace_element_n<T, R>(X, u, k, v);
+          for (int a = 0; a < 8; ++a)
+            __hip_atomic_fetch_add(&acc[c * P.max_nodes + lc[a]], double(v[0][a]),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      } else {
+        T u[R][8], v[R][8];
 #pragma unroll
-      for (int c = 0; c < R; ++c) {
-        if (skip[c]) continue;
+        for (int a = 0; a < 8; ++a)
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-          __hip_atomic_fetch_add(&acc[c * P.max_nodes + lc[a]], double(v[c][a]),
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          for (int c = 0; c < R; ++c) u[c][a] = (fx[a] || ((skip_m >> c) & 1)) ? T(0) : get(&src[g[a] * R + c]);
+        if constexpr (PAR)
+          laplace_element_parallelepiped_n<T, R>(X, u, k, v);
+        else
+          laplace_element_n<T, R>(X, u, k, v);
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+          if (((skip_m >> c) & 1)) continue;
+#pragma unroll
+          for (int a = 0; a < 8; ++a) {
+            __hip_atomic_fetch_add(&acc[c * P.max_nodes + lc[a]], double(v[c][a]),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
         }
       }
     }
     __syncthreads();
-    for (int i = lane; i < nm; i += kW) {
-      const uint32_t raw = sId[i];
-      if (raw & kFixedBitB) continue;  // set by the caller
-      const int64_t gg = raw & kIdMaskB;
-#pragma unroll
-      for (int c = 0; c < R; ++c) {
-        if (skip[c]) continue;
-        const T vv = T(acc[c * P.max_nodes + i]);
-        if (raw & kSharedBitB)
-          unsafeAtomicAdd(&dst[gg * R + c], vv);
-        else
-          dst[gg * R + c] = vv;
-      }
+    const Lanes<R, NW> L;
+    const bool put_c = L.act && !((skip_m >> L.c) & 1);
+    for (int i = put_c ? L.sub : nm; i < nm; i += L.NL) {
+      const int32_t sl = P.pos[n0 + i];
+      if (sl >= 0) put(&dst[int64_t(sl) * R + L.c], T(acc[L.c * P.max_nodes + i]));
     }
     __syncthreads();
   }
 }
 
-// The direction update and q = A p in one pass over this wave's tiles.  For
+// The direction update and q = A p in one pass over this workgroup's tiles.  For
 // each tile node the new direction p = D^-1 r + beta p_old (p = D^-1 r on the
 // first iteration) is computed into LDS, where the element loop reads it (zero
 // on Dirichlet corners and for finished right-hand sides); the node's writer
-// entry also stores it to pnew and, on a Dirichlet node, sets q = p there (its
-// row of A p) and adds p^2 to mp.  A node held by several tiles is computed
-// by each from the same values, so every copy agrees.  Reading p_old from one
-// buffer and writing pnew to the other lets the update run without a barrier
-// before the apply.  With the element energies p_e^T A_e p_e (energy), mp
-// completes p^T A p.  T is the precision of p, q and the element arithmetic.
-template <typename T, int R, bool PAR>
-__device__ __forceinline__ void update_apply_phase(const BProb &P, int me, int nwg, int lane,
+// entry also stores it to pnew and, on a Dirichlet node (whose row of A p is p
+// itself), adds p^2 to pq.  A node held by several tiles is computed by each
+// from the same values, so every copy agrees.  Reading p_old from one buffer
+// and writing pnew to the other lets the update run without a barrier before
+// the apply.  The tile's sums go to its slots of the nodes, and p times them to
+// pq, this lane's share of p^T A p for its right-hand side.  T is the precision
+// of p, q and the element arithmetic.
+template <typename T, int R, bool PAR, int NW>
+__device__ __forceinline__ void update_apply_phase(const BProb &P, int me, int nwg, int lane, int wave,
                                                    double *acc, uint32_t *sId, T *sP,
                                                    const T *xyz, const T *coef_t, const T *pold,
-                                                   T *pnew, T *q, const bool (&done)[R],
-                                                   const double (&beta)[R], bool first,
-                                                   double (&energy)[R], double (&mp)[R]) {
+                                                   T *pnew, T *q, int done_m, double beta,
+                                                   bool first, double &pq) {
   const int M = P.max_nodes;
+  const Lanes<R, NW> L;
+  const bool on = L.act && !((done_m >> L.c) & 1);
+  constexpr int kStage = Lanes<R, NW>::kStage, kIds = Lanes<R, NW>::kIds;
   for (int t = me; t < P.n_tiles; t += nwg) {
     const int n0 = P.node_ptr[t], nm = P.node_ptr[t + 1] - n0;
     const int s0 = P.tile_step[t], s1 = P.tile_step[t + 1];
     uint4 pk_next = make_uint4(0xffffffffu, 0, 0, 0);
     T k_next = T(0);
-    if (s0 < s1) {
-      pk_next = P.lconn[int64_t(s0) * kW + lane];
-      k_next = coef_t[int64_t(s0) * kW + lane];
+    if (s0 + wave < s1) {
+      pk_next = P.lconn[int64_t(s0 + wave) * kW + lane];
+      k_next = coef_t[int64_t(s0 + wave) * kW + lane];
     }
-    for (int ib = lane; ib < nm; ib += kStage * kW) {
-      uint32_t id[kStage];
+    for (int ib = threadIdx.x; ib < nm; ib += kIds * NW * kW) {
+      uint32_t id[kIds];
 #pragma unroll
-      for (int u = 0; u < kStage; ++u)
-        id[u] = ib + u * kW < nm ? P.onodes[n0 + ib + u * kW] : 0u;
-      double wv[kStage], rv[kStage][R], pv[kStage][R];
+      for (int u = 0; u < kIds; ++u) id[u] = P.onodes[n0 + min(ib + u * NW * kW, nm - 1)];
+#pragma unroll
+      for (int u = 0; u < kIds; ++u)
+        if (ib + u * NW * kW < nm) sId[ib + u * NW * kW] = id[u];
+    }
+    __syncthreads();
+    for (int ib = L.act ? L.sub : nm; ib < nm; ib += kStage * L.NL) {
+      uint32_t id[kStage];
+      double wv[kStage], rv[kStage], pv[kStage];
 #pragma unroll
       for (int u = 0; u < kStage; ++u) {
-        const bool in = ib + u * kW < nm;
+        id[u] = sId[min(ib + u * L.NL, nm - 1)];
         const int64_t g = id[u] & kIdMaskOwnB;
-        wv[u] = in ? P.w[g] : 0.0;
-#pragma unroll
-        for (int c = 0; c < R; ++c) {
-          const bool ld = in && !done[c];
-          rv[u][c] = ld ? P.r[g * R + c] : 0.0;
-          pv[u][c] = (ld && !first) ? double(pold[g * R + c]) : 0.0;
+        wv[u] = rv[u] = pv[u] = 0.0;
+        if (on) {
+          wv[u] = P.w[g];
+          rv[u] = get(&P.r[g * R + L.c]);
+          if (!first) pv[u] = double(get(&pold[g * R + L.c]));
         }
       }
 #pragma unroll
       for (int u = 0; u < kStage; ++u) {
-        const int i = ib + u * kW;
+        const int i = ib + u * L.NL;
         if (i >= nm) continue;
-        const uint32_t raw = id[u];
-        const bool fixed = (raw & kFixedBitB) != 0, own = (raw & kOwnBitB) != 0;
-        const int64_t g = raw & kIdMaskOwnB;
-        sId[i] = raw;
-#pragma unroll
-        for (int c = 0; c < R; ++c) {
-          acc[c * M + i] = 0.0;
-          if (done[c]) {
-            sP[c * M + i] = T(0);
-            continue;
-          }
-          const T pn = T(wv[u] * rv[u][c] + beta[c] * pv[u][c]);
-          sP[c * M + i] = fixed ? T(0) : pn;
-          if (own) {
-            pnew[g * R + c] = pn;
-            if (fixed) {
-              q[g * R + c] = pn;  // Dirichlet rows of A p: the entry itself
-              mp[c] += double(pn) * double(pn);
-            }
-          }
+        const bool fixed = (id[u] & kFixedBitB) != 0;
+        const T pn = on ? T(wv[u] * rv[u] + beta * pv[u]) : T(0);
+        acc[L.c * M + i] = 0.0;
+        sP[L.c * M + i] = fixed ? T(0) : pn;
+        if (on && (id[u] & kOwnEntry)) {
+          put(&pnew[int64_t(id[u] & kIdMaskOwnB) * R + L.c], pn);
+          if (fixed) pq += double(pn) * double(pn);
         }
       }
     }
     __syncthreads();
-    for (int s = s0; s < s1; ++s) {
+    for (int s = s0 + wave; s < s1; s += NW) {
       const int64_t slot = int64_t(s) * kW + lane;
       const uint4 pk = pk_next;
       const T k = k_next;
-      if (s + 1 < s1) {
-        pk_next = P.lconn[slot + kW];
-        k_next = coef_t[slot + kW];
+      if (s + NW < s1) {
+        pk_next = P.lconn[slot + NW * kW];
+        k_next = coef_t[slot + NW * kW];
       }
       if (pk.x == 0xffffffffu) continue;
       const int lc[8] = {int(pk.x & 0xffff), int(pk.x >> 16), int(pk.y & 0xffff),
@@ -508,51 +610,93 @@ __device__ __forceinline__ void update_apply_phase(const BProb &P, int me, int n
 #pragma unroll
           for (int d = 0; d < 3; ++d) X[d][a] = xyz[d * P.nn + g];
         }
-      T u[R][8], v[R][8];
+      if constexpr (NW > 1) {  // one right-hand side at a time: a quarter of the registers
+#pragma unroll 1
+        for (int c = 0; c < R; ++c) {
+          if ((done_m >> c) & 1) continue;
+          T u[1][8], v[1][8];
 #pragma unroll
-      for (int a = 0; a < 8; ++a)
+          for (int a = 0; a < 8; ++a) u[0][a] = sP[c * M + lc[a]];
+          laplace_element_parallelepiped_n<T, 1>(X, u, k, v);
 #pragma unroll
-        for (int c = 0; c < R; ++c) u[c][a] = sP[c * M + lc[a]];
-      if constexpr (PAR)
-        laplace_element_parallelepiped_n<T, R>(X, u, k, v);
-      else
-        laplace_element_n<T, R>(X, u, k, v);
+          for (int a = 0; a < 8; ++a)
+            __hip_atomic_fetch_add(&acc[c * M + lc[a]], double(v[0][a]), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      } else {
+        T u[R][8], v[R][8];
 #pragma unroll
-      for (int c = 0; c < R; ++c) {
-        if (done[c]) continue;
+        for (int a = 0; a < 8; ++a)
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-          energy[c] += double(u[c][a]) * double(v[c][a]);
-          __hip_atomic_fetch_add(&acc[c * M + lc[a]], double(v[c][a]), __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          for (int c = 0; c < R; ++c) u[c][a] = sP[c * M + lc[a]];
+        if constexpr (PAR)
+          laplace_element_parallelepiped_n<T, R>(X, u, k, v);
+        else
+          laplace_element_n<T, R>(X, u, k, v);
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+          if ((done_m >> c) & 1) continue;
+#pragma unroll
+          for (int a = 0; a < 8; ++a)
+            __hip_atomic_fetch_add(&acc[c * M + lc[a]], double(v[c][a]), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }
       }
     }
     __syncthreads();
-    for (int i = lane; i < nm; i += kW) {
-      const uint32_t raw = sId[i];
-      if (raw & kFixedBitB) continue;  // set above by the writer entry
-      const int64_t gg = raw & kIdMaskOwnB;
+    for (int ib = on ? L.sub : nm; ib < nm; ib += kStage * L.NL) {
+      int32_t sl[kStage];
 #pragma unroll
-      for (int c = 0; c < R; ++c) {
-        if (done[c]) continue;
-        const T vv = T(acc[c * M + i]);
-        if (raw & kSharedBitB)
-          unsafeAtomicAdd(&q[gg * R + c], vv);
-        else
-          q[gg * R + c] = vv;
+      for (int u = 0; u < kStage; ++u) sl[u] = P.pos[n0 + min(ib + u * L.NL, nm - 1)];
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) {
+        const int i = ib + u * L.NL;
+        if (i >= nm || sl[u] < 0) continue;
+        const double vv = acc[L.c * M + i];
+        put(&q[int64_t(sl[u]) * R + L.c], T(vv));
+        pq += double(sP[L.c * M + i]) * vv;
       }
     }
     __syncthreads();
   }
 }
 
-template <int R, bool MIXED, bool PAR>
-__global__ __launch_bounds__(kW) void k_batched_pcg(const BProb *__restrict__ probs, int nprob,
-                                                    const int *__restrict__ wg_prob, double tol2,
-                                                    int maxit, double delta2, int *error) {
+// The sums of the slots of U nodes (slots [e0, e1) of each, in order) for one right-hand
+// side; the first two slots of every node are requested together, then two at a time.
+template <int R, int U, typename T>
+__device__ __forceinline__ void slot_sums(const BProb &P, const T *q, int c,
+                                          const uint32_t (&e0)[U], const uint32_t (&e1)[U],
+                                          double (&sum)[U]) {
+  int m = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    m = max(m, int(e1[u] - e0[u]));
+    sum[u] = 0.0;
+  }
+  const int64_t last = P.n_slots - 1;
+  for (int k = 0; k < m; k += 2) {
+    T v[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        v[u][d] = T(0);
+        if (e0[u] + k + d < e1[u]) v[u][d] = get(&q[min(int64_t(e0[u]) + k + d, last) * R + c]);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+        if (e0[u] + k + d < e1[u]) sum[u] += double(v[u][d]);
+  }
+}
+
+template <int R, bool MIXED, bool PAR, int NW>
+__global__ __launch_bounds__(kW * NW, NW > 1 ? 3 : 1) void k_batched_pcg(
+    const BProb *__restrict__ probs, int nprob, const int *__restrict__ wg_prob, double tol2,
+    int maxit, double delta2, int *error) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & (kW - 1), wave = threadIdx.x / kW;
   const BProb P = load_problem(probs + wg_prob[blockIdx.x]);
   const int me = int(blockIdx.x) - P.wg0;
   const int nwg = P.nwg;
@@ -561,79 +705,54 @@ __global__ __launch_bounds__(kW) void k_batched_pcg(const BProb *__restrict__ pr
   TP *sP = reinterpret_cast<TP *>(acc + R * P.max_nodes);              // [R][max_nodes]
   uint32_t *sId = reinterpret_cast<uint32_t *>(sP + R * P.max_nodes);  // [max_nodes]
   auto part = [&](int slot, int r) { return P.part + (int64_t(slot) * R + r) * nwg; };
-  // node range of this wave for the vector phases
+  // node range of this workgroup for the vector phases
   const int64_t chunk = (P.nn + nwg - 1) / nwg;
   const int64_t i0 = min(P.nn, int64_t(me) * chunk), i1 = min(P.nn, i0 + chunk);
-  const int64_t rchunk = (P.n_reset + nwg - 1) / nwg;
-  const int64_t j0 = min(P.n_reset, int64_t(me) * rchunk), j1 = min(P.n_reset, j0 + rchunk);
+  static_assert(NW == 1 || PAR, "several waves per workgroup: parallelepiped tiles");
+  const Lanes<R, NW> L;
+  constexpr int kU = Lanes<R, NW>::kU;
 
-  // ---- init: x = 0, r = b, both direction buffers 0 (nodes in no tile keep p = 0),
-  // q = 0 on shared nodes; partials rho_0 = b^T D^-1 b, b.b
+  // ---- init: x = 0, r = b, both direction buffers 0 (nodes in no tile keep p = 0);
+  // partials rho_0 = b^T D^-1 b, b.b
   {
-    double v_rho[R], v_bb[R];
-#pragma unroll
-    for (int c = 0; c < R; ++c) v_rho[c] = v_bb[c] = 0.0;
-    for (int64_t i = i0 + lane; i < i1; i += kW) {
-      const double wi = P.w[i];
-#pragma unroll
-      for (int c = 0; c < R; ++c) {
-        const double bi = P.b[i * R + c];
-        P.x[i * R + c] = 0.0;
-        P.r[i * R + c] = bi;
-        if constexpr (MIXED) {
-          P.p32[0][i * R + c] = 0.0f;
-          P.p32[1][i * R + c] = 0.0f;
-        } else {
-          P.p[0][i * R + c] = 0.0;
-          P.p[1][i * R + c] = 0.0;
-        }
-        v_rho[c] += bi * (wi * bi);
-        v_bb[c] += bi * bi;
+    double v_rho = 0.0, v_bb = 0.0;
+    for (int64_t i = L.act ? i0 + L.sub : i1; i < i1; i += L.NL) {
+      const int64_t o = i * R + L.c;
+      const double wi = P.w[i], bi = P.b[o];
+      if constexpr (MIXED)
+        put(&P.x[o], 0.0);
+      else
+        P.x[o] = 0.0;
+      put(&P.r[o], bi);
+      if constexpr (MIXED) {
+        put(&P.p32[0][o], 0.0f);
+        put(&P.p32[1][o], 0.0f);
+      } else {
+        put(&P.p[0][o], 0.0);
+        put(&P.p[1][o], 0.0);
       }
+      v_rho += bi * (wi * bi);
+      v_bb += bi * bi;
     }
-    for (int64_t j = j0 + lane; j < j1; j += kW) {
-      const int64_t g = P.reset[j];
-      if (P.mask && P.mask[g]) continue;  // Dirichlet rows: set by the first update
-#pragma unroll
-      for (int c = 0; c < R; ++c) {
-        if constexpr (MIXED) {
-          P.q32[g * R + c] = 0.0f;
-          P.t[g * R + c] = 0.0;  // shared nodes of the refresh apply
-        } else {
-          P.q[g * R + c] = 0.0;
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-      const double a = wave_sum64(v_rho[c]), bq = wave_sum64(v_bb[c]);
-      if (lane == 0) {
-        part(kRho0, c)[me] = a;
-        part(kBB, c)[me] = bq;
-      }
+    v_rho = group_sum<R, NW>(v_rho, lane);
+    v_bb = group_sum<R, NW>(v_bb, lane);
+    if (threadIdx.x < R) {
+      put(&part(kRho0, lane)[me], v_rho);
+      put(&part(kBB, lane)[me], v_bb);
     }
   }
-  double rho[R], bb[R];
-  if (!problem_sync<R>(P, unsigned(me), unsigned(nwg), error, kRho0, kBB, rho, bb)) return;
-  bool done[R];
-  int it_done[R], st[R], nref[R];
-  double rr_last[R], rr_ref[R];
-#pragma unroll
-  for (int c = 0; c < R; ++c) {
-    done[c] = !(bb[c] > 0.0);
-    it_done[c] = 0;
-    st[c] = Q1_OK;
-    rr_last[c] = rr_ref[c] = bb[c];
-    nref[c] = 0;
-  }
-  bool all_done = true;
-#pragma unroll
-  for (int c = 0; c < R; ++c) all_done = all_done && done[c];
-  double beta[R];
-#pragma unroll
-  for (int c = 0; c < R; ++c) beta[c] = 0.0;
+  // Each lane keeps the scalars of its right-hand side (the lanes of one side hold the same
+  // bits); done_m has a bit for each finished side.
+  double rho = 0.0, bb = 0.0;
+  unsigned gen = 0;  // barriers so far
+  if (!group_sync<R, NW>(P, unsigned(me), unsigned(nwg), error, gen, kRho0, kBB, rho, bb)) return;
+  constexpr int kAll = (1 << R) - 1;
+  bool done = !(bb > 0.0);
+  int it_done = 0, st = Q1_OK, nref = 0;
+  double rr_last = bb, rr_ref = bb, beta = 0.0;
+  int done_m = int(__ballot(done)) & kAll;  // lane c < R holds side c
 
-  for (int it = 1; it <= maxit && !all_done; ++it) {
+  for (int it = 1; it <= maxit && done_m != kAll; ++it) {
     // ---- P1: p = D^-1 r + beta p_old and q = A p over this wave's tiles, with the
     // partials of p^T A p (element energies, Dirichlet p^2).  The direction
     // buffers of this iteration and the previous one are selected, not indexed,
@@ -643,216 +762,170 @@ __global__ __launch_bounds__(kW) void k_batched_pcg(const BProb *__restrict__ pr
     double *const p64_old = odd ? P.p[0] : P.p[1];
     float *const p32 = odd ? P.p32[1] : P.p32[0];
     float *const p32_old = odd ? P.p32[0] : P.p32[1];
-    double energy[R], v_mp[R];
-#pragma unroll
-    for (int c = 0; c < R; ++c) energy[c] = v_mp[c] = 0.0;
+    double v_pq = 0.0;
     if constexpr (MIXED)
-      update_apply_phase<float, R, PAR>(P, me, nwg, lane, acc, sId, sP, P.xyz32, P.coef32,
-                                        p32_old, p32, P.q32, done, beta, it == 1,
-                                        energy, v_mp);
+      update_apply_phase<float, R, PAR, NW>(P, me, nwg, lane, wave, acc, sId, sP, P.xyz32, P.coef32,
+                                        p32_old, p32, P.q32, done_m, beta, it == 1, v_pq);
     else
-      update_apply_phase<double, R, PAR>(P, me, nwg, lane, acc, sId, sP, P.xyz, P.coef_t,
-                                         p64_old, p64, P.q, done, beta, it == 1, energy,
-                                         v_mp);
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-      const double e = wave_sum64(energy[c]), m = wave_sum64(v_mp[c]);
-      if (lane == 0) {
-        part(kEnergy, c)[me] = e;
-        part(kMp2, c)[me] = m;
-      }
-    }
-    double alpha[R], en[R], mp[R];
-    if (!problem_sync<R>(P, unsigned(me), unsigned(nwg), error, kEnergy, kMp2, en, mp)) return;
+      update_apply_phase<double, R, PAR, NW>(P, me, nwg, lane, wave, acc, sId, sP, P.xyz, P.coef_t,
+                                         p64_old, p64, P.q, done_m, beta, it == 1, v_pq);
+    v_pq = group_sum<R, NW>(v_pq, lane);
+    if (threadIdx.x < R) put(&part(kPQ, lane)[me], v_pq);
+    double pq = 0.0, none = 0.0;
+    if (!group_sync<R, NW>(P, unsigned(me), unsigned(nwg), error, gen, kPQ, -1, pq, none)) return;
 
     // ---- P2: alpha, x, r; partials rho', r.r
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-      const double pq = en[c] + mp[c];
-      alpha[c] = 0.0;
-      if (!done[c]) {
-        if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho[c])) {
-          done[c] = true;
-          st[c] = Q1_EBREAKDOWN;
-          it_done[c] = it - 1;
-        } else {
-          alpha[c] = rho[c] / pq;
-        }
+    double alpha = 0.0;
+    if (!done) {
+      if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
+        done = true;
+        st = Q1_EBREAKDOWN;
+        it_done = it - 1;
+      } else {
+        alpha = rho / pq;
       }
     }
     {
-      double v_rho[R], v_rr[R];
-#pragma unroll
-      for (int c = 0; c < R; ++c) v_rho[c] = v_rr[c] = 0.0;
-      for (int64_t ib = i0 + lane; ib < i1; ib += kU * kW) {
-        double wv[kU], po[kU][R], qo[kU][R], xo[kU][R], ro[kU][R];
+      double v_rho = 0.0, v_rr = 0.0;
+      const bool on = L.act && !done;
+      for (int64_t ib = on ? i0 + L.sub : i1; ib < i1; ib += kU * L.NL) {
+        uint32_t e0[kU], e1[kU];
+        bool fx[kU];
+        double wv[kU], po[kU], qo[kU], xo[kU], ro[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-          const int64_t i = ib + u * kW;
-          const bool in = i < i1;
-          wv[u] = in ? P.w[i] : 0.0;
-#pragma unroll
-          for (int c = 0; c < R; ++c) {
-            const int64_t o = i * R + c;
-            const bool ld = in && !done[c];
-            if constexpr (MIXED) {
-              po[u][c] = ld ? double(p32[o]) : 0.0;
-              qo[u][c] = ld ? double(P.q32[o]) : 0.0;
-            } else {
-              po[u][c] = ld ? p64[o] : 0.0;
-              qo[u][c] = ld ? P.q[o] : 0.0;
-            }
-            xo[u][c] = ld ? P.x[o] : 0.0;
-            ro[u][c] = ld ? P.r[o] : 0.0;
-          }
+          const int64_t i = min(ib + u * L.NL, i1 - 1);
+          e0[u] = P.nptr[i];
+          e1[u] = P.nptr[i + 1];
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-          const int64_t i = ib + u * kW;
-          if (i >= i1) continue;
-#pragma unroll
-          for (int c = 0; c < R; ++c) {
-            if (done[c]) continue;
-            const int64_t o = i * R + c;
-            P.x[o] = xo[u][c] + alpha[c] * po[u][c];
-            const double rn = ro[u][c] - alpha[c] * qo[u][c];
-            P.r[o] = rn;
-            // q was last read here: zero it for the next P1, whose tiles store
-            // their private nodes and add into shared ones (P3 then sets the
-            // Dirichlet rows)
-            if constexpr (MIXED)
-              P.q32[o] = 0.0f;
-            else
-              P.q[o] = 0.0;
-            v_rho[c] += rn * wv[u] * rn;
-            v_rr[c] += rn * rn;
+          const int64_t i = min(ib + u * L.NL, i1 - 1), o = i * R + L.c;
+          wv[u] = P.w[i];
+          if constexpr (MIXED) {
+            po[u] = double(get(&p32[o]));
+            xo[u] = get(&P.x[o]);
+          } else {
+            po[u] = get(&p64[o]);
+            xo[u] = P.x[o];
           }
+          ro[u] = get(&P.r[o]);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          fx[u] = (e0[u] >> 31) != 0;
+          e0[u] &= 0x7fffffffu;
+          e1[u] &= 0x7fffffffu;
+        }
+        if constexpr (MIXED)
+          slot_sums<R>(P, P.q32, L.c, e0, e1, qo);
+        else
+          slot_sums<R>(P, P.q, L.c, e0, e1, qo);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int64_t i = ib + u * L.NL, o = i * R + L.c;
+          if (i >= i1) continue;
+          if (fx[u]) qo[u] = po[u];
+          const double xn = xo[u] + alpha * po[u], rn = ro[u] - alpha * qo[u];
+          if constexpr (MIXED)
+            put(&P.x[o], xn);
+          else
+            P.x[o] = xn;
+          put(&P.r[o], rn);
+          v_rho += rn * wv[u] * rn;
+          v_rr += rn * rn;
         }
       }
-#pragma unroll
-      for (int c = 0; c < R; ++c) {
-        const double a = wave_sum64(v_rho[c]), bq = wave_sum64(v_rr[c]);
-        if (lane == 0) {
-          part(kRho, c)[me] = a;
-          part(kRR, c)[me] = bq;
-        }
+      v_rho = group_sum<R, NW>(v_rho, lane);
+      v_rr = group_sum<R, NW>(v_rr, lane);
+      if (threadIdx.x < R) {
+        put(&part(kRho, lane)[me], v_rho);
+        put(&part(kRR, lane)[me], v_rr);
       }
     }
-    double rho_n[R], rr_n[R];
-    if (!problem_sync<R>(P, unsigned(me), unsigned(nwg), error, kRho, kRR, rho_n, rr_n)) return;
+    double rho_n = 0.0, rr_n = 0.0;
+    if (!group_sync<R, NW>(P, unsigned(me), unsigned(nwg), error, gen, kRho, kRR, rho_n, rr_n)) return;
 
     // ---- convergence and beta (the direction update runs with the next apply)
-    bool refresh[R];
-    bool any_refresh = false;
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-      beta[c] = 0.0;
-      refresh[c] = false;
-      if (done[c]) continue;
-      const double rho1 = rho_n[c];
-      const double rr = rr_n[c];
-      rr_last[c] = rr;
+    bool refresh = false;
+    beta = 0.0;
+    if (!done) {
+      rr_last = rr_n;
       if constexpr (MIXED) {
         // the recurrence only triggers a refresh; convergence is decided on b - A64 x
-        if (!isfinite(rr)) {
-          done[c] = true;
-          st[c] = Q1_EBREAKDOWN;
-          it_done[c] = it;
-        } else if (rr <= fmax(delta2 * rr_ref[c], 0.5 * tol2 * bb[c]) || it >= maxit) {
-          refresh[c] = true;
-          any_refresh = true;
+        if (!isfinite(rr_n)) {
+          done = true;
+          st = Q1_EBREAKDOWN;
+          it_done = it;
+        } else if (rr_n <= fmax(delta2 * rr_ref, 0.5 * tol2 * bb) || it >= maxit) {
+          refresh = true;
         } else {
-          beta[c] = rho1 / rho[c];
-          rho[c] = rho1;
+          beta = rho_n / rho;
+          rho = rho_n;
         }
       } else {
-        if (rr <= tol2 * bb[c] || !isfinite(rr) || it >= maxit) {
-          done[c] = true;
-          st[c] = rr <= tol2 * bb[c] ? Q1_OK : (!isfinite(rr) ? Q1_EBREAKDOWN : Q1_ENOCONV);
-          it_done[c] = it;
+        if (rr_n <= tol2 * bb || !isfinite(rr_n) || it >= maxit) {
+          done = true;
+          st = rr_n <= tol2 * bb ? Q1_OK : (!isfinite(rr_n) ? Q1_EBREAKDOWN : Q1_ENOCONV);
+          it_done = it;
         } else {
-          beta[c] = rho1 / rho[c];
-          rho[c] = rho1;
+          beta = rho_n / rho;
+          rho = rho_n;
         }
       }
     }
     if constexpr (MIXED) {
-      if (any_refresh) {
+      const int refresh_m = int(__ballot(refresh)) & kAll;
+      if (refresh_m) {
         // R1: t = A64 x for the refreshed right-hand sides (FP64 geometry and coefficients)
-        bool skip[R];
-#pragma unroll
-        for (int c = 0; c < R; ++c) skip[c] = !refresh[c];
-        apply_phase<double, R, PAR>(P, me, nwg, lane, acc, sId, P.xyz, P.coef_t, P.x, P.t, skip);
-        if (!problem_barrier<R>(P, unsigned(me), unsigned(nwg), error)) return;
+        apply_phase<double, R, PAR, NW>(P, me, nwg, lane, wave, acc, sId, P.xyz, P.coef_t, P.x, P.t, ~refresh_m);
+        if (!problem_barrier<R, NW>(P, unsigned(me), unsigned(nwg), error, gen)) return;
         // R2: r = b - A64 x (Dirichlet rows are the identity); partials rho', r.r
-        double v_rho[R], v_rr[R];
-#pragma unroll
-        for (int c = 0; c < R; ++c) v_rho[c] = v_rr[c] = 0.0;
-        for (int64_t i = i0 + lane; i < i1; i += kW) {
-          const double wi = P.w[i];
-          const bool fx = P.mask && P.mask[i];
-#pragma unroll
-          for (int c = 0; c < R; ++c) {
-            if (!refresh[c]) continue;
-            const int64_t o = i * R + c;
-            const double rn = P.b[o] - (fx ? P.x[o] : P.t[o]);
-            P.r[o] = rn;
-            v_rho[c] += rn * wi * rn;
-            v_rr[c] += rn * rn;
-          }
+        double v_rho = 0.0, v_rr = 0.0;
+        for (int64_t i = L.act && refresh ? i0 + L.sub : i1; i < i1; i += L.NL) {
+          const int64_t o = i * R + L.c;
+          const uint32_t f = P.nptr[i];
+          const uint32_t e0[1] = {f & 0x7fffffffu}, e1[1] = {P.nptr[i + 1] & 0x7fffffffu};
+          double t[1];
+          slot_sums<R>(P, P.t, L.c, e0, e1, t);
+          const double rn = P.b[o] - (f >> 31 ? get(&P.x[o]) : t[0]);
+          put(&P.r[o], rn);
+          v_rho += rn * P.w[i] * rn;
+          v_rr += rn * rn;
         }
-#pragma unroll
-        for (int c = 0; c < R; ++c) {
-          const double a = wave_sum64(v_rho[c]), bq = wave_sum64(v_rr[c]);
-          if (lane == 0) {
-            part(kRho, c)[me] = a;
-            part(kRR, c)[me] = bq;
-          }
+        v_rho = group_sum<R, NW>(v_rho, lane);
+        v_rr = group_sum<R, NW>(v_rr, lane);
+        if (threadIdx.x < R) {
+          put(&part(kRho, lane)[me], v_rho);
+          put(&part(kRR, lane)[me], v_rr);
         }
-        if (!problem_sync<R>(P, unsigned(me), unsigned(nwg), error, kRho, kRR, rho_n, rr_n))
+        if (!group_sync<R, NW>(P, unsigned(me), unsigned(nwg), error, gen, kRho, kRR, rho_n, rr_n))
           return;
         // R3: decide on the true residual; otherwise continue from it with p kept
-#pragma unroll
-        for (int c = 0; c < R; ++c) {
-          if (!refresh[c]) continue;
-          const double rho1 = rho_n[c];
-          const double rr = rr_n[c];
-          rr_last[c] = rr;
-          ++nref[c];
-          if (rr <= tol2 * bb[c] || !isfinite(rr) || it >= maxit) {
-            done[c] = true;
-            st[c] = rr <= tol2 * bb[c] ? Q1_OK : (!isfinite(rr) ? Q1_EBREAKDOWN : Q1_ENOCONV);
-            it_done[c] = it;
+        if (refresh) {
+          rr_last = rr_n;
+          ++nref;
+          if (rr_n <= tol2 * bb || !isfinite(rr_n) || it >= maxit) {
+            done = true;
+            st = rr_n <= tol2 * bb ? Q1_OK : (!isfinite(rr_n) ? Q1_EBREAKDOWN : Q1_ENOCONV);
+            it_done = it;
           } else {
-            rr_ref[c] = rr;
-            beta[c] = rho1 / rho[c];
-            rho[c] = rho1;
+            rr_ref = rr_n;
+            beta = rho_n / rho;
+            rho = rho_n;
           }
-        }
-        // shared nodes of t start the next refresh at zero (their values were read in R2)
-        for (int64_t j = j0 + lane; j < j1; j += kW) {
-          const int64_t g = P.reset[j];
-          if (P.mask && P.mask[g]) continue;
-#pragma unroll
-          for (int c = 0; c < R; ++c)
-            if (refresh[c]) P.t[g * R + c] = 0.0;
         }
       }
     }
-    all_done = true;
-#pragma unroll
-    for (int c = 0; c < R; ++c) all_done = all_done && done[c];
-    if (all_done) break;
+    done_m = int(__ballot(done)) & kAll;
   }
-  if (me == 0 && lane == 0) {
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-      P.iters[c] = it_done[c];
-      P.status[c] = done[c] ? st[c] : Q1_ENOCONV;
-      P.rr[c] = rr_last[c];
-      P.bb[c] = bb[c];
-      P.nref[c] = nref[c];
-    }
+  if (me == 0 && threadIdx.x < R) {
+    const int c = threadIdx.x;
+    P.iters[c] = it_done;
+    P.status[c] = done ? st : Q1_ENOCONV;
+    P.rr[c] = rr_last;
+    P.bb[c] = bb;
+    P.nref[c] = nref;
   }
 }
 
@@ -877,28 +950,7 @@ __global__ void k_to_f32(int64_t n, const double *__restrict__ src, float *__res
   if (i < n) dst[i] = float(src[i]);
 }
 
-__global__ void k_fill_i32(int64_t n, int32_t *__restrict__ a, int32_t v) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = v;
-}
-
-// first[g] = the smallest entry index of node g over the tile node lists
-__global__ void k_first_entry(int64_t nent, const uint32_t *__restrict__ nodes,
-                              int32_t *__restrict__ first) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e < nent) atomicMin(&first[nodes[e] & kIdMaskB], int32_t(e));
-}
-
-// the node lists with the writer bit set on each node's first entry
-__global__ void k_mark_writers(int64_t nent, const uint32_t *__restrict__ nodes,
-                               const int32_t *__restrict__ first, uint32_t *__restrict__ onodes) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= nent) return;
-  const uint32_t raw = nodes[e];
-  onodes[e] = raw | (first[raw & kIdMaskB] == int32_t(e) ? kOwnBitB : 0u);
-}
-
-template <int R, bool MIXED, bool PAR>
+template <int R, bool MIXED, bool PAR, int NW>
 int run_batched(const std::vector<BProb> &hp, const std::vector<int> &wg_prob, double tol2,
                 int maxit, double delta2, size_t lds, hipStream_t s, int *d_error) {
   BProb *dp = nullptr;
@@ -910,8 +962,8 @@ int run_batched(const std::vector<BProb> &hp, const std::vector<int> &wg_prob, d
   int nprob = int(hp.size());
   void *args[] = {&dp, &nprob, &dwg, &tol2, &maxit, &delta2, &d_error};
   hipError_t e = hipLaunchCooperativeKernel(
-      reinterpret_cast<const void *>(k_batched_pcg<R, MIXED, PAR>),
-      dim3(unsigned(wg_prob.size())), dim3(kW), args, unsigned(lds), s);
+      reinterpret_cast<const void *>(k_batched_pcg<R, MIXED, PAR, NW>),
+      dim3(unsigned(wg_prob.size())), dim3(kW * NW), args, unsigned(lds), s);
   hipError_t e2 = hipStreamSynchronize(s);
   (void)hipFree(dp);
   (void)hipFree(dwg);
@@ -920,11 +972,11 @@ int run_batched(const std::vector<BProb> &hp, const std::vector<int> &wg_prob, d
   return Q1_OK;
 }
 
-template <int R, bool MIXED, bool PAR>
+template <int R, bool MIXED, bool PAR, int NW>
 int max_coresident(size_t lds) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &per_cu, reinterpret_cast<const void *>(k_batched_pcg<R, MIXED, PAR>), kW, lds) !=
+          &per_cu, reinterpret_cast<const void *>(k_batched_pcg<R, MIXED, PAR, NW>), kW * NW, lds) !=
       hipSuccess)
     return 0;
   int dev = 0, cus = 0;
@@ -933,25 +985,37 @@ int max_coresident(size_t lds) {
   return per_cu * cus;
 }
 
-template <bool MIXED, bool PAR>
+template <bool MIXED, bool PAR, int NW>
 int coresident_for(int nrhs, size_t lds) {
   switch (nrhs) {
-    case 1: return max_coresident<1, MIXED, PAR>(lds);
-    case 2: return max_coresident<2, MIXED, PAR>(lds);
-    case 3: return max_coresident<3, MIXED, PAR>(lds);
-    default: return max_coresident<4, MIXED, PAR>(lds);
+    case 1: return max_coresident<1, MIXED, PAR, NW>(lds);
+    case 2: return max_coresident<2, MIXED, PAR, NW>(lds);
+    case 3: return max_coresident<3, MIXED, PAR, NW>(lds);
+    default: return max_coresident<4, MIXED, PAR, NW>(lds);
   }
 }
 
-template <bool MIXED, bool PAR>
+template <bool MIXED, bool PAR, int NW>
 int run_for(int nrhs, const std::vector<BProb> &hp, const std::vector<int> &wg_prob, double tol2,
             int maxit, double delta2, size_t lds, hipStream_t s, int *d_error) {
   switch (nrhs) {
-    case 1: return run_batched<1, MIXED, PAR>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
-    case 2: return run_batched<2, MIXED, PAR>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
-    case 3: return run_batched<3, MIXED, PAR>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
-    default: return run_batched<4, MIXED, PAR>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
+    case 1: return run_batched<1, MIXED, PAR, NW>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
+    case 2: return run_batched<2, MIXED, PAR, NW>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
+    case 3: return run_batched<3, MIXED, PAR, NW>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
+    default: return run_batched<4, MIXED, PAR, NW>(hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
   }
+}
+
+// f(MIXED, PAR, NW as integral constants) of the form to run
+template <class F>
+auto with_form(bool mixed, bool par, int nw, F f) {
+  using t = std::true_type;
+  using n = std::false_type;
+  using one = std::integral_constant<int, 1>;
+  using four = std::integral_constant<int, 4>;
+  if (par && nw == 4) return mixed ? f(t{}, t{}, four{}) : f(n{}, t{}, four{});
+  if (par) return mixed ? f(t{}, t{}, one{}) : f(n{}, t{}, one{});
+  return mixed ? f(t{}, n{}, one{}) : f(n{}, n{}, one{});
 }
 
 // Shared host side of the FP64 and mixed-precision batched solvers.
@@ -982,10 +1046,14 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
                                           sizeof(uint32_t));
   bool par = true;  // every tile of every problem a parallelepiped tile
   for (int p = 0; p < nprob; ++p) par = par && reinterpret_cast<const Op *>(ops[p])->tiles.all_affine;
-  const int cap = mixed ? (par ? coresident_for<true, true>(nrhs, lds)
-                               : coresident_for<true, false>(nrhs, lds))
-                        : (par ? coresident_for<false, true>(nrhs, lds)
-                               : coresident_for<false, false>(nrhs, lds));
+  // four waves per workgroup on parallelepiped tiles, where one workgroup per problem fits so
+  auto cap_of = [&](int nw) {
+    return with_form(mixed, par, nw, [&](auto m, auto p, auto w) {
+      return coresident_for<decltype(m)::value, decltype(p)::value, decltype(w)::value>(nrhs, lds);
+    });
+  };
+  int nw = par ? 4 : 1, cap = cap_of(nw);
+  if (cap < nprob) cap = cap_of(nw = 1);
   Q1_CHECK(cap >= nprob, Q1_EUNSUPPORTED,
            "%s: %d problems need one co-resident wave each, but only %d fit", name, nprob, cap);
   // waves per problem in proportion to its expected work, at least one each:
@@ -1046,30 +1114,20 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
     B.lconn = reinterpret_cast<const uint4 *>(tm.lconn);
     B.coef_t = static_cast<const double *>(tm.coef_t);
     B.xyz = static_cast<const double *>(o.xyz);
-    B.reset = tm.reset;
-    B.n_reset = tm.n_reset;
     B.mask = o.mask;
-    Q1_CHECK(n < int64_t(kIdMaskOwnB), Q1_EUNSUPPORTED, "%s: operator %d has %lld nodes (at most %u)",
+    Q1_CHECK(n < int64_t(kIdMaskOwnB) && tm.onodes, Q1_EUNSUPPORTED, "%s: operator %d has %lld nodes (at most %u)",
              name, p, (long long)n, kIdMaskOwnB);
-    // the node lists with the writer bit on each node's first entry (first tile in order)
-    {
-      const int64_t nent = tm.n_entries;
-      int32_t *first = nullptr;
-      uint32_t *onodes = nullptr;
-      if ((rc = dalloc(reinterpret_cast<void **>(&first), size_t(n) * sizeof(int32_t))) ||
-          (rc = dalloc(reinterpret_cast<void **>(&onodes), size_t(nent) * sizeof(uint32_t))))
-        return rc;
-      hipLaunchKernelGGL(k_fill_i32, grid(n), dim3(256), 0, s, n, first, INT32_MAX);
-      hipLaunchKernelGGL(k_first_entry, grid(nent), dim3(256), 0, s, nent, tm.nodes, first);
-      hipLaunchKernelGGL(k_mark_writers, grid(nent), dim3(256), 0, s, nent, tm.nodes, first,
-                         onodes);
-      B.onodes = onodes;
-    }
+    B.onodes = tm.onodes;
+    B.nptr = tm.nptr;
+    B.pos = tm.pos;
+    B.n_slots = tm.n_node_slots;
+    const size_t ns = size_t(tm.n_node_slots) * nrhs;
     const size_t nv = size_t(n) * nrhs;
     double *vec[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     for (int v = 0; v < 6; ++v) {
       if (mixed && v >= 3) continue;  // p, q are FP32 in the mixed form
-      if ((rc = dalloc(reinterpret_cast<void **>(&vec[v]), nv * sizeof(double)))) return rc;
+      if ((rc = dalloc(reinterpret_cast<void **>(&vec[v]), (v == 3 ? ns : nv) * sizeof(double))))
+        return rc;
     }
     B.b = vec[0]; B.x = vec[1]; B.r = vec[2]; B.q = vec[3]; B.p[0] = vec[4]; B.p[1] = vec[5];
     if (mixed) {
@@ -1078,8 +1136,8 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
       const int64_t ncoef = tm.n_steps * kW;
       if ((rc = dalloc(reinterpret_cast<void **>(&B.p32[0]), nv * sizeof(float))) ||
           (rc = dalloc(reinterpret_cast<void **>(&B.p32[1]), nv * sizeof(float))) ||
-          (rc = dalloc(reinterpret_cast<void **>(&B.q32), nv * sizeof(float))) ||
-          (rc = dalloc(reinterpret_cast<void **>(&B.t), nv * sizeof(double))) ||
+          (rc = dalloc(reinterpret_cast<void **>(&B.q32), ns * sizeof(float))) ||
+          (rc = dalloc(reinterpret_cast<void **>(&B.t), ns * sizeof(double))) ||
           (rc = dalloc(reinterpret_cast<void **>(&xyz32), size_t(3 * n) * sizeof(float))) ||
           (rc = dalloc(reinterpret_cast<void **>(&coef32), size_t(ncoef) * sizeof(float))))
         return rc;
@@ -1100,7 +1158,7 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
                                                              sizeof(double))))
       return rc;
     if ((rc = dalloc(reinterpret_cast<void **>(&B.bar), kBarWords * sizeof(unsigned)))) return rc;
-    if ((rc = dalloc(reinterpret_cast<void **>(&B.tot), (kSub + 1) * 2 * nrhs * sizeof(double))))
+    if ((rc = dalloc(reinterpret_cast<void **>(&B.tot), 2 * kSub * 2 * nrhs * sizeof(double))))
       return rc;
     Q1_HIP(hipMemsetAsync(B.bar, 0, kBarWords * sizeof(unsigned), s));
     B.wg0 = int(wg_prob.size());
@@ -1116,11 +1174,10 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
   Q1_HIP(hipStreamSynchronize(s));
   const auto t_setup = std::chrono::steady_clock::now();
   const double tol2 = rtol * rtol, delta2 = delta * delta;
-  rc = mixed ? (par ? run_for<true, true>(nrhs, hp, wg_prob, tol2, maxit, delta2, lds, s, d_error)
-                    : run_for<true, false>(nrhs, hp, wg_prob, tol2, maxit, delta2, lds, s, d_error))
-             : (par ? run_for<false, true>(nrhs, hp, wg_prob, tol2, maxit, delta2, lds, s, d_error)
-                    : run_for<false, false>(nrhs, hp, wg_prob, tol2, maxit, delta2, lds, s,
-                                            d_error));
+  rc = with_form(mixed, par, nw, [&](auto m, auto p, auto w) {
+    return run_for<decltype(m)::value, decltype(p)::value, decltype(w)::value>(
+        nrhs, hp, wg_prob, tol2, maxit, delta2, lds, s, d_error);
+  });
   if (rc) return rc;
   const auto t_solve = std::chrono::steady_clock::now();
   int h_error = 0;

@@ -44,6 +44,12 @@ struct TileMap {
   int64_t n_reset = 0;            // shared or Dirichlet nodes, reset before each apply
   bool orphans = false;           // some node belongs to no element (and so to no tile)
   int32_t *reset = nullptr;
+  // Scalar FP64 operators of the LDS-tile variant (the batched solver's): a slot per free
+  // node and tile that holds it, a node's slots contiguous and in tile order
+  uint32_t *onodes = nullptr;     // [n_entries] nodes, bit kOwnEntry on a node's first entry
+  uint32_t *nptr = nullptr;       // [n_nodes + 1] first slot, bit 31 on Dirichlet nodes
+  int32_t *pos = nullptr;         // [n_entries] slot of an entry, -1 on Dirichlet nodes
+  int64_t n_node_slots = 0;
   bool lds_atomic = false;        // corners collide within a step: accumulate with LDS atomics
   bool split = false;             // block variants: bitwise-reproducible split accumulation
   bool all_affine = false;        // every tile is a parallelepiped tile
@@ -135,6 +141,7 @@ int launch_diag_family(Op &op, void *d, hipStream_t s);
 // Q1_EINVAL unless every connectivity entry is in [0, n_nodes) (synchronises s).
 int validate_conn(const Op &op, hipStream_t s);
 int build_tiles(Op &op, hipStream_t s);
+constexpr uint32_t kOwnEntry = 0x20000000u;
 int launch_apply_tile(Op &op, const void *x, void *y, hipStream_t s, const int *stop);
 // y = A x with the partial sums of x.y formed where y is written (per tile over its
 // own nodes, per halo-sum workgroup over shared and Dirichlet nodes plus a fixed

@@ -1812,6 +1812,29 @@ int build_tiles_t(Op &op, hipStream_t s, int patch_x, int patch_y, int layers) {
       (rc = up(&tm.tile_addr, H.tile_addr)) || (rc = up(&tm.tile_g0, H.tile_g0)))
     return rc;
   tm.coef_t = coef_dev;
+  if (op.variant == Q1_V_LDS_TILE && op.physics == Q1_LAPLACE && sizeof(T) == 8 &&
+      nn < int64_t(kOwnEntry)) {
+    std::vector<uint32_t> onodes(H.nodes), nptr(size_t(nn) + 1, 0u), next(size_t(nn), 0u);
+    std::vector<int32_t> pos(H.nodes.size(), -1);
+    std::vector<uint8_t> seen(size_t(nn), 0);
+    for (uint32_t v : H.nodes)
+      if (!(v & kFixedBit)) ++nptr[(v & kIdMask) + 1];
+    for (int64_t g = 0; g < nn; ++g) {
+      nptr[g + 1] += nptr[g];
+      next[g] = nptr[g];
+    }
+    for (size_t i = 0; i < H.nodes.size(); ++i) {
+      const uint32_t v = H.nodes[i], g = v & kIdMask;
+      if (!seen[g]) onodes[i] |= kOwnEntry;
+      seen[g] = 1;
+      if (!(v & kFixedBit)) pos[i] = int32_t(next[g]++);
+    }
+    tm.n_node_slots = int64_t(nptr[nn]);
+    for (int64_t g = 0; g < nn; ++g)
+      if (!mask.empty() && mask[g]) nptr[g] |= 0x80000000u;
+    if ((rc = up(&tm.onodes, onodes)) || (rc = up(&tm.nptr, nptr)) || (rc = up(&tm.pos, pos)))
+      return rc;
+  }
   if (op.variant == Q1_V_BLOCK || op.variant == Q1_V_PA) {
     if ((rc = up(&tm.slot, H.slot)) || (rc = up(&tm.hptr, H.hptr)) ||
         (rc = up(&tm.hnode, H.hnode)))
@@ -2140,7 +2163,7 @@ void free_tiles(Op &op) {
   void *ptrs[] = {t.node_ptr, t.nodes, t.tile_step, t.lconn, t.reset,
                   t.coef_t,   t.tile_affine, t.slot, t.hptr, t.halo, t.qdata, t.tile_lat,
                   t.tile_addr, t.tile_g0,
-                  t.hnode, t.hmap};
+                  t.hnode, t.hmap, t.onodes, t.nptr, t.pos};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   t = TileMap{};
