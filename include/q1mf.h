@@ -171,9 +171,9 @@ int q1_op_create(q1_op **op, int physics, int dtype, int variant, int64_t n_node
 enum { Q1_HEX8 = 8, Q1_TET4 = 4, Q1_HEX27 = 27, Q1_HEX64 = 64 };
 /* q1_op_create for an element family.  Q1_HEX8 is q1_op_create.  Q1_TET4,
  * Q1_HEX27 and Q1_HEX64: physics Q1_LAPLACE or Q1_ELASTICITY, variants
- * Q1_V_AUTO or Q1_V_ATOMIC (one thread per tetrahedron, one thread per node
- * and quadrature point of a triquadratic or tricubic element with the
- * element's nodes staged in LDS; global atomic scatter); other
+ * Q1_V_AUTO or Q1_V_ATOMIC (one thread per tetrahedron, one thread per line of
+ * nodes of a triquadratic or tricubic element, sum-factorised with the lines
+ * turned in LDS; global atomic scatter); other
  * variants and physics give Q1_EUNSUPPORTED.  The apply, diagonal, byte model
  * and the Krylov solvers accept these operators; q1_csr_create, the fused and
  * the batched solvers do not (Q1_EUNSUPPORTED). */
