@@ -42,6 +42,7 @@ struct TileMap {
   uint16_t *lconn = nullptr;      // [n_steps*64][8] corner indices into the tile list (0xffff: empty)
   void *coef_t = nullptr;         // cell coefficients in lane order [ncoef][n_steps*64]
   int64_t n_reset = 0;            // shared or Dirichlet nodes, reset before each apply
+  bool cells = false;             // tetrahedra in lane slots of one Kuhn cell each
   bool orphans = false;           // some node belongs to no element (and so to no tile)
   int32_t *reset = nullptr;
   // Scalar FP64 operators of the LDS-tile variant (the batched solver's): a slot per free

@@ -971,7 +971,15 @@ __host__ __device__ inline size_t tet_acc_offset(int max_nodes, size_t rec_bytes
 // each tetrahedron's 4 corner contributions into one FP64 LDS accumulator with
 // LDS atomics (the order of those additions varies; FP64 in both precisions,
 // since the FP32 LDS atomic add measured twice as slow here).
-template <typename T, int PH>
+// CELLS: where every six elements in a row are a Kuhn cell (kuhn_cells), a lane
+// slot is a cell: the lane reads the cell's 8 corners once instead of 24, forms
+// its six products from registers and adds 8 corners instead of 24.  The LDS had
+// bounded the kernel (57% of its time busy, a third of that in conflicts, now
+// rare: neighbouring lanes hold neighbouring cells).  us per streaming apply with
+// its halo sum, one tetrahedron per lane -> cells, jittered 51 x 47 x 61 cells:
+// elasticity FP64 36.1 -> 18.8, FP32 33.2 -> 12.8; Laplace FP64 21.0 -> 11.7, FP32
+// 19.6 -> 9.8; 12 x 13 x 11 elasticity 12.0 -> 10.2; 96 x 80 x 72 90.6 -> 42.1.
+template <typename T, int PH, bool CELLS>
 __global__ __launch_bounds__(256) void k_apply_block_tet(
     int max_nodes, int64_t nn, const int32_t *__restrict__ node_ptr,
     const uint32_t *__restrict__ nodes, const int32_t *__restrict__ tile_step,
@@ -1034,37 +1042,87 @@ __global__ __launch_bounds__(256) void k_apply_block_tet(
     }
   }
   __syncthreads();
-  // steps w, w + 4, ...: each step's corner indices and coefficients are
-  // requested one step ahead (at a clamped step, unconditionally)
-  int s = s0 + w;
-  int64_t sl0 = int64_t(min(s, s1 - 1)) * kLanes + lane;
-  uint4 pk = lconn[sl0];
-  T c0 = coef_t[sl0], c1 = PH == 3 ? coef_t[coef_stride + sl0] : T(0);
-  for (; s < s1; s += 4) {
-    const int64_t sn = int64_t(min(s + 4, s1 - 1)) * kLanes + lane;
-    const uint4 pkn = lconn[sn];
-    const T c0n = coef_t[sn], c1n = PH == 3 ? coef_t[coef_stride + sn] : T(0);
-    if (pk.x != 0xffffffffu) {  // empty lanes skip
-      const int lc[4] = {int(pk.x & 0xffff), int(pk.x >> 16), int(pk.y & 0xffff),
-                         int(pk.y >> 16)};
-      T X[3][4], u[DPN][4], v[DPN][4];
+  if constexpr (CELLS) {
+    constexpr int NC = PH == 3 ? 2 : 1;
+    for (int s = s0 + w; s < s1; s += 4) {
+      const int64_t sl = int64_t(s) * kLanes + lane;
+      const uint4 pk = lconn[sl];
+      T c[6][2];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
+      for (int t = 0; t < 6; ++t) {
+        c[t][0] = coef_t[(t * NC) * coef_stride + sl];
+        c[t][1] = PH == 3 ? coef_t[(t * NC + NC - 1) * coef_stride + sl] : T(0);
+      }
+      if (pk.x == 0xffffffffu) continue;  // empty lane
+      const int lc[8] = {int(pk.x & 0xffff), int(pk.x >> 16), int(pk.y & 0xffff),
+                         int(pk.y >> 16),    int(pk.z & 0xffff), int(pk.z >> 16),
+                         int(pk.w & 0xffff), int(pk.w >> 16)};
+      T X[3][8], u[DPN][8], v[DPN][8];
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
 #pragma unroll
         for (int r = 0; r < 3; ++r) X[r][a] = sR[size_t(r) * max_nodes + lc[a]];
 #pragma unroll
-        for (int j = 0; j < DPN; ++j) u[j][a] = sR[size_t(3 + j) * max_nodes + lc[a]];
+        for (int j = 0; j < DPN; ++j) {
+          u[j][a] = sR[size_t(3 + j) * max_nodes + lc[a]];
+          v[j][a] = T(0);
+        }
       }
-      tet_element<T, PH>(X, u, c0, c1, v);
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int t = 5; t >= 0; --t) {  // the last path first: any order does
+        T Xt[3][4], ut[DPN][4], vt[DPN][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+          for (int r = 0; r < 3; ++r) Xt[r][q] = X[r][kKuhn[t][q]];
+#pragma unroll
+          for (int j = 0; j < DPN; ++j) ut[j][q] = u[j][kKuhn[t][q]];
+        }
+        tet_element<T, PH>(Xt, ut, c[t][0], c[t][1], vt);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int j = 0; j < DPN; ++j) v[j][kKuhn[t][q]] += vt[j][q];
+      }
+#pragma unroll
+      for (int a = 0; a < 8; ++a)
 #pragma unroll
         for (int j = 0; j < DPN; ++j)
           lds_add(&sV[size_t(j) * max_nodes + lc[a]], double(v[j][a]));
     }
-    pk = pkn;
-    c0 = c0n;
-    c1 = c1n;
+  } else {
+    // steps w, w + 4, ...: each step's corner indices and coefficients are
+    // requested one step ahead (at a clamped step, unconditionally)
+    int s = s0 + w;
+    int64_t sl0 = int64_t(min(s, s1 - 1)) * kLanes + lane;
+    uint4 pk = lconn[sl0];
+    T c0 = coef_t[sl0], c1 = PH == 3 ? coef_t[coef_stride + sl0] : T(0);
+    for (; s < s1; s += 4) {
+      const int64_t sn = int64_t(min(s + 4, s1 - 1)) * kLanes + lane;
+      const uint4 pkn = lconn[sn];
+      const T c0n = coef_t[sn], c1n = PH == 3 ? coef_t[coef_stride + sn] : T(0);
+      if (pk.x != 0xffffffffu) {  // empty lanes skip
+        const int lc[4] = {int(pk.x & 0xffff), int(pk.x >> 16), int(pk.y & 0xffff),
+                           int(pk.y >> 16)};
+        T X[3][4], u[DPN][4], v[DPN][4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+#pragma unroll
+          for (int r = 0; r < 3; ++r) X[r][a] = sR[size_t(r) * max_nodes + lc[a]];
+#pragma unroll
+          for (int j = 0; j < DPN; ++j) u[j][a] = sR[size_t(3 + j) * max_nodes + lc[a]];
+        }
+        tet_element<T, PH>(X, u, c0, c1, v);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int j = 0; j < DPN; ++j)
+            lds_add(&sV[size_t(j) * max_nodes + lc[a]], double(v[j][a]));
+      }
+      pk = pkn;
+      c0 = c0n;
+      c1 = c1n;
+    }
   }
   __syncthreads();
   auto write_node = [&](int i, uint32_t raw, int32_t sl) {
@@ -1312,6 +1370,7 @@ struct HostTiles {
   std::vector<uint8_t> tile_affine;  // every element of the tile is a parallelepiped
   std::vector<int32_t> slot, hptr, hnode;  // halo slots of the block variant
   bool orphans = false;            // some node, free or Dirichlet, belongs to no element
+  bool cells = false;              // a lane slot is a Kuhn cell (its first tetrahedron)
   std::vector<uint32_t> tile_lat;    // lattice description of each tile (0: none)
   bool split = true;                 // every tile admits the split accumulation
   std::vector<uint32_t> tile_addr;   // lattice addressing: kAddrValid | face bits, or 0
@@ -1407,6 +1466,27 @@ bool fixed_tiles(const HostTiles &H) {
   return true;
 }
 
+// Corners of Kuhn cell c (elements 6c .. 6c + 5 along the split's paths, kKuhn); false where
+// the six do not form one.  The nodes' places do not matter.
+bool kuhn_cell(const std::vector<int32_t> &conn, int64_t ne, int64_t c, int32_t (&corner)[8]) {
+  static constexpr int kt[6][4] = {{0, 1, 3, 7}, {0, 5, 1, 7}, {0, 3, 2, 7},
+                                   {0, 2, 6, 7}, {0, 6, 4, 7}, {0, 4, 5, 7}};
+  for (int t = 0; t < 6; ++t)
+    for (int q = 0; q < 4; ++q) corner[kt[t][q]] = conn[size_t(q) * ne + 6 * c + t];
+  for (int t = 0; t < 6; ++t)
+    for (int q = 0; q < 4; ++q)
+      if (corner[kt[t][q]] != conn[size_t(q) * ne + 6 * c + t]) return false;
+  return true;
+}
+
+bool kuhn_cells(const std::vector<int32_t> &conn, int64_t ne) {
+  if (ne <= 0 || ne % 6) return false;
+  int32_t corner[8];
+  for (int64_t c = 0; c < ne / 6; ++c)
+    if (!kuhn_cell(conn, ne, c, corner)) return false;
+  return true;
+}
+
 // Group elements into tiles and steps; record node lists and corner indices.
 template <typename T>
 // nloc: nodes per element (8 hexahedra, 4 tetrahedra; a tetrahedron's corner
@@ -1426,6 +1506,13 @@ int plan_tiles(const std::vector<int32_t> &conn, const std::vector<T> &xyz,
       cen[3 * e + r] = c;
       lo[r] = std::min(lo[r], c);
     }
+  if (H.cells)  // a cell's tetrahedra stay together
+    for (int64_t e = 0; e < ne; e += 6)
+      for (int r = 0; r < 3; ++r) {
+        double c = 0;
+        for (int t = 0; t < 6; ++t) c += cen[3 * (e + t) + r];
+        for (int t = 0; t < 6; ++t) cen[3 * (e + t) + r] = c / 6;
+      }
   // element size from the node bounding box
   double vol = 1.0;
   int live = 0;
@@ -1493,6 +1580,22 @@ int plan_tiles(const std::vector<int32_t> &conn, const std::vector<T> &xyz,
       H.nodes.push_back(v);
     }
     H.node_ptr.push_back(int32_t(H.nodes.size()));
+    if (H.cells) {  // steps of 64 cells in order
+      for (int64_t k = tb[t]; k < tb[t + 1]; k += 6 * kLanes)
+        for (int64_t l = 0; l < kLanes; ++l) {
+          int32_t corner[8];
+          const int64_t e = k + 6 * l < tb[t + 1] ? order[k + 6 * l] : -1;
+          if (e >= 0) (void)kuhn_cell(conn, ne, e / 6, corner);
+          H.step_elem.push_back(int32_t(e));
+          for (int a = 0; a < 8; ++a)
+            H.lconn.push_back(e >= 0 ? uint16_t(local[corner[a]]) : uint16_t(0xffff));
+        }
+      H.tile_step.push_back(int32_t(H.step_elem.size() / kLanes));
+      H.tile_lat.push_back(0u);
+      H.tile_affine.push_back(0);
+      for (int32_t g : list) local[g] = -1;
+      continue;
+    }
     // steps: runs of one layer, at most 64 elements; (first, end, layer) with
     // the layer counted within the tile
     struct Run {
@@ -1744,9 +1847,18 @@ int build_tiles_t(Op &op, hipStream_t s, int patch_x, int patch_y, int layers) {
   HostTiles H;
   const bool block = op.variant == Q1_V_BLOCK || op.variant == Q1_V_PA;
   const bool hex = op.elem == Q1_HEX8;
+  H.cells = block && op.elem == Q1_TET4 && kuhn_cells(conn, ne);
   int rc = plan_tiles<T>(conn, xyz, mask, nn, ne, patch_x, patch_y, layers, block && hex,
                          op.dpn(), H, nloc, hex ? 1.0 : 6.0);
+  const size_t node_b = sizeof(T) * (3 + op.dpn());
+  if (H.cells && (rc || tet_acc_offset(H.max_nodes, node_b) + size_t(H.max_nodes) * 8 * op.dpn() >
+                            64 * 1024)) {  // cells that do not fit: single tetrahedra
+    H = HostTiles();
+    rc = plan_tiles<T>(conn, xyz, mask, nn, ne, patch_x, patch_y, layers, false, op.dpn(), H, nloc,
+                       6.0);
+  }
   if (rc) return rc;
+  tm.cells = H.cells;
   // lattice addressing for the scalar kind only: measured on 128^3 Laplace FP64
   // (applies streaming from HBM) 46.8 against 44.9 GDOF/s, while the 3-DOF kinds
   // (fewer nodes per element, more arithmetic per node) ran 3-5% slower with it;
@@ -1760,10 +1872,13 @@ int build_tiles_t(Op &op, hipStream_t s, int patch_x, int patch_y, int layers) {
   tm.sy = H.sy;
   tm.sz = H.sz;
   const int64_t n_slots = int64_t(H.step_elem.size());
-  std::vector<T> coef_t(size_t(ncoef) * n_slots, T(0));
+  const int per = H.cells ? 6 : 1;  // elements per lane slot
+  std::vector<T> coef_t(size_t(per * ncoef) * n_slots, T(0));
   for (int64_t k = 0; k < n_slots; ++k)
     if (H.step_elem[k] >= 0)
-      for (int c = 0; c < ncoef; ++c) coef_t[c * n_slots + k] = coef[c * ne + H.step_elem[k]];
+      for (int t = 0; t < per; ++t)
+        for (int c = 0; c < ncoef; ++c)
+          coef_t[(t * ncoef + c) * n_slots + k] = coef[c * ne + H.step_elem[k] + t];
   tm.n_tiles = int(H.node_ptr.size()) - 1;
   tm.n_steps = n_slots / kLanes;
   tm.max_nodes = H.max_nodes;
@@ -1934,7 +2049,9 @@ int apply_tile_t(Op &op, const void *xv, void *yv, hipStream_t s, const int *sto
   if (block && op.elem == Q1_TET4) {
     if constexpr (PH != 2) {
       const size_t tl = block_lds_bytes(op);
-      hipLaunchKernelGGL((k_apply_block_tet<T, PH>), dim3(tm.n_tiles), dim3(256), tl, s,
+      hipLaunchKernelGGL((tm.cells ? k_apply_block_tet<T, PH, true>
+                                   : k_apply_block_tet<T, PH, false>),
+                         dim3(tm.n_tiles), dim3(256), tl, s,
                          tm.max_nodes, op.n_nodes, tm.node_ptr, tm.nodes, tm.tile_step,
                          reinterpret_cast<const uint4 *>(tm.lconn),
                          static_cast<const T *>(tm.coef_t), tm.n_steps * kLanes,
