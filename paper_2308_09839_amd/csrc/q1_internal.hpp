@@ -72,7 +72,6 @@ struct TileMap {
   int32_t *hptr = nullptr;        // [n_reset+1] extra-slot range of each reset node
   int32_t *hnode = nullptr;       // [n_reset] node id, bit 31 set on Dirichlet nodes
   void *halo = nullptr;           // [n_halo][dpn] partial sums, overwritten by every apply
-  int32_t *hmap = nullptr;        // [n_nodes] the halo sum by node (OpenSum), where it may be open
   void *qdata = nullptr;          // partial assembly: [48][n_steps*64] quadrature data
   size_t bytes = 0;
 };
@@ -150,20 +149,8 @@ int launch_apply_tile(Op &op, const void *x, void *y, hipStream_t s, const int *
 // apply_dot_parts: doubles the launch needs at parts (0: not available) and, in
 // *n_final, how many partials at parts[0..) make up x.y.
 int64_t apply_dot_parts(const Op &op, int64_t *n_final);
-// open: without the halo sum, n_tiles partials at parts (apply_open must hold).
 int launch_apply_dot(Op &op, const void *x, void *y, hipStream_t s, const int *stop,
-                     double *parts, bool open = false);
-// An apply on block tiles of hexahedra whose halo sum is left to the kernel that reads y: of a
-// node's map entry m, y is as written (m = -1), the input (bit kOpenFixed) or the sum of halo
-// slots m, nr + m and 2 nr + [hptr[m], hptr[m + 1]) in this order.
-constexpr int32_t kOpenFixed = 0x40000000;
-struct OpenSum {
-  const int32_t *map = nullptr, *hptr = nullptr;
-  const void *halo = nullptr;
-  int64_t nr = 0;
-  int n_tiles = 0;
-};
-bool apply_open(const Op &op, OpenSum *o);
+                     double *parts);
 // The apply of launch_apply_dot with the solver's direction step in its staging: the test
 // after iteration `it` (see direction_test) and, unless it stops the solve, p_new = w r +
 // beta p_old, q = A p_new and the partials of p_new.q.  r and w are FP64 when wide, else of
@@ -180,8 +167,7 @@ struct DirStep {
   Status *st;
 };
 bool apply_dir_ok(const Op &op);
-int launch_apply_dir(Op &op, const DirStep &d, void *q, hipStream_t s, double *parts,
-                     bool open = false);
+int launch_apply_dir(Op &op, const DirStep &d, void *q, hipStream_t s, double *parts);
 int launch_diag_tile(Op &op, void *d, hipStream_t s);
 // The diagonal on owner-computes tiles of tetrahedra (bitwise reproducible).
 int launch_diag_owner(Op &op, void *d, hipStream_t s);

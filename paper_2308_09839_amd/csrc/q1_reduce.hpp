@@ -84,28 +84,10 @@ __device__ __forceinline__ void sum_partials_n(const double *const (&rows)[R], i
   sum_partials_nc<R>(rows, cnt, out);
 }
 
-// The same for one row; between() runs once this thread's partials are added, before the
-// block sum (loads that it issues are in flight during it).
-template <class F>
-__device__ __forceinline__ double sum_partials(const double *__restrict__ part, int nb,
-                                               F between) {
-  constexpr int U = 4;
-  double out[1] = {0.0};
-  for (int j0 = int(threadIdx.x); j0 < nb; j0 += U * kRT) {
-    double a[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = part[min(j0 + u * kRT, nb - 1)];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (j0 + u * kRT < nb) out[0] += a[u];
-  }
-  between();
-  block_sum<1>(out);
-  return out[0];
-}
-
 __device__ __forceinline__ double sum_partials(const double *__restrict__ part, int nb) {
-  return sum_partials(part, nb, [] {});
+  double out[1];
+  sum_partials_n<1>({part}, nb, out);
+  return out[0];
 }
 
 // The test after iteration `it` of the PCG and beta = rho_it / rho_{it-1}, the same in every

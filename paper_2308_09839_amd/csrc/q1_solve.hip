@@ -133,84 +133,17 @@ __global__ __launch_bounds__(kRT) void k_dot(int64_t n, const T *__restrict__ a,
   if (threadIdx.x == 0) part[blockIdx.x] = v[0];
 }
 
-// q as the apply left it: whole, or with the halo sum open (see OpenSum).  An open sum spares
-// a kernel between the apply and the update, whose work hides in the update: the slots are
-// read while the block adds the p.q partials, and q is neither written nor read back on the
-// shared nodes.  p.q does not need the sums, being linear in what each tile adds to them.
-// Microseconds per iteration, closed -> open: mixed elasticity 48^3 23.5 -> 20.7, 96^3
-// 64.9 -> 62.4; elasticity PCG 96^3 82.0 -> 77.9; jittered Laplace 64^3 27.6 -> 25.5, 128^3
-// 108.1 -> 104.4: at every size.
-struct Whole {};
-template <typename TP, int DPN>
-struct Open {
-  const int32_t *__restrict__ map, *__restrict__ hptr;
-  const TP *__restrict__ halo;
-  int64_t nr;
-  explicit Open(const OpenSum &o)
-      : map(o.map), hptr(o.hptr), halo(static_cast<const TP *>(o.halo)), nr(o.nr) {}
-};
-
-// Of the U values i0 + 256 u of a thread: the map entries, and then the values of q, the
-// slots added in the order of the halo-sum kernel.  The first two slots of every value are
-// requested together, then two further slots (edges and corners of the tiles) at a time.
-template <int U, typename TP, int DPN>
-__device__ __forceinline__ void hmap_load(const Open<TP, DPN> &o, int64_t n, int64_t i0,
-                                          int32_t (&hm)[U]) {
-#pragma unroll
-  for (int u = 0; u < U; ++u) hm[u] = o.map[uint32_t(min(i0 + u * kRT, n - 1)) / DPN];
-}
-template <int U, typename TP, int DPN>
-__device__ __forceinline__ void halo_gather(const Open<TP, DPN> &o, int64_t n, int64_t i0,
-                                            const int32_t (&hm)[U], const TP (&p)[U],
-                                            TP (&q)[U]) {
-  TP h0[U], h1[U];
-  int32_t e0[U], e1[U];
-  uint32_t c[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int64_t j = hm[u] < 0 ? 0 : hm[u] & ~kOpenFixed;
-    c[u] = uint32_t(min(i0 + u * kRT, n - 1)) % DPN;
-    h0[u] = o.halo[j * DPN + c[u]];
-    h1[u] = o.halo[(o.nr + j) * DPN + c[u]];
-    e0[u] = o.hptr[j];
-    e1[u] = o.hptr[j + 1];
-  }
-  int m = 0;
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (hm[u] < 0) e1[u] = e0[u];
-    m = max(m, e1[u] - e0[u]);
-    h0[u] += h1[u];
-  }
-  for (int t = 0; t < m; t += 2) {
-    TP a[U][2];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int d = 0; d < 2; ++d)
-        a[u][d] = t + d < e1[u] - e0[u] ? o.halo[(2 * o.nr + e0[u] + t + d) * DPN + c[u]] : TP(0);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int d = 0; d < 2; ++d)
-        if (t + d < e1[u] - e0[u]) h0[u] += a[u][d];
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (hm[u] >= 0) q[u] = hm[u] & kOpenFixed ? p[u] : h0[u];
-}
-
-// alpha = rho_k / p.q; x += alpha p; r -= alpha q; partials rho_{k+1}, r.r.  TP, the
-// type of p and q, is float in the mixed-precision solver (FP32 operator), whose x, r
-// and w stay in double.
+// alpha = rho_k / p.q; x += alpha p; r -= alpha q; partials rho_{k+1}, r.r.
+// FLEX (flexible PCG): keeps r_k in r_old and leaves rho_{k+1} to the
+// preconditioner step.  TP, the type of p and q, is float in the mixed-precision
+// solver (FP32 operator), whose x, r and w stay in double.
 // npq: the number of p.q partials (the apply's when it forms them, else gridDim.x).
-template <typename T, typename TP, class Q>
+template <typename T, bool FLEX, typename TP = T>
 __global__ __launch_bounds__(kRT) void k_pcg_update(
     int64_t n, const TP *__restrict__ p, const TP *__restrict__ q, const T *__restrict__ w,
-    T *__restrict__ x, T *__restrict__ r, const double *__restrict__ part_pq, int npq, int k,
-    double *__restrict__ part_rho_k1, double *__restrict__ part_rr, Status *__restrict__ st,
-    Q open) {
-  constexpr bool OPEN = !std::is_same<Q, Whole>::value;
+    T *__restrict__ x, T *__restrict__ r, T *__restrict__ r_old,
+    const double *__restrict__ part_pq, int npq, int k, double *__restrict__ part_rho_k1,
+    double *__restrict__ part_rr, Status *__restrict__ st) {
   // Nothing below depends on another load's result until alpha: the flag, the partials and
   // the first round of the vectors are requested together, one memory latency in all.
   const int done = st->done;
@@ -221,9 +154,7 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
   constexpr int U = 4;
   T rv[U], xv[U], wv[U];
   TP pv[U], qv[U];
-  int32_t hm[U];
   auto load = [&](int64_t i0) {
-    if constexpr (OPEN) hmap_load(open, n, i0, hm);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t i = min(i0 + u * kRT, n - 1);
@@ -231,15 +162,12 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
       xv[u] = x[i];
       pv[u] = p[i];
       qv[u] = q[i];
-      wv[u] = w[i];
+      if constexpr (!FLEX) wv[u] = w[i];
     }
-  };
-  auto gather = [&](int64_t i0) {
-    if constexpr (OPEN) halo_gather(open, n, i0, hm, pv, qv);
   };
   load(rg.i0 + threadIdx.x);
   const double rho = st->rho2[k & 1];
-  const double pq = sum_partials(part_pq, npq, [&] { gather(rg.i0 + threadIdx.x); });
+  const double pq = sum_partials(part_pq, npq);
   if (done) return;
   if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -251,24 +179,22 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
   const double alpha = rho / pq;
   double v[2] = {0.0, 0.0};
   for (int64_t i0 = rg.i0 + threadIdx.x; i0 < rg.i1; i0 += U * kRT) {
-    if (i0 >= rg.i0 + U * kRT) {
-      load(i0);
-      gather(i0);
-    }
+    if (i0 >= rg.i0 + U * kRT) load(i0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t i = i0 + u * kRT;
       if (i >= rg.i1) continue;
+      if constexpr (FLEX) r_old[i] = rv[u];
       const T rn = T(double(rv[u]) - alpha * double(qv[u]));
       x[i] = T(double(xv[u]) + alpha * double(pv[u]));
       r[i] = rn;
-      v[0] += double(rn) * double(wv[u] * rn);
+      if constexpr (!FLEX) v[0] += double(rn) * double(wv[u] * rn);
       v[1] += double(rn) * double(rn);
     }
   }
   block_sum<2>(v);
   if (threadIdx.x == 0) {
-    part_rho_k1[blockIdx.x] = v[0];
+    if constexpr (!FLEX) part_rho_k1[blockIdx.x] = v[0];
     part_rr[blockIdx.x] = v[1];
   }
 }
@@ -643,15 +569,6 @@ int nblocks_for(int64_t n) {
   return int(std::max<int64_t>(1, std::min<int64_t>(kMaxRB, b)));
 }
 
-// Blocks of the PCG vector kernels: 1,024 entries each, one round of four per thread, up to
-// kMaxRB.  At 2,048 a 48^3 elasticity solve had 173 blocks for 256 compute units and paid the
-// second round's latencies: mixed 48^3 elasticity 21.0 -> 19.0 us per iteration, 33 x 41 x 27
-// Laplace 20.7 -> 18.5; 128^3 (kMaxRB blocks either way) unchanged.
-int solve_blocks(int64_t n) {
-  const int64_t b = (n + int64_t(kRT) * 4 - 1) / (int64_t(kRT) * 4);
-  return int(std::max<int64_t>(1, std::min<int64_t>(kMaxRB, b)));
-}
-
 inline dim3 grid1(int64_t n) { return dim3(unsigned((n + 255) / 256)); }
 
 template <typename T>
@@ -683,23 +600,6 @@ int setup_diag(Op &op, Work &W, int pc, hipStream_t s) {
                      static_cast<T *>(W.w), pc == Q1_PC_JACOBI ? 1 : 0);
   Q1_HIP(hipGetLastError());
   return Q1_OK;
-}
-
-// k_pcg_update; os: q with the halo sum open
-template <typename T, typename TP>
-void launch_update(const OpenSum *os, int dpn, int nb, hipStream_t s, int64_t n, const TP *p,
-                   const TP *q, const T *w, T *x, T *r, const double *part_pq, int npq, int k,
-                   double *part_rho_k1, double *part_rr, Status *st) {
-  auto go = [&](auto o) {
-    hipLaunchKernelGGL((k_pcg_update<T, TP, decltype(o)>), dim3(nb), dim3(kRT), 0, s, n, p, q, w,
-                       x, r, part_pq, npq, k, part_rho_k1, part_rr, st, o);
-  };
-  if (!os)
-    go(Whole{});
-  else if (dpn == 1)
-    go(Open<TP, 1>(*os));
-  else
-    go(Open<TP, 3>(*os));
 }
 
 int read_status(Work &W, hipStream_t s) {
@@ -778,7 +678,7 @@ int pcg_t(Op &op, int pc, const T *b, T *x, double rtol, int maxit, q1_stats *st
   Work &W = given ? *given : own;
   const auto t0 = std::chrono::steady_clock::now();
   if ((rc = setup_diag<T>(op, W, pc, s))) return rc;
-  const int nb = solve_blocks(n);
+  const int nb = nblocks_for(n);
   double *P = W.part;
   double *part_rho[2] = {P, P + kMaxRB};
   double *part_pq = P + 2 * kMaxRB, *part_rr = P + 3 * kMaxRB, *part_bb = P + 4 * kMaxRB;
@@ -790,9 +690,7 @@ int pcg_t(Op &op, int pc, const T *b, T *x, double rtol, int maxit, q1_stats *st
   int64_t n_dot = 0;
   const int64_t need_dot = apply_dot_parts(op, &n_dot);
   const bool fused_dot = need_dot > 0 && need_dot <= kMaxDotParts && W.dparts;
-  OpenSum os;
-  const bool open = fused_dot && apply_open(op, &os) && os.n_tiles <= kMaxDotParts;
-  const int npq = open ? os.n_tiles : fused_dot ? int(n_dot) : nb;
+  const int npq = fused_dot ? int(n_dot) : nb;
   // within a batch of iterations the apply takes the previous iteration's direction step
   // where it can (p then alternates between two buffers, if the second one fits)
   const bool fused_dir = fused_dot && W.owned && apply_dir_ok(op) &&
@@ -823,17 +721,17 @@ int pcg_t(Op &op, int pc, const T *b, T *x, double rtol, int maxit, q1_stats *st
         if (fused_dir && j > 0) {  // the test and the direction of iteration k, then the apply
           const DirStep d{r,  w,    p, p_alt,  part_rho[k & 1], part_rr,
                           nb, tol2, k, maxit, sizeof(T) == 8,  W.st};
-          if ((rc = launch_apply_dir(op, d, q, s, W.dparts, open))) return rc;
+          if ((rc = launch_apply_dir(op, d, q, s, W.dparts))) return rc;
           std::swap(p, p_alt);
         } else if (fused_dot) {  // p.q partials formed by the apply
-          if ((rc = launch_apply_dot(op, p, q, s, &W.st->done, W.dparts, open))) return rc;
+          if ((rc = launch_apply_dot(op, p, q, s, &W.st->done, W.dparts))) return rc;
         } else {
           if ((rc = launch_apply(op, p, q, s, &W.st->done))) return rc;
           hipLaunchKernelGGL((k_dot<T>), dim3(nb), dim3(kRT), 0, s, n, p, q, part_pq, W.st);
         }
-        launch_update<T, T>(open ? &os : nullptr, op.dpn(), nb, s, n, p, q, w, x, r,
-                            fused_dot ? W.dparts : part_pq, npq, k, part_rho[(k + 1) & 1], part_rr,
-                            W.st);
+        hipLaunchKernelGGL((k_pcg_update<T, false>), dim3(nb), dim3(kRT), 0, s, n, p, q, w, x, r,
+                           nullptr, fused_dot ? W.dparts : part_pq, npq, k,
+                           part_rho[(k + 1) & 1], part_rr, W.st);
         if (!fused_dir || j + 1 == m)
           hipLaunchKernelGGL((k_pcg_direction<T>), dim3(nb), dim3(kRT), 0, s, n, r, w, nullptr, p,
                              part_rho[(k + 1) & 1], part_rr, tol2, k + 1, maxit, W.st);
@@ -1075,7 +973,7 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
   Q1_HIP(hipMalloc(&q, size_t(n) * sizeof(float)));
   const auto t0 = std::chrono::steady_clock::now();
   if ((rc = setup_diag<double>(A64, W, Q1_PC_JACOBI, s))) return rc;
-  const int nb = solve_blocks(n);
+  const int nb = nblocks_for(n);
   double *P = W.part;
   double *part_rho[2] = {P, P + kMaxRB};
   double *part_pq = P + 2 * kMaxRB, *part_rr = P + 3 * kMaxRB, *part_bb = P + 4 * kMaxRB;
@@ -1084,9 +982,7 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
   int64_t n_dot = 0;
   const int64_t need_dot = apply_dot_parts(A32, &n_dot);
   const bool fused_dot = need_dot > 0 && need_dot <= kMaxDotParts && W.dparts;
-  OpenSum os;
-  const bool open = fused_dot && apply_open(A32, &os) && os.n_tiles <= kMaxDotParts;
-  const int npq = open ? os.n_tiles : fused_dot ? int(n_dot) : nb;
+  const int npq = fused_dot ? int(n_dot) : nb;
   const bool fused_dir = fused_dot && apply_dir_ok(A32) &&  // as in pcg_t
                          second_buffer(reinterpret_cast<void **>(&p_alt), size_t(n) * sizeof(float));
   Q1_HIP(hipMemsetAsync(W.st, 0, sizeof(Status), s));
@@ -1117,18 +1013,18 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
           if (fused_dir && j > 0) {
             const DirStep d{r,  w,        p, p_alt, part_rho[k & 1], part_rr,
                             nb, thr / bb, k, maxit, true,           W.st};
-            if ((rc = launch_apply_dir(A32, d, q, s, W.dparts, open))) return rc;
+            if ((rc = launch_apply_dir(A32, d, q, s, W.dparts))) return rc;
             std::swap(p, p_alt);
           } else if (fused_dot) {
-            if ((rc = launch_apply_dot(A32, p, q, s, &W.st->done, W.dparts, open))) return rc;
+            if ((rc = launch_apply_dot(A32, p, q, s, &W.st->done, W.dparts))) return rc;
           } else {
             if ((rc = launch_apply(A32, p, q, s, &W.st->done))) return rc;
             hipLaunchKernelGGL((k_dot<float>), dim3(nb), dim3(kRT), 0, s, n, p, q, part_pq,
                                W.st);
           }
-          launch_update<double, float>(open ? &os : nullptr, A32.dpn(), nb, s, n, p, q, w, x, r,
-                                       fused_dot ? W.dparts : part_pq, npq, k,
-                                       part_rho[(k + 1) & 1], part_rr, W.st);
+          hipLaunchKernelGGL((k_pcg_update<double, false, float>), dim3(nb), dim3(kRT), 0, s, n,
+                             p, q, w, x, r, nullptr, fused_dot ? W.dparts : part_pq, npq, k,
+                             part_rho[(k + 1) & 1], part_rr, W.st);
           if (!fused_dir || j + 1 == m)
             hipLaunchKernelGGL((k_pcg_direction<double, float>), dim3(nb), dim3(kRT), 0, s, n, r,
                                w, nullptr, p, part_rho[(k + 1) & 1], part_rr, thr / bb, k + 1,

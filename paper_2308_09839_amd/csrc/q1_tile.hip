@@ -502,7 +502,7 @@ __global__ __launch_bounds__(256) void k_apply_block(
     const int32_t *__restrict__ slot, T *__restrict__ halo, const T *__restrict__ qdata,
     const uint32_t *__restrict__ tile_lat, const uint32_t *__restrict__ tile_addr,
     const int32_t *__restrict__ tile_g0, int64_t sy, int64_t sz, double *__restrict__ dot_part,
-    int open, DIR dir) {
+    DIR dir) {
   constexpr int DPN = phys_dpn(PH);
   constexpr bool STEP = !std::is_same<DIR, NoDir>::value;
   const int halt = stop ? *stop : 0;  // tested once the tile's records are requested
@@ -551,7 +551,6 @@ __global__ __launch_bounds__(256) void k_apply_block(
   // The first round's node words stay in registers for the write-back.
   uint32_t keep[KN];
   int32_t kslot[KN];
-  double dsum = 0.0;
   for (int base = 0; base < nm; base += KN * 256) {
     uint32_t raw[KN];
     T rec[KN][NR];
@@ -611,10 +610,6 @@ __global__ __launch_bounds__(256) void k_apply_block(
           sR[size_t(UOFF + j) * MN + i] = fixed ? T(0) : rec[k][UOFF + j];
 #pragma unroll
         for (int c = 0; c < NACC * DPN; ++c) sV[size_t(c) * MN + i] = T(0);
-        if (open && fixed && !(raw[k] & kSharedBit))
-#pragma unroll
-          for (int j = 0; j < DPN; ++j)
-            dsum += double(rec[k][UOFF + j]) * double(rec[k][UOFF + j]);
       }
     }
   }
@@ -641,9 +636,8 @@ __global__ __launch_bounds__(256) void k_apply_block(
   __syncthreads();
   // nodes of this tile only: y; nodes shared with other tiles: this tile's halo
   // slot (summed by k_halo_sum); Dirichlet nodes: written by k_halo_sum.
-  // dot_part: this tile's share of x.y, over the nodes it writes to y or, where the halo
-  // sum is left open, over x and its own sums of every free node (x.y is linear in
-  // them) and the Dirichlet nodes (y = x) that no earlier tile stages
+  // dot_part: this tile's share of x.y, over the nodes it writes to y
+  double dsum = 0.0;
   auto write_node = [&](int i, uint32_t raw, int32_t sl) {
     if (raw & kFixedBit) return;
     const int64_t gg = raw & kIdMask;
@@ -655,12 +649,12 @@ __global__ __launch_bounds__(256) void k_apply_block(
         v = sV[o];
       else
         v = (sV[o] + sV[cs + o]) + (sV[2 * cs + o] + sV[3 * cs + o]);
-      if (raw & kSharedBit)
+      if (raw & kSharedBit) {
         halo[int64_t(sl) * DPN + j] = v;
-      else
+      } else {
         y[gg * DPN + j] = v;
-      if (dot_part && (open || !(raw & kSharedBit)))
-        dsum += double(sR[size_t(UOFF + j) * MN + i]) * double(v);
+        if (dot_part) dsum += double(sR[size_t(UOFF + j) * MN + i]) * double(v);
+      }
     }
   };
 #pragma unroll
@@ -1683,12 +1677,8 @@ int plan_tiles(const std::vector<int32_t> &conn, const std::vector<T> &xyz,
   std::vector<int32_t> rank(nr, 0);
   for (size_t i = 0; i < H.nodes.size(); ++i) {
     const uint32_t v = H.nodes[i];
-    if (!(v & kSharedBit)) continue;
+    if (!(v & kSharedBit) || (v & kFixedBit)) continue;
     const int32_t jj = local[v & kIdMask], r = rank[jj]++;
-    if (v & kFixedBit) {  // the shared bit of a Dirichlet entry: an earlier tile has the node
-      if (r == 0) H.nodes[i] &= ~kSharedBit;
-      continue;
-    }
     H.slot[i] = r < 2 ? int32_t(r * nr + jj) : int32_t(2 * nr + H.hptr[jj] + (r - 2));
   }
   return Q1_OK;
@@ -1955,12 +1945,6 @@ int build_tiles_t(Op &op, hipStream_t s, int patch_x, int patch_y, int layers) {
         (rc = up(&tm.hnode, H.hnode)))
       return rc;
     tm.n_halo = 2 * int64_t(H.reset.size()) + H.hptr.back();
-    if (hex && !H.orphans && tm.own_nx == 0 && !H.reset.empty()) {
-      std::vector<int32_t> hmap(size_t(nn), -1);
-      for (size_t j = 0; j < H.hnode.size(); ++j)
-        hmap[H.hnode[j] & 0x3fffffff] = int32_t(j) | (H.hnode[j] < 0 ? kOpenFixed : 0);
-      if ((rc = up(&tm.hmap, hmap))) return rc;
-    }
     const size_t hb = std::max<int64_t>(1, tm.n_halo) * op.dpn() * sizeof(T);
     Q1_HIP(hipMalloc(&tm.halo, hb));
     tm.bytes += hb;
@@ -2014,11 +1998,9 @@ int64_t halo_blocks(const TileMap &tm) {
 // halo_blocks(tm) partials at dot[0..) that include the tile partials at
 // dot[halo_blocks(tm)..); without them, the tile partials at dot[0..).
 // dir: the direction step in the staging (x is then p_old, and the apply's input p_new).
-// open: the halo sum is left to the caller (see OpenSum), y is written on the nodes of one
-// tile only, and dot holds one partial per tile.
 template <typename T, int PH, class DIR = NoDir>
 int apply_tile_t(Op &op, const void *xv, void *yv, hipStream_t s, const int *stop,
-                 double *dot = nullptr, const DIR &dir = DIR(), bool open = false) {
+                 double *dot = nullptr, const DIR &dir = DIR()) {
   constexpr int DPN = phys_dpn(PH);
   const TileMap &tm = op.tiles;
   const T *x = static_cast<const T *>(xv);
@@ -2097,11 +2079,10 @@ int apply_tile_t(Op &op, const void *xv, void *yv, hipStream_t s, const int *sto
                        static_cast<const T *>(op.xyz), x, y, stop, tm.tile_affine, tm.slot,
                        static_cast<T *>(tm.halo), static_cast<const T *>(tm.qdata),
                        tm.tile_lat, tm.tile_addr, tm.tile_g0, tm.sy, tm.sz,
-                       dot ? dot + (tm.n_reset > 0 && !open ? halo_blocks(tm) : 0) : nullptr,
-                       open ? 1 : 0, dir);
+                       dot ? dot + (tm.n_reset > 0 ? halo_blocks(tm) : 0) : nullptr, dir);
     const T *in = x;
     if constexpr (STEP) in = dir.p_new;
-    if (tm.n_reset > 0 && !open)
+    if (tm.n_reset > 0)
       hipLaunchKernelGGL((k_halo_sum<T, DPN>), dim3(int(halo_blocks(tm))), dim3(256), 0, s,
                          tm.n_reset, tm.hnode, tm.hptr, in, static_cast<const T *>(tm.halo), y,
                          stop, dot, dot ? dot + halo_blocks(tm) : nullptr, int64_t(tm.n_tiles));
@@ -2218,20 +2199,12 @@ int64_t apply_dot_parts(const Op &op, int64_t *n_final) {
   return h + op.tiles.n_tiles;
 }
 
-bool apply_open(const Op &op, OpenSum *o) {
-  const TileMap &tm = op.tiles;
-  if (!tm.hmap || apply_dot_parts(op, nullptr) == 0) return false;
-  if (o) *o = {tm.hmap, tm.hptr, tm.halo, tm.n_reset, tm.n_tiles};
-  return true;
-}
-
 int launch_apply_dot(Op &op, const void *x, void *y, hipStream_t s, const int *stop,
-                     double *parts, bool open) {
-  Q1_CHECK(apply_dot_parts(op, nullptr) > 0 && (!open || apply_open(op, nullptr)),
-           Q1_EUNSUPPORTED, "apply with partial dot products: block variants of hexahedra only");
+                     double *parts) {
+  Q1_CHECK(apply_dot_parts(op, nullptr) > 0, Q1_EUNSUPPORTED,
+           "apply with partial dot products: block variants of hexahedra only");
   return dispatch_phys(op, [&](auto t, auto ph) {
-    return apply_tile_t<decltype(t), decltype(ph)::value>(op, x, y, s, stop, parts, NoDir(),
-                                                          open);
+    return apply_tile_t<decltype(t), decltype(ph)::value>(op, x, y, s, stop, parts);
   });
 }
 
@@ -2241,18 +2214,16 @@ bool apply_dir_ok(const Op &op) {
   return tm.own_nx > 0 || (op.elem == Q1_HEX8 && tm.split && !tm.orphans);
 }
 
-int launch_apply_dir(Op &op, const DirStep &d, void *q, hipStream_t s, double *parts,
-                     bool open) {
-  Q1_CHECK(apply_dir_ok(op) && (!open || apply_open(op, nullptr)), Q1_EUNSUPPORTED,
-           "direction step: block tiles of hexahedra only");
+int launch_apply_dir(Op &op, const DirStep &d, void *q, hipStream_t s, double *parts) {
+  Q1_CHECK(apply_dir_ok(op), Q1_EUNSUPPORTED, "direction step: block tiles of hexahedra only");
   const int *stop = &d.st->done;
   return dispatch_phys(op, [&](auto t, auto ph) -> int {
     using T = decltype(t);
     constexpr int PH = decltype(ph)::value;
     if constexpr (std::is_same<T, float>::value)
       if (!d.wide)
-        return apply_tile_t<T, PH>(op, d.p_old, q, s, stop, parts, Dir<float, T>(d), open);
-    return apply_tile_t<T, PH>(op, d.p_old, q, s, stop, parts, Dir<double, T>(d), open);
+        return apply_tile_t<T, PH>(op, d.p_old, q, s, stop, parts, Dir<float, T>(d));
+    return apply_tile_t<T, PH>(op, d.p_old, q, s, stop, parts, Dir<double, T>(d));
   });
 }
 
@@ -2280,7 +2251,7 @@ void free_tiles(Op &op) {
   void *ptrs[] = {t.node_ptr, t.nodes, t.tile_step, t.lconn, t.reset,
                   t.coef_t,   t.tile_affine, t.slot, t.hptr, t.halo, t.qdata, t.tile_lat,
                   t.tile_addr, t.tile_g0,
-                  t.hnode, t.hmap, t.onodes, t.nptr, t.pos};
+                  t.hnode, t.onodes, t.nptr, t.pos};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   t = TileMap{};
