@@ -613,7 +613,7 @@ int read_status(Work &W, hipStream_t s) {
 // a batch is three quarters of what the mean rate of a cycle (the solve, or the iterations
 // between two refreshes) still needs, at least 6, and the next cycle starts with the rate of
 // the one before.  Doubling from 1 to 32 in every cycle instead, a 48^3 mixed elasticity
-// solve took 25.3 ms (now 23.7), a 64^3 Laplace PCG 7.10 (7.01).
+// solve to 1e-8 took 27.3 ms (now 25.9), a 64^3 Laplace PCG 6.27 (6.11).
 struct Batches {
   double rate = 0.0, lr0 = 0.0;  // of ln r.r per iteration; ln r.r at the start of the cycle
   int k0 = 0, last = 0;

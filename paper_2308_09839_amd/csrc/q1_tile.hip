@@ -506,6 +506,8 @@ __global__ __launch_bounds__(256) void k_apply_block(
   constexpr int DPN = phys_dpn(PH);
   constexpr bool STEP = !std::is_same<DIR, NoDir>::value;
   const int halt = stop ? *stop : 0;  // tested once the tile's records are requested
+  if constexpr (!ALLPAR && !STEP)  // (at once in the general instance: 1% on its 58 us)
+    if (halt) return;
   double beta = 0.0;
   constexpr int UOFF = PA ? 0 : 3;
   constexpr int NR = UOFF + DPN;  // [x, y, z,] u[DPN], stored field by field
@@ -1252,7 +1254,7 @@ __global__ __launch_bounds__(256) void k_halo_sum(int64_t n, const int32_t *__re
                                                   double *__restrict__ dot_part,
                                                   const double *__restrict__ tile_part,
                                                   int64_t n_tiles) {
-  constexpr int kHaloX = DPN == 1 ? 6 : 2;
+  constexpr int kHaloX = DPN == 1 && sizeof(T) == 4 ? 6 : 2;
   const int halt = stop ? *stop : 0;  // tested once the first loads are out
   const int64_t base = int64_t(blockIdx.x) * 256 * kHaloNpt + threadIdx.x;
   int64_t jj[kHaloNpt];
@@ -1276,7 +1278,7 @@ __global__ __launch_bounds__(256) void k_halo_sum(int64_t n, const int32_t *__re
     for (int c = 0; c < DPN; ++c)
       xv[p][c] = x ? x[int64_t(dot_part || h[p] < 0 ? h[p] & 0x3fffffff : 0) * DPN + c] : T(1);
   // the extra slots of nodes on more than two tiles, several at a time (on a lattice an
-  // edge has two and a corner six; six at a time cost the 3-DOF kinds their occupancy)
+  // edge has two and a corner six; six at a time cost the FP64 and 3-DOF kinds occupancy)
 #pragma unroll
   for (int p = 0; p < kHaloNpt; ++p)
     for (int32_t k = e0[p]; k < e1[p]; k += kHaloX) {
