@@ -92,18 +92,21 @@ __device__ __forceinline__ double sum_partials(const double *__restrict__ part, 
 
 // The test after iteration `it` of the PCG and beta = rho_it / rho_{it-1}, the same in every
 // block (of kRT threads); block 0 records the status and rho_it.  True: the solve stops.
-// part_num, part_rr: nb partials of rho_it and of r.r.
-__device__ __forceinline__ bool direction_test(const double *part_num, const double *part_rr,
-                                               int nb, double tol2, int it, int maxit, Status *st,
-                                               double &beta) {
+// part_num, part_rr: nb partials of rho_it and of r.r.  done: this thread's reading of st->done,
+// which block 0 of the same launch may raise between the readings of two waves.  So every
+// thread takes part in the sums whatever it read: one that read the raised flag stops by it,
+// one that did not by the test that raised it, and the waves of a block never part.
+__device__ __forceinline__ bool direction_test(int done, const double *part_num,
+                                               const double *part_rr, int nb, double tol2, int it,
+                                               int maxit, Status *st, double &beta) {
   const double den = st->rho2[(it + 1) & 1], bb = st->bb;  // neither is written in this kernel
   double t[2];
   sum_partials_n<2>({part_num, part_rr}, nb, t);
   const double num = t[0], rr = t[1];
   const bool conv = rr <= tol2 * bb, bad = !isfinite(rr);
-  const bool stop = conv || bad || it >= maxit;
+  const bool stop = done || conv || bad || it >= maxit;
   beta = num / den;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (!done && blockIdx.x == 0 && threadIdx.x == 0) {
     st->iter = it;
     st->rr = rr;
     st->rho = num;

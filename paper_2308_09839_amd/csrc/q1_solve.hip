@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
   load(rg.i0 + threadIdx.x);
   const double rho = st->rho2[k & 1];
   const double pq = sum_partials(part_pq, npq);
-  if (done) return;
+  if (done) return;  // (after the sum: see direction_test)
   if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       st->done = 1;
@@ -223,8 +223,7 @@ __global__ __launch_bounds__(kRT) void k_pcg_direction(
   };
   load(rg.i0 + threadIdx.x);
   double beta;
-  if (done) return;
-  if (direction_test(part_num, part_rr, nb, tol2, it, maxit, st, beta)) return;
+  if (direction_test(done, part_num, part_rr, nb, tol2, it, maxit, st, beta)) return;
   for (int64_t i0 = rg.i0 + threadIdx.x; i0 < rg.i1; i0 += U * kRT) {
     if (i0 >= rg.i0 + U * kRT) load(i0);
 #pragma unroll
@@ -457,11 +456,12 @@ __global__ __launch_bounds__(kRT) void k_fcg_update(int64_t n, const T *__restri
                                                     const double *__restrict__ part_pr,
                                                     double *__restrict__ part_rr,
                                                     Status *__restrict__ st) {
-  if (st->done) return;
+  const int done = st->done;
   const int nb = gridDim.x;
   double t[2];
   sum_partials_n<2>({part_pq, part_pr}, nb, t);
   const double pq = t[0], pr = t[1];
+  if (done) return;  // (after the sum: see direction_test)
   if (!(pq > 0.0) || !isfinite(pq) || !isfinite(pr)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       st->done = 1;

@@ -473,8 +473,8 @@ struct Dir {
       : r(static_cast<const TS *>(d.r)), w(static_cast<const TS *>(d.w)),
         p_new(static_cast<T *>(d.p_new)), num(d.num), rr(d.rr), nb(d.nb), tol2(d.tol2), it(d.it),
         maxit(d.maxit), st(d.st) {}
-  __device__ __forceinline__ bool test(double &beta) const {
-    return direction_test(num, rr, nb, tol2, it, maxit, st, beta);
+  __device__ __forceinline__ bool test(int done, double &beta) const {
+    return direction_test(done, num, rr, nb, tol2, it, maxit, st, beta);
   }
   static __device__ __forceinline__ T value(TS z, T p, double beta) {
     return direction_value<T>(z, p, beta);
@@ -505,7 +505,11 @@ __global__ __launch_bounds__(256) void k_apply_block(
     DIR dir) {
   constexpr int DPN = phys_dpn(PH);
   constexpr bool STEP = !std::is_same<DIR, NoDir>::value;
-  const int halt = stop ? *stop : 0;  // tested once the tile's records are requested
+  int halt;  // tested once the tile's records are requested; with the step, in its test
+  if constexpr (STEP)
+    halt = dir.st->done;
+  else
+    halt = stop ? *stop : 0;
   if constexpr (!ALLPAR && !STEP)  // (at once in the general instance: 1% on its 58 us)
     if (halt) return;
   double beta = 0.0;
@@ -586,10 +590,11 @@ __global__ __launch_bounds__(256) void k_apply_block(
       }
     }
     if (base == 0) first_step();
-    if (halt) return;
-    if constexpr (STEP) {
+    if constexpr (!STEP) {
+      if (halt) return;
+    } else {
       // the direction, stored by every tile that stages the node (the same value)
-      if (base == 0 && dir.test(beta)) return;
+      if (base == 0 && dir.test(halt, beta)) return;
 #pragma unroll
       for (int k = 0; k < KN; ++k) {
         const int64_t g = raw[k] & kIdMask;
@@ -747,7 +752,11 @@ __global__ __launch_bounds__(256) void k_apply_owner(int nx, int ny, int nz,
   constexpr bool STEP = !std::is_same<DIR, NoDir>::value;
   constexpr int NC = EK >= kOwnKuhn ? 6 : 1;  // cell coefficients
   constexpr bool ALLX = EK != kOwnPar;          // all 8 corners' coordinates
-  const int halt = stop ? *stop : 0;  // tested once the staging loads are out
+  int halt;  // tested once the staging loads are out; with the step, in its test
+  if constexpr (STEP)
+    halt = dir.st->done;
+  else
+    halt = stop ? *stop : 0;
   __shared__ T sR[4 * F::NS];   // x, y, z, input (0 on Dirichlet nodes), field by field
   __shared__ double sV[F::NA];  // accumulator over the owned box
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -834,10 +843,11 @@ __global__ __launch_bounds__(256) void k_apply_owner(int nx, int ny, int nz,
   T cnext[NC];
 #pragma unroll
   for (int t = 0; t < NC; ++t) cnext[t] = ld_off(coef, eo[0] + uint32_t(t * sizeof(T)));
-  if (halt) return;
-  if constexpr (STEP) {
+  if constexpr (!STEP) {
+    if (halt) return;
+  } else {
     double beta;
-    if (dir.test(beta)) return;
+    if (dir.test(halt, beta)) return;
 #pragma unroll
     for (int k = 0; k < F::KN; ++k) {
       rec[k][3] = dir.value(zr[k], rec[k][3], beta);
