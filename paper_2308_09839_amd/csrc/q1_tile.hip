@@ -979,12 +979,14 @@ __host__ __device__ inline size_t tet_acc_offset(int max_nodes, size_t rec_bytes
 // since the FP32 LDS atomic add measured twice as slow here).
 // CELLS: where every six elements in a row are a Kuhn cell (kuhn_cells), a lane
 // slot is a cell: the lane reads the cell's 8 corners once instead of 24, forms
-// its six products from registers and adds 8 corners instead of 24.  The LDS had
+// its six products from registers, sums them in FP64 and adds 8 corners instead of 24
+// (sums in the FP32 operator's own precision were 3% faster there).  The LDS had
 // bounded the kernel (57% of its time busy, a third of that in conflicts, now
 // rare: neighbouring lanes hold neighbouring cells).  us per streaming apply with
 // its halo sum, one tetrahedron per lane -> cells, jittered 51 x 47 x 61 cells:
-// elasticity FP64 36.1 -> 18.8, FP32 33.2 -> 12.8; Laplace FP64 21.0 -> 11.7, FP32
-// 19.6 -> 9.8; 12 x 13 x 11 elasticity 12.0 -> 10.2; 96 x 80 x 72 90.6 -> 42.1.
+// elasticity FP64 36.4 -> 18.3, FP32 33.7 -> 13.2; Laplace FP64 21.0 -> 11.7, FP32
+// 20.2 -> 11.3; 12 x 13 x 11 elasticity FP64 12.0 -> 10.2, FP32 Laplace 11.2 -> 11.3
+// (both launch-bound); 64 x 60 x 60 elasticity FP32 47.6 -> 14.7.
 template <typename T, int PH, bool CELLS>
 __global__ __launch_bounds__(256) void k_apply_block_tet(
     int max_nodes, int64_t nn, const int32_t *__restrict__ node_ptr,
@@ -1063,7 +1065,8 @@ __global__ __launch_bounds__(256) void k_apply_block_tet(
       const int lc[8] = {int(pk.x & 0xffff), int(pk.x >> 16), int(pk.y & 0xffff),
                          int(pk.y >> 16),    int(pk.z & 0xffff), int(pk.z >> 16),
                          int(pk.w & 0xffff), int(pk.w >> 16)};
-      T X[3][8], u[DPN][8], v[DPN][8];
+      T X[3][8], u[DPN][8];
+      double v[DPN][8];  // FP64 in both precisions, as the accumulator
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
 #pragma unroll
@@ -1071,7 +1074,7 @@ __global__ __launch_bounds__(256) void k_apply_block_tet(
 #pragma unroll
         for (int j = 0; j < DPN; ++j) {
           u[j][a] = sR[size_t(3 + j) * max_nodes + lc[a]];
-          v[j][a] = T(0);
+          v[j][a] = 0.0;
         }
       }
 #pragma unroll
@@ -1088,13 +1091,13 @@ __global__ __launch_bounds__(256) void k_apply_block_tet(
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int j = 0; j < DPN; ++j) v[j][kKuhn[t][q]] += vt[j][q];
+          for (int j = 0; j < DPN; ++j) v[j][kKuhn[t][q]] += double(vt[j][q]);
       }
 #pragma unroll
       for (int a = 0; a < 8; ++a)
 #pragma unroll
         for (int j = 0; j < DPN; ++j)
-          lds_add(&sV[size_t(j) * max_nodes + lc[a]], double(v[j][a]));
+          lds_add(&sV[size_t(j) * max_nodes + lc[a]], v[j][a]);
     }
   } else {
     // steps w, w + 4, ...: each step's corner indices and coefficients are
