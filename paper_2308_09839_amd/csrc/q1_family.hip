@@ -481,6 +481,11 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
 #pragma unroll
   for (int m = 0; m < 3 + DPN; ++m) {
     T B[N], D[N], U[N], a[N], b[N], c[N];
+    if (m < 3) {  // from the middle node (see above)
+      const T o = __shfl(f[m][1], (N + 1) * Q::EW + le);
+#pragma unroll
+      for (int i = 0; i < N; ++i) f[m][i] -= o;
+    }
     Ln::template eval<true, true>(f[m], B, D);
 #pragma unroll
     for (int q = 0; q < N; ++q) px[q] = {B[q], D[q]};
