@@ -324,10 +324,15 @@ __device__ __forceinline__ T qp_point(int r, const T (*sX)[QP<P>::NPTS],
 // nodes are symmetric): 10 operations for B f and D f at the three points of order 2, not
 // 18.  The last node of a line is added to the next element's first when the two lanes
 // hold the same node id, which saves a third (order 2) or a quarter of the atomics.
+// Coordinates are taken from the element's middle node (order 3: a node next to the middle),
+// since the Jacobian is of differences only and pass A's values would round at the size of the
+// coordinates: error of an apply against 64 bits, absolute coordinates -> here, order 2 on
+// 64^3 7.1e-15 -> 5.0e-15, order 3 on 42^3 2.6e-14 -> 2.3e-14 (5.8e-15 and 4.0e-14 with direct
+// sums per point); FP32 2.3e-6 -> 1.7e-7 on 33 x 29 x 41.  Its cost is 1.4%.
 //
 // What bounds it: the LDS turns (busy 71% of the time at order 2 in FP64), then the
 // gathers' cache accesses and FP64 issue.  FP64 Laplace, order 2 on 64^3 74 us, order 3 on
-// 42^3 64 us; with an atomic per lane and node in place of the rows (2.4 sums to a request;
+// 42^3 65 us; with an atomic per lane and node in place of the rows (2.4 sums to a request;
 // the requests leave L2 for memory) 111 and 119 us; one thread per node and point, which
 // read each line N times and met at workgroup barriers, 285 and 349 us.  Measured and
 // dropped: box tiles on lattices with sums kept in LDS over a march in z (114 us at order
@@ -481,7 +486,7 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
 #pragma unroll
   for (int m = 0; m < 3 + DPN; ++m) {
     T B[N], D[N], U[N], a[N], b[N], c[N];
-    if (m < 3) {  // from the middle node (see above)
+    if (m < 3) {  // from the element's middle node, which line (1, 1) holds
       const T o = __shfl(f[m][1], (N + 1) * Q::EW + le);
 #pragma unroll
       for (int i = 0; i < N; ++i) f[m][i] -= o;
