@@ -455,7 +455,11 @@ __device__ __forceinline__ void block_steps_split(int s0, int s1, int w, int lan
 // round trip through memory are saved; r and w are multiplied as they arrive, so the staging
 // holds one register more per value.  Microseconds per iteration, separate -> here: Laplace PCG
 // 64^3 23.5 -> 19.7, 128^3 76.1 -> 69.0, jittered 128^3 111.9 -> 109.7; elasticity PCG 96^3
-// 86.4 -> 82.6; mixed elasticity 48^3 26.6 -> 23.5: faster at every size, so no size rule.
+// 86.4 -> 82.6; mixed elasticity 48^3 26.6 -> 23.5.  On boxes that are no multiple of the
+// tile (the general-shape instances), whole solves to 1e-10 in ms: Laplace 63 x 50 x 45
+// 7.89 -> 6.87, 13 x 11 x 17 2.25 -> 1.98, jittered 57 x 61 x 63 11.9 -> 10.8; elasticity 47 x
+// 45 x 43 32.1 -> 28.8; mixed elasticity 45 x 37 x 41 28.2 -> 25.8, mixed Laplace jittered 57 x
+// 61 x 63 12.4 -> 12.0: faster in all of 15 cases and 4 kinds of tile, so no rule on sizes.
 struct NoDir {
   using Real = char;
 };
@@ -492,7 +496,7 @@ struct Dir {
 // accumulation), whose shape is built in.
 constexpr int kAccSplit = 0, kAccShared = 1, kAccCopies = 2;
 template <typename T, int PH, bool LDS_ATOMIC, int ACC, bool PA, bool ALLPAR, bool FX = false,
-          class DIR = NoDir>
+          class DIR = NoDir, int KG = 4>
 __global__ __launch_bounds__(256) void k_apply_block(
     int max_nodes, int64_t nn, const int32_t *__restrict__ node_ptr,
     const uint32_t *__restrict__ nodes, const int32_t *__restrict__ tile_step,
@@ -516,8 +520,11 @@ __global__ __launch_bounds__(256) void k_apply_block(
   constexpr int UOFF = PA ? 0 : 3;
   constexpr int NR = UOFF + DPN;  // [x, y, z,] u[DPN], stored field by field
   using FT = FxTile<DPN>;
-  // node records per thread issued together (all of a fixed tile, else 1024 per round)
-  constexpr int KN = FX ? (FT::NODES + 255) / 256 : 4;
+  // node records per thread issued together: all of a fixed tile, else 256 KG per round
+  // (the host's choice by the largest tile: loads past a tile's end are repeats, and with the
+  // direction step their registers had cost residency, 4 -> 2 waves per SIMD in FP64
+  // elasticity, where KG is 2 and not 4 now: 47 x 45 x 43 PCG 31.0 -> 29.1 ms)
+  constexpr int KN = FX ? (FT::NODES + 255) / 256 : KG;
   static_assert(!FX || (ACC == kAccSplit && !PA), "FX instance");
   // the LDS stride of a field: a constant on the fixed tile
   const int MN = FX ? FT::NODES : max_nodes;
@@ -2068,9 +2075,14 @@ int apply_tile_t(Op &op, const void *xv, void *yv, hipStream_t s, const int *sto
     // fallback accumulation when some tile does not admit the split one
     constexpr int FB = std::is_same<T, double>::value ? kAccShared : kAccCopies;
     const bool allpar = tm.all_affine && !pa;
+    // staging rounds that hold a box's tiles (at most 765 nodes, 425 with 3 DOF) at once;
+    // tiles of more nodes, as unstructured meshes have, keep four
+    constexpr int KS = DPN == 1 ? 3 : 2;
+    const bool few = tm.max_nodes <= KS * 256;
     auto pick = [&](auto pa_c, auto allpar_c) {
       constexpr bool P = decltype(pa_c)::value, AP = decltype(allpar_c)::value;
-      return tm.split        ? k_apply_block<T, PH, false, kAccSplit, P, AP>
+      return tm.split ? (few ? k_apply_block<T, PH, false, kAccSplit, P, AP, false, NoDir, KS>
+                             : k_apply_block<T, PH, false, kAccSplit, P, AP>)
              : tm.lds_atomic ? k_apply_block<T, PH, true, FB, P, AP>
                              : k_apply_block<T, PH, false, FB, P, AP>;
     };
@@ -2078,8 +2090,10 @@ int apply_tile_t(Op &op, const void *xv, void *yv, hipStream_t s, const int *sto
     using ff = std::false_type;
     auto plain = [&]() {
       if constexpr (STEP)  // split tiles only (apply_dir_ok)
-        return allpar ? k_apply_block<T, PH, false, kAccSplit, false, true, false, DIR>
-                      : k_apply_block<T, PH, false, kAccSplit, false, false, false, DIR>;
+        return few ? (allpar ? k_apply_block<T, PH, false, kAccSplit, false, true, false, DIR, KS>
+                             : k_apply_block<T, PH, false, kAccSplit, false, false, false, DIR, KS>)
+                   : (allpar ? k_apply_block<T, PH, false, kAccSplit, false, true, false, DIR>
+                             : k_apply_block<T, PH, false, kAccSplit, false, false, false, DIR>);
       else
         return pa ? pick(tt{}, ff{}) : allpar ? pick(ff{}, tt{}) : pick(ff{}, ff{});
     };
