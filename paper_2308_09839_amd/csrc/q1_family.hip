@@ -446,8 +446,14 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
   using Q = QL<P>;
   using Ln = Line<T, P>;
   if (stop && *stop) return;
-  constexpr int NP = Q::EW * Q::S;
-  __shared__ Two<T> area[kFB / 64][NP + (NP + 1) / 2];  // pairs, then single values
+  // Fields at a time.  Small meshes leave a SIMD one wave, whose time is its chain of LDS
+  // turns; two fields share each turn's latency: order 3, FP64 elasticity, 4 x 5 x 6 elements
+  // 11.6 -> 10.8 us (11.1 with one thread per node and point; the two launches take 10.3), 13 x
+  // 15 x 17 14.1 -> 13.8, 21 x 20 x 19 20.9 -> 21.1.  Registers allow two waves per SIMD there,
+  // and two areas of LDS as well; order 2 would lose the third.
+  constexpr int F = P == 3 && DPN == 3 ? 2 : 1;
+  constexpr int NP = Q::EW * Q::S, FS = NP + (NP + 1) / 2;
+  __shared__ Two<T> area[kFB / 64][F * FS];  // per field: pairs, then single values
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   Two<T> *pairs = area[w];
   T *singles = reinterpret_cast<T *>(pairs + NP);
@@ -484,43 +490,56 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
 
   T G[3 + DPN][3][N];  // reference gradients at the lane's points (ra, rb, 0..N-1)
 #pragma unroll
-  for (int m = 0; m < 3 + DPN; ++m) {
-    T B[N], D[N], U[N], a[N], b[N], c[N];
-    if (m < 3) {  // from the element's middle node, which line (1, 1) holds
-      const T o = __shfl(f[m][1], (N + 1) * Q::EW + le);
+  for (int m = 0; m < 3 + DPN; m += F) {
+    T B[F][N], D[F][N], U[N], a[F][N], b[F][N], c[F][N];
 #pragma unroll
-      for (int i = 0; i < N; ++i) f[m][i] -= o;
-    }
-    Ln::template eval<true, true>(f[m], B, D);
+    for (int h = 0; h < F; ++h) {
+      if (m + h < 3) {  // from the element's middle node, which line (1, 1) holds
+        const T o = __shfl(f[m + h][1], (N + 1) * Q::EW + le);
 #pragma unroll
-    for (int q = 0; q < N; ++q) px[q] = {B[q], D[q]};
-    lds_turn();
+        for (int i = 0; i < N; ++i) f[m + h][i] -= o;
+      }
+      Ln::template eval<true, true>(f[m + h], B[h], D[h]);
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const Two<T> t = py[Q::A * q];
-      a[q] = t.a;
-      b[q] = t.b;
-    }
-    lds_turn();
-    Ln::template eval<true, true>(a, B, D);
-    Ln::template eval<true, false>(b, U, U);
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      py[Q::A * q] = {U[q], D[q]};
-      sy[Q::A * q] = B[q];
+      for (int q = 0; q < N; ++q) px[h * FS + q] = {B[h][q], D[h][q]};
     }
     lds_turn();
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const Two<T> t = pz[Q::B * q];
-      a[q] = t.a;
-      b[q] = t.b;
-      c[q] = sz[Q::B * q];
+    for (int h = 0; h < F; ++h)
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const Two<T> t = py[h * FS + Q::A * q];
+        a[h][q] = t.a;
+        b[h][q] = t.b;
+      }
+    lds_turn();
+#pragma unroll
+    for (int h = 0; h < F; ++h) {
+      Ln::template eval<true, true>(a[h], B[h], D[h]);
+      Ln::template eval<true, false>(b[h], U, U);
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        py[h * FS + Q::A * q] = {U[q], D[h][q]};
+        sy[2 * h * FS + Q::A * q] = B[h][q];
+      }
     }
     lds_turn();
-    Ln::template eval<true, false>(a, G[m][0], G[m][0]);
-    Ln::template eval<true, false>(b, G[m][1], G[m][1]);
-    Ln::template eval<false, true>(c, G[m][2], G[m][2]);
+#pragma unroll
+    for (int h = 0; h < F; ++h)
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const Two<T> t = pz[h * FS + Q::B * q];
+        a[h][q] = t.a;
+        b[h][q] = t.b;
+        c[h][q] = sz[2 * h * FS + Q::B * q];
+      }
+    lds_turn();
+#pragma unroll
+    for (int h = 0; h < F; ++h) {
+      Ln::template eval<true, false>(a[h], G[m + h][0], G[m + h][0]);
+      Ln::template eval<true, false>(b[h], G[m + h][1], G[m + h][1]);
+      Ln::template eval<false, true>(c[h], G[m + h][2], G[m + h][2]);
+    }
   }
   // the flux of component c and direction d, in place of the input's gradients
   const T wxy = gwt<T, P>(ra) * gwt<T, P>(rb);
@@ -562,40 +581,53 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
   }
   T v[DPN][N];
 #pragma unroll
-  for (int m = 0; m < DPN; ++m) {
-    T a[N], b[N], c[N], u0[N], u1[N];
-    Ln::template transp<false, false>(G[3 + m][0], a);
-    Ln::template transp<false, false>(G[3 + m][1], b);
-    Ln::template transp<true, false>(G[3 + m][2], c);
+  for (int m = 0; m < DPN; m += F) {
+    T a[F][N], b[F][N], c[F][N], u0[N], u1[N];
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      pz[Q::B * q] = {a[q], b[q]};
-      sz[Q::B * q] = c[q];
+    for (int h = 0; h < F && m + h < DPN; ++h) {
+      Ln::template transp<false, false>(G[3 + m + h][0], a[h]);
+      Ln::template transp<false, false>(G[3 + m + h][1], b[h]);
+      Ln::template transp<true, false>(G[3 + m + h][2], c[h]);
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        pz[h * FS + Q::B * q] = {a[h][q], b[h][q]};
+        sz[2 * h * FS + Q::B * q] = c[h][q];
+      }
     }
     lds_turn();
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const Two<T> t = py[Q::A * q];
-      a[q] = t.a;
-      b[q] = t.b;
-      c[q] = sy[Q::A * q];
-    }
-    lds_turn();
-    Ln::template transp<false, false>(a, u0);
-    Ln::template transp<true, false>(b, u1);
-    Ln::template transp<false, true>(c, u1);
+    for (int h = 0; h < F && m + h < DPN; ++h)
 #pragma unroll
-    for (int q = 0; q < N; ++q) py[Q::A * q] = {u0[q], u1[q]};
+      for (int q = 0; q < N; ++q) {
+        const Two<T> t = py[h * FS + Q::A * q];
+        a[h][q] = t.a;
+        b[h][q] = t.b;
+        c[h][q] = sy[2 * h * FS + Q::A * q];
+      }
     lds_turn();
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const Two<T> t = px[q];
-      a[q] = t.a;
-      b[q] = t.b;
+    for (int h = 0; h < F && m + h < DPN; ++h) {
+      Ln::template transp<false, false>(a[h], u0);
+      Ln::template transp<true, false>(b[h], u1);
+      Ln::template transp<false, true>(c[h], u1);
+#pragma unroll
+      for (int q = 0; q < N; ++q) py[h * FS + Q::A * q] = {u0[q], u1[q]};
     }
     lds_turn();
-    Ln::template transp<true, false>(a, v[m]);
-    Ln::template transp<false, true>(b, v[m]);
+#pragma unroll
+    for (int h = 0; h < F && m + h < DPN; ++h)
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const Two<T> t = px[h * FS + q];
+        a[h][q] = t.a;
+        b[h][q] = t.b;
+      }
+    lds_turn();
+#pragma unroll
+    for (int h = 0; h < F && m + h < DPN; ++h) {
+      Ln::template transp<true, false>(a[h], v[m + h]);
+      Ln::template transp<false, true>(b[h], v[m + h]);
+    }
   }
   // the line's last node goes to the next element's lane when that starts with it
   const int32_t next = __shfl(nid[0], (lane + Q::LS) & 63);
@@ -623,11 +655,21 @@ __global__ __launch_bounds__(kFB) void k_qp_apply(int64_t ne, int64_t nn,
       ids[at + i] = active && !fixed[i] && !(i == P && give) ? nid[i] : -1;
     }
   lds_turn();
+  // (all LDS reads before the first addition: under its branch each waited for the one before)
+  constexpr int K = (ENT * DPN + 63) / 64;
+  int32_t n[K];
+  T sum[K];
 #pragma unroll
-  for (int k = 0; k < (ENT * DPN + 63) / 64; ++k) {
+  for (int k = 0; k < K; ++k) {
+    const int j = min(k * 64 + lane, ENT * DPN - 1);
+    n[k] = ids[j / DPN];
+    sum[k] = out[j];
+  }
+  lds_turn();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
     const int j = k * 64 + lane;
-    const int32_t n = j < ENT * DPN ? ids[j / DPN] : -1;
-    if (n >= 0) gadd(&y[int64_t(n) * DPN + j % DPN], out[j]);
+    if (j < ENT * DPN && n[k] >= 0) gadd(&y[int64_t(n[k]) * DPN + j % DPN], sum[k]);
   }
 }
 
