@@ -50,7 +50,6 @@ namespace {
 
 constexpr int kW = 64;            // one wavefront per workgroup
 constexpr int kRmax = 4;
-constexpr uint32_t kSharedBitB = 0x80000000u;
 constexpr uint32_t kFixedBitB = 0x40000000u;
 constexpr uint32_t kIdMaskB = 0x3fffffffu;
 // In the copy of the tile node lists the search-direction phase reads, bit 29
@@ -100,7 +99,6 @@ struct BProb {
   const uint4 *lconn;
   const double *coef_t;
   const double *xyz;
-  const uint8_t *mask;
   const uint32_t *nptr;       // [nn + 1]: first slot of a node (bit 31: Dirichlet, no slots)
   const int32_t *pos;         // [entries]: slot of a tile entry (-1 on Dirichlet nodes)
   int64_t n_slots;
@@ -140,7 +138,6 @@ struct BProbG {
   const Q1_GLB uint4 *lconn;
   const Q1_GLB double *coef_t;
   const Q1_GLB double *xyz;
-  const Q1_GLB uint8_t *mask;
   const Q1_GLB uint32_t *nptr;
   const Q1_GLB int32_t *pos;
   int64_t n_slots;
@@ -178,7 +175,6 @@ __device__ __forceinline__ BProb load_problem(const BProb *src) {
   P.lconn = (const uint4 *)G.lconn;
   P.coef_t = (const double *)G.coef_t;
   P.xyz = (const double *)G.xyz;
-  P.mask = (const uint8_t *)G.mask;
   P.nptr = (const uint32_t *)G.nptr;
   P.pos = (const int32_t *)G.pos;
   P.n_slots = G.n_slots;
@@ -1026,7 +1022,6 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
   Q1_CHECK(nrhs >= 1 && nrhs <= kRmax, Q1_EINVAL, "%s: 1 <= nrhs <= %d", name, kRmax);
   Q1_CHECK(rtol >= 0 && maxit >= 0, Q1_EINVAL, "%s: bad tolerance or limit", name);
   Q1_CHECK(!mixed || (delta > 0 && delta < 1), Q1_EINVAL, "%s: need 0 < delta < 1", name);
-  int64_t total_elems = 0;
   int max_nodes = 0;
   for (int p = 0; p < nprob; ++p) {
     const Op *o = reinterpret_cast<const Op *>(ops[p]);
@@ -1036,7 +1031,6 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
              name, p);
     for (int c = 0; c < nrhs; ++c)
       Q1_CHECK(b_d[p * nrhs + c] && x_d[p * nrhs + c], Q1_EINVAL, "%s: NULL vector", name);
-    total_elems += o->n_elems;
     max_nodes = std::max(max_nodes, o->tiles.max_nodes);
   }
   // LDS per wave: FP64 accumulators, the staged directions (FP32 in the mixed form)
@@ -1114,7 +1108,6 @@ int batched_impl(const char *name, bool mixed, int nprob, q1_op *const *ops, int
     B.lconn = reinterpret_cast<const uint4 *>(tm.lconn);
     B.coef_t = static_cast<const double *>(tm.coef_t);
     B.xyz = static_cast<const double *>(o.xyz);
-    B.mask = o.mask;
     Q1_CHECK(n < int64_t(kIdMaskOwnB) && tm.onodes, Q1_EUNSUPPORTED, "%s: operator %d has %lld nodes (at most %u)",
              name, p, (long long)n, kIdMaskOwnB);
     B.onodes = tm.onodes;

@@ -309,7 +309,6 @@ constexpr int kWZero = 256;           // bytes of zeros that absent pieces read
 constexpr int kWAcc = 27 * 64 * 16;   // bytes of one wave's accumulators
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ bf16x8 ld_tr(const char *lds0, const char *lds1) {
   using L = __attribute__((address_space(3))) s16x4;

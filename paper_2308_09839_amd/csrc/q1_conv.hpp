@@ -43,7 +43,7 @@ struct ConvArgs {
   int cin = 0;
   PGrid g;                    // input and output grid
   const bf16 *wp = nullptr;   // packed weights [nchunks*4][cout][8], chunk-major K order
-  int ngroups = 0, nchunks = 0, cout = 0;  // nchunks: K-steps (conv_ksteps(cin))
+  int nchunks = 0, cout = 0;  // nchunks: K-steps (conv_ksteps(cin))
   const float *bias = nullptr;  // [cout] or null
   int relu = 0;
   Slice mask;                   // outputs where mask <= 0 become 0 (same grid), or p == null

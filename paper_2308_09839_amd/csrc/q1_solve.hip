@@ -134,20 +134,18 @@ __global__ __launch_bounds__(kRT) void k_dot(int64_t n, const T *__restrict__ a,
 }
 
 // alpha = rho_k / p.q; x += alpha p; r -= alpha q; partials rho_{k+1}, r.r.
-// FLEX (flexible PCG): keeps r_k in r_old and leaves rho_{k+1} to the
-// preconditioner step.  TP, the type of p and q, is float in the mixed-precision
+// TP, the type of p and q, is float in the mixed-precision
 // solver (FP32 operator), whose x, r and w stay in double.
 // npq: the number of p.q partials (the apply's when it forms them, else gridDim.x).
-template <typename T, bool FLEX, typename TP = T>
+template <typename T, typename TP = T>
 __global__ __launch_bounds__(kRT) void k_pcg_update(
     int64_t n, const TP *__restrict__ p, const TP *__restrict__ q, const T *__restrict__ w,
-    T *__restrict__ x, T *__restrict__ r, T *__restrict__ r_old,
+    T *__restrict__ x, T *__restrict__ r,
     const double *__restrict__ part_pq, int npq, int k, double *__restrict__ part_rho_k1,
     double *__restrict__ part_rr, Status *__restrict__ st) {
   // Nothing below depends on another load's result until alpha: the flag, the partials and
   // the first round of the vectors are requested together, one memory latency in all.
   const int done = st->done;
-  const int nb = gridDim.x;
   const Range rg = block_range(n);
   // four elements per thread and round: all their loads (at clamped indices)
   // before any store; the additions keep the order i, i + 256, ...
@@ -162,7 +160,7 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
       xv[u] = x[i];
       pv[u] = p[i];
       qv[u] = q[i];
-      if constexpr (!FLEX) wv[u] = w[i];
+      wv[u] = w[i];
     }
   };
   load(rg.i0 + threadIdx.x);
@@ -184,29 +182,27 @@ __global__ __launch_bounds__(kRT) void k_pcg_update(
     for (int u = 0; u < U; ++u) {
       const int64_t i = i0 + u * kRT;
       if (i >= rg.i1) continue;
-      if constexpr (FLEX) r_old[i] = rv[u];
       const T rn = T(double(rv[u]) - alpha * double(qv[u]));
       x[i] = T(double(xv[u]) + alpha * double(pv[u]));
       r[i] = rn;
-      if constexpr (!FLEX) v[0] += double(rn) * double(wv[u] * rn);
+      v[0] += double(rn) * double(wv[u] * rn);
       v[1] += double(rn) * double(rn);
     }
   }
   block_sum<2>(v);
   if (threadIdx.x == 0) {
-    if constexpr (!FLEX) part_rho_k1[blockIdx.x] = v[0];
+    part_rho_k1[blockIdx.x] = v[0];
     part_rr[blockIdx.x] = v[1];
   }
 }
 
 // Convergence test after iteration `it`; beta = rho_{k+1} / rho_k;
-// p = z + beta p with z = w r (PCG) or the stored z (flexible PCG); p of type TP
-// (rounded to it).
+// p = w r + beta p, of type TP (rounded to it).
 template <typename T, typename TP = T>
 __global__ __launch_bounds__(kRT) void k_pcg_direction(
-    int64_t n, const T *__restrict__ r, const T *__restrict__ w, const T *__restrict__ z,
-    TP *__restrict__ p, const double *__restrict__ part_num, const double *__restrict__ part_rr,
-    double tol2, int it, int maxit, Status *__restrict__ st) {
+    int64_t n, const T *__restrict__ r, const T *__restrict__ w, TP *__restrict__ p,
+    const double *__restrict__ part_num, const double *__restrict__ part_rr, double tol2, int it,
+    int maxit, Status *__restrict__ st) {
   const int done = st->done;  // as in k_pcg_update: one memory latency for all first loads
   const int nb = gridDim.x;
   const Range rg = block_range(n);
@@ -217,7 +213,7 @@ __global__ __launch_bounds__(kRT) void k_pcg_direction(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t i = min(i0 + u * kRT, n - 1);
-      zv[u] = z ? z[i] : T(w[i] * r[i]);
+      zv[u] = T(w[i] * r[i]);
       pv[u] = p[i];
     }
   };
@@ -231,29 +227,6 @@ __global__ __launch_bounds__(kRT) void k_pcg_direction(
       const int64_t i = i0 + u * kRT;
       if (i < rg.i1) p[i] = direction_value<TP>(zv[u], pv[u], beta);
     }
-  }
-}
-
-// Flexible PCG: partials of z.r (rho_{k+1}) and z.(r - r_old)
-template <typename T>
-__global__ __launch_bounds__(kRT) void k_fpcg_dots(int64_t n, const T *__restrict__ z,
-                                                   const T *__restrict__ r,
-                                                   const T *__restrict__ r_old,
-                                                   double *__restrict__ part_rho,
-                                                   double *__restrict__ part_num,
-                                                   const Status *__restrict__ st) {
-  if (st->done) return;
-  const Range rg = block_range(n);
-  double v[2] = {0.0, 0.0};
-  for (int64_t i = rg.i0 + threadIdx.x; i < rg.i1; i += kRT) {
-    const double zi = double(z[i]), ri = double(r[i]);
-    v[0] += zi * ri;
-    v[1] += zi * (ri - double(r_old[i]));
-  }
-  block_sum<2>(v);
-  if (threadIdx.x == 0) {
-    part_rho[blockIdx.x] = v[0];
-    part_num[blockIdx.x] = v[1];
   }
 }
 
@@ -537,8 +510,7 @@ __global__ __launch_bounds__(kRT) void k_fcg_check(const double *__restrict__ pa
 namespace {
 
 struct Work {
-  void *r = nullptr, *p = nullptr, *q = nullptr, *w = nullptr, *r_old = nullptr,
-       *z = nullptr;
+  void *r = nullptr, *p = nullptr, *q = nullptr, *w = nullptr, *z = nullptr;
   void *p2 = nullptr;      // second direction buffer (applies that take the direction step)
   double *part = nullptr;  // [8][kMaxRB]
   double *dparts = nullptr;  // [kMaxDotParts]: p.q partials formed by the apply
@@ -549,7 +521,7 @@ struct Work {
   Work(const Work &) = delete;
   ~Work() {
     if (!owned) return;
-    void *d[] = {r, p, q, w, r_old, z, p2, part, dparts, st};
+    void *d[] = {r, p, q, w, z, p2, part, dparts, st};
     for (void *v : d)
       if (v) (void)hipFree(v);
     if (hst) (void)hipHostFree(hst);
@@ -578,10 +550,7 @@ int alloc_work(Work &W, int64_t n, bool flex) {
   Q1_HIP(hipMalloc(&W.p, b));
   Q1_HIP(hipMalloc(&W.q, b));
   Q1_HIP(hipMalloc(&W.w, b));
-  if (flex) {
-    Q1_HIP(hipMalloc(&W.r_old, b));
-    Q1_HIP(hipMalloc(&W.z, b));
-  }
+  if (flex) Q1_HIP(hipMalloc(&W.z, b));
   Q1_HIP(hipMalloc(&W.part, 8 * kMaxRB * sizeof(double)));
   Q1_HIP(hipMalloc(&W.dparts, kMaxDotParts * sizeof(double)));
   Q1_HIP(hipMalloc(&W.st, sizeof(Status)));
@@ -729,11 +698,11 @@ int pcg_t(Op &op, int pc, const T *b, T *x, double rtol, int maxit, q1_stats *st
           if ((rc = launch_apply(op, p, q, s, &W.st->done))) return rc;
           hipLaunchKernelGGL((k_dot<T>), dim3(nb), dim3(kRT), 0, s, n, p, q, part_pq, W.st);
         }
-        hipLaunchKernelGGL((k_pcg_update<T, false>), dim3(nb), dim3(kRT), 0, s, n, p, q, w, x, r,
-                           nullptr, fused_dot ? W.dparts : part_pq, npq, k,
+        hipLaunchKernelGGL((k_pcg_update<T>), dim3(nb), dim3(kRT), 0, s, n, p, q, w, x, r,
+                           fused_dot ? W.dparts : part_pq, npq, k,
                            part_rho[(k + 1) & 1], part_rr, W.st);
         if (!fused_dir || j + 1 == m)
-          hipLaunchKernelGGL((k_pcg_direction<T>), dim3(nb), dim3(kRT), 0, s, n, r, w, nullptr, p,
+          hipLaunchKernelGGL((k_pcg_direction<T>), dim3(nb), dim3(kRT), 0, s, n, r, w, p,
                              part_rho[(k + 1) & 1], part_rr, tol2, k + 1, maxit, W.st);
         while (next_snap < snap.n && snap.iters[next_snap] == k + 1)
           Q1_HIP(hipMemcpyAsync(snap.dst[next_snap++], x, size_t(n) * sizeof(T),
@@ -1022,12 +991,12 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
             hipLaunchKernelGGL((k_dot<float>), dim3(nb), dim3(kRT), 0, s, n, p, q, part_pq,
                                W.st);
           }
-          hipLaunchKernelGGL((k_pcg_update<double, false, float>), dim3(nb), dim3(kRT), 0, s, n,
-                             p, q, w, x, r, nullptr, fused_dot ? W.dparts : part_pq, npq, k,
+          hipLaunchKernelGGL((k_pcg_update<double, float>), dim3(nb), dim3(kRT), 0, s, n,
+                             p, q, w, x, r, fused_dot ? W.dparts : part_pq, npq, k,
                              part_rho[(k + 1) & 1], part_rr, W.st);
           if (!fused_dir || j + 1 == m)
             hipLaunchKernelGGL((k_pcg_direction<double, float>), dim3(nb), dim3(kRT), 0, s, n, r,
-                               w, nullptr, p, part_rho[(k + 1) & 1], part_rr, thr / bb, k + 1,
+                               w, p, part_rho[(k + 1) & 1], part_rr, thr / bb, k + 1,
                                maxit, W.st);
         }
         Q1_HIP(hipGetLastError());
@@ -1064,7 +1033,7 @@ int mpcg_t(Op &A64, Op &A32, const double *b, double *x, double rtol, double del
       // continue from the true residual, keeping p: beta = rho(new r) / rho_{k-1}
       hipLaunchKernelGGL(k_clear_done, dim3(1), dim3(1), 0, s, W.st);
       hipLaunchKernelGGL((k_pcg_direction<double, float>), dim3(nb), dim3(kRT), 0, s, n, r, w,
-                         nullptr, p, part_rho[k & 1], part_rr, 0.0, k, maxit + 1, W.st);
+                         p, part_rho[k & 1], part_rr, 0.0, k, maxit + 1, W.st);
       Q1_HIP(hipGetLastError());
     }
   }

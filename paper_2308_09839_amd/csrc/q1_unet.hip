@@ -42,7 +42,7 @@ constexpr int kInC = 8;  // stored input channels (2 used)
 struct Layer {
   LayerSpec s;
   int64_t wo = 0, bo = 0;
-  int ngroups = 0, nchunks = 0, ngroups_b = 0, nchunks_b = 0;
+  int nchunks = 0, nchunks_b = 0;
   bf16 *wp = nullptr, *wq = nullptr;
 };
 
@@ -163,7 +163,6 @@ int layer_forward(UNet &n, int l, int nb, hipStream_t s) {
   c.cin = L.s.cin;
   c.g = n.grid(L.s.level, nb);
   c.wp = L.wp;
-  c.ngroups = L.ngroups;
   c.nchunks = L.nchunks;
   c.cout = L.s.cout;
   c.bias = n.theta + L.bo;
@@ -182,7 +181,6 @@ int layer_backward_data(UNet &n, int l, int nb, const bf16 *g, Slice mask, bf16 
   c.cin = L.s.cout;
   c.g = n.grid(L.s.level, nb);
   c.wp = L.wq;
-  c.ngroups = L.ngroups_b;
   c.nchunks = L.nchunks_b;
   c.cout = L.s.cin;
   c.mask = mask;
@@ -517,9 +515,7 @@ int q1_unet_create(q1_unet **out, int D, int H, int W, int batch, uint64_t seed,
     L.wo = off;
     L.bo = off + int64_t(27) * L.s.cin_real * L.s.cout;
     off = L.bo + L.s.cout;
-    L.ngroups = 27 * L.s.cin / 8;
     L.nchunks = conv_ksteps(L.s.cin);
-    L.ngroups_b = 27 * L.s.cout / 8;
     L.nchunks_b = conv_ksteps(L.s.cout);
     ConvWArgs w;
     w.cin = L.s.cin;
@@ -702,7 +698,7 @@ int q1_conv3d_forward(int B, int D, int H, int W, const uint16_t *a_d, int ca, i
   Q1_CHECK(conv_cout_ok(cout), Q1_EUNSUPPORTED, "q1_conv3d_forward: cout %d", cout);
   Q1_CHECK(ca + cb <= 96, Q1_EUNSUPPORTED, "q1_conv3d_forward: more than 96 input channels");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int cin = ca + cb, ngroups = 27 * cin / 8, nchunks = conv_ksteps(cin);
+  const int cin = ca + cb, nchunks = conv_ksteps(cin);
   const PGrid g(B, D, H, W);
   TmpBuf wp, xp, yp;
   Q1_HIP(hipMalloc(&wp.p, size_t(nchunks) * 4 * cout * 8 * sizeof(bf16)));
@@ -719,7 +715,6 @@ int q1_conv3d_forward(int B, int D, int H, int W, const uint16_t *a_d, int ca, i
   c.cin = cin;
   c.g = g;
   c.wp = static_cast<bf16 *>(wp.p);
-  c.ngroups = ngroups;
   c.nchunks = nchunks;
   c.cout = cout;
   c.bias = bias_d;
@@ -738,7 +733,7 @@ int q1_conv3d_backward_data(int B, int D, int H, int W, const uint16_t *gy_d, in
            Q1_EINVAL, "q1_conv3d_backward_data: bad sizes");
   Q1_CHECK(conv_cout_ok(cin), Q1_EUNSUPPORTED, "q1_conv3d_backward_data: cin %d", cin);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int ngroups = 27 * cout / 8, nchunks = conv_ksteps(cout);
+  const int nchunks = conv_ksteps(cout);
   const PGrid g(B, D, H, W);
   TmpBuf wq, gp, xp;
   Q1_HIP(hipMalloc(&wq.p, size_t(nchunks) * 4 * cin * 8 * sizeof(bf16)));
@@ -755,7 +750,6 @@ int q1_conv3d_backward_data(int B, int D, int H, int W, const uint16_t *gy_d, in
   c.cin = cout;
   c.g = g;
   c.wp = static_cast<bf16 *>(wq.p);
-  c.ngroups = ngroups;
   c.nchunks = nchunks;
   c.cout = cin;
   c.o32 = static_cast<float *>(xp.p);
