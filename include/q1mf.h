@@ -358,9 +358,12 @@ int q1_mpcg(q1_op *op64, q1_op *op32, const double *b_d, double *x_d, double rto
  * nprob*nrhs records.  Each problem gets a share of the co-resident
  * wavefronts in proportion to its expected work (elements^(4/3)) and
  * synchronises them with its own barrier, two per iteration: the direction
- * update runs inside the apply and p^T A p comes from element energies.
- * Workspace (per problem: nrhs * 6 FP64 vectors, tile bookkeeping) is
- * allocated and freed by the call.  Returns the worst status over all solves;
+ * update runs inside the apply and p^T A p comes from the tiles' sums.
+ * Workspace (per problem and right-hand side: five FP64 vectors, and A p with
+ * one entry for each tile that holds a free node, about two vectors more;
+ * the inverse diagonal, partial sums) is allocated and freed by the call.  The
+ * operators themselves hold the map of those entries from their creation on:
+ * 8 bytes per tile entry of a node (about two per node) and 4 per node.  Returns the worst status over all solves;
  * Q1_EUNSUPPORTED for other operators or when more problems than co-resident
  * wavefronts are given.  Synchronises `stream`. */
 int q1_batched_pcg(int nprob, q1_op *const *ops, int nrhs, const double *const *b_d,
@@ -377,8 +380,9 @@ int q1_batched_pcg(int nprob, q1_op *const *ops, int nrhs, const double *const *
  * continue from it with p kept.  st[k].outer_iters counts the refreshes and
  * st[k].rel_res is the true relative residual of the last refresh.  Device
  * memory per problem: FP32 copies of the geometry and coefficients, and per
- * right-hand side three FP32 vectors (two direction buffers, q) and four FP64
- * ones (b, x, r, the refresh apply's output), allocated and freed by the call.
+ * right-hand side two FP32 vectors (direction buffers), three FP64 ones (b, x,
+ * r), and q in FP32 and the refresh apply's output in FP64 with an entry for
+ * each tile that holds a free node, allocated and freed by the call.
  * Returns Q1_EINVAL for delta outside (0, 1); otherwise as q1_batched_pcg. */
 int q1_batched_mpcg(int nprob, q1_op *const *ops, int nrhs, const double *const *b_d,
                     double *const *x_d, double rtol, double delta, int maxit, q1_stats *st,

@@ -48,7 +48,7 @@ namespace q1 {
 
 namespace {
 
-constexpr int kW = 64;            // one wavefront per workgroup
+constexpr int kW = 64;            // lanes of a wavefront
 constexpr int kRmax = 4;
 constexpr uint32_t kFixedBitB = 0x40000000u;
 constexpr uint32_t kIdMaskB = 0x3fffffffu;
@@ -67,7 +67,9 @@ constexpr unsigned kSpinLimit = 1u << 26;  // barrier polls before giving up
 // write one tile together (one step of 64 elements each, the right-hand sides in turn, so that
 // three fit a SIMD), and one otherwise (general elements keep their geometry for all sides at
 // once, in 256 and more registers).  Twelve problems of 16^3 to 40^3 with four right-hand sides:
-// 74 us per iteration with one wave per workgroup, 57 with four.
+// 74 us per iteration with one wave per workgroup, 57 with four.  Three waves per SIMD are asked
+// for: that spills 2 registers with four FP64 sides and 2 to 8 in the mixed form with two to
+// four; two waves per SIMD would spill none, and run two thirds of the workgroups.
 template <int R, int NW>
 struct Lanes {
   static constexpr int NLW = kW / R;    // nodes per instruction of a wave

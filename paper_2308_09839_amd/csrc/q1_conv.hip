@@ -12,11 +12,11 @@
 // groups of 8 channels: group g = tap * Cin/8 + cg.  The 16x16x32 instruction
 // takes, per lane l, 8 consecutive K of row l%16 of the first operand and 8
 // consecutive K of column l%16 of the second, K-block l/16; so each lane
-// loads one group (16 bytes) of the packed weights for its output channel and
-// one group of the shifted input voxel for its voxel, the shift of group g
-// coming from a per-block table in LDS.  The result holds 4 consecutive
-// output channels of one voxel per lane.  A wavefront owns a 4 x 4 x 4 voxel
-// tile: 16 voxels per instruction column block, 4 z-slices.
+// reads one group (16 bytes) of the packed weights for its output channel and
+// one group of the shifted input voxel for its voxel, at an address that it
+// holds in a register per K-step.  The result holds 4 consecutive output
+// channels of one voxel per lane.  A wavefront owns two 8-voxel rows (16 voxels,
+// the columns of an instruction) in each of a tile's 4 z-slices.
 //
 // Backward-data is the same kernel: the adjoint of a 3x3x3 correlation is
 // the correlation with the tap-reversed kernel and transposed channel blocks,

@@ -40,7 +40,8 @@ struct TileMap {
   int64_t n_entries = 0;          // entries of nodes (node_ptr[n_tiles])
   int32_t *tile_step = nullptr;   // [n_tiles+1] step range of each tile
   uint16_t *lconn = nullptr;      // [n_steps*64][8] corner indices into the tile list (0xffff: empty)
-  void *coef_t = nullptr;         // cell coefficients in lane order [ncoef][n_steps*64]
+  void *coef_t = nullptr;         // cell coefficients in lane order [ncoef][n_steps*64]; with
+                                  // cells, of the cell's six tetrahedra: [6][ncoef][n_steps*64]
   int64_t n_reset = 0;            // shared or Dirichlet nodes, reset before each apply
   bool cells = false;             // tetrahedra in lane slots of one Kuhn cell each
   bool orphans = false;           // some node belongs to no element (and so to no tile)

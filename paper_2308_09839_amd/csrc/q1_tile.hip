@@ -1058,6 +1058,8 @@ __global__ __launch_bounds__(256) void k_apply_block_tet(
   }
   __syncthreads();
   if constexpr (CELLS) {
+    // (a box's tile has one step per wave with 3 DOF, two for the scalar kind: the next
+    // step's six or twelve coefficients are not worth their registers ahead of time)
     constexpr int NC = PH == 3 ? 2 : 1;
     for (int s = s0 + w; s < s1; s += 4) {
       const int64_t sl = int64_t(s) * kLanes + lane;
