@@ -329,7 +329,7 @@ __device__ __forceinline__ T qp_point(int r, const T (*sX)[QP<P>::NPTS],
 // coordinates: error of an FP64 apply against 80 bits, absolute coordinates -> here, order 2 on
 // 9 x 8 x 7 elements 9.3e-16 -> 1.6e-16, order 3 on 4 x 5 x 4 2.5e-15 -> 2.2e-15 (6.6e-16 and
 // 2.8e-15 with direct sums per point); FP32, order 2 on 33 x 29 x 41, 2.3e-6 -> 1.7e-7 (1.6e-6).
-// Its cost is 1.4%.
+// Its cost is 1 to 3%.
 //
 // What bounds it: the LDS turns (busy 71% of the time at order 2 in FP64), then the
 // gathers' cache accesses and FP64 issue.  FP64 Laplace, order 2 on 64^3 74 us, order 3 on
